@@ -19,108 +19,303 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // ------------------------------------------------------------ FP64 GEMM
 // C(m,n) = alpha sum_k A(m,k) w_k B(k,n) + beta C(m,n), A(m,k) = A[m*sam + k*sak],
-// B(k,n) = B[k*sbk + n*sbn], C(m,n) = C[m*scm + n*scn], w_k = wk[k] or 1.
-// FP64 matrix cores (16x16x4 FP64 MFMA, FP32 operands widened on load): a
-// workgroup computes a 64 x 64 tile, wavefront w the 32 x 32 quarter
-// (w >> 1, w & 1) as 2 x 2 MFMA blocks, K in steps of 16 through LDS with the
-// next step's operands loaded into registers while the current step's MFMAs
-// run.  With gridDim.z > 1 each z handles a K chunk and writes the raw sum to
-// C + z*split_stride (layout m*N + n); k_split_reduce finishes.
+// B(k,n) = B[k*sbk + n*sbn], C(m,n) = C[m*scm + n*scn], w_k = wk[k] or 1;
+// with FUSE the left operand is A + ca A2 (A2 laid out as A).
+//
+// Bound: the FP64 matrix cores (16x16x4 FP64 MFMA, 64 cycles each) for large
+// products, the latency of the loads for small ones.  An MFMA takes one double
+// per lane of either operand, so a wavefront that holds a 16 RB x 64 tile of C
+// asks the caches for at most 10 bytes per cycle: the operands go from global
+// memory (L1/L2) straight into registers, without LDS and without barriers,
+// the next D steps of 16 k loaded while the current step's products run.  Each
+// wavefront is a unit of work of its own (tile, K chunk); consecutive units
+// take the column tiles of one row tile, so that its A panel is read from HBM
+// once.  A lane of a k-contiguous operand reads 4 consecutive k.  With NAT it
+// trades them across the four 16-lane rows (MFMA s sums k0 + 4 s .. + 3, so the
+// sums run in ascending k whatever the layout); without, MFMA s sums the k's
+// k0 + s + 4 row, in either operand.  The MFMA's
+// rows are n and its columns m: a store instruction writes 16 consecutive m.
+// Measured on A Omega and A^T T at 20000 x 2000, 100 columns, FP32 A: 250
+// and 187 us, 32 and 43 TFLOP/s (64 x 64 tiles through LDS with two barriers
+// per 16 k before: 1.22 ms each); 20000 x 800 x 800 in FP64 486 us, 53 TFLOP/s
+// (1.1 ms before); 2000 x 50 x 500 13 us (75 before).
 typedef double d4 __attribute__((ext_vector_type(4)));
+// vectors at element alignment: the hardware takes them at any 4-byte boundary
+typedef float f4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef double d2e __attribute__((ext_vector_type(2), aligned(8)));
+typedef float f2e __attribute__((ext_vector_type(2), aligned(4)));
+constexpr int kGemmNB = 4;   // 16-column blocks of a wavefront's tile, at most
 
-template <typename TA, typename TB>
-__global__ __launch_bounds__(256) void k_gemm64(int M, int N, int K, int kchunk,
-                                               const TA* __restrict__ A, int64_t sam, int64_t sak,
-                                               const TB* __restrict__ B, int64_t sbk, int64_t sbn,
-                                               double* __restrict__ C, int64_t scm, int64_t scn,
-                                               int64_t split_stride, double alpha, double beta,
-                                               const double* __restrict__ wk) {
-  __shared__ double As[16][65];
-  __shared__ double Bs[16][65];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int wm = 32 * (wv >> 1), wn = 32 * (wv & 1);
-  const int kb = blockIdx.z * kchunk;
-  const int ke = min(K, kb + kchunk);
-  d4 acc[2][2];
+__device__ __forceinline__ void load4(const float* p, float (&x)[4]) {
+  const f4e v = *reinterpret_cast<const f4e*>(p);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int s = 0; s < 4; ++s) x[s] = v[s];
+}
+__device__ __forceinline__ void load4(const double* p, double (&x)[4]) {
+  const d2e v = *reinterpret_cast<const d2e*>(p), w = *reinterpret_cast<const d2e*>(p + 2);
+  x[0] = v[0]; x[1] = v[1]; x[2] = w[0]; x[3] = w[1];
+}
+__device__ __forceinline__ void load2(const float* p, float& x, float& y) {
+  const f2e v = *reinterpret_cast<const f2e*>(p);
+  x = v[0]; y = v[1];
+}
+__device__ __forceinline__ void load2(const double* p, double& x, double& y) {
+  const d2e v = *reinterpret_cast<const d2e*>(p);
+  x = v[0]; y = v[1];
+}
+
+// x[s] of lane row g (16 lanes each) <- x[g] of lane row s: halves of 32
+// lanes traded between registers s and s + 2, then rows of 16 between s and s + 1
+__device__ __forceinline__ void swap32(unsigned& a, unsigned& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0]; b = r[1];
+}
+__device__ __forceinline__ void swap16(unsigned& a, unsigned& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0]; b = r[1];
+}
+__device__ __forceinline__ void row_transpose(unsigned (&x)[4]) {
+  swap32(x[0], x[2]);
+  swap32(x[1], x[3]);
+  swap16(x[0], x[1]);
+  swap16(x[2], x[3]);
+}
+__device__ __forceinline__ void row_transpose(const float (&x)[4], double (&y)[4]) {
+  unsigned u[4];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (d4)0.0;
-  // consecutive threads take consecutive elements along whichever index has
-  // unit stride (k for the Gram-type products X^T Y of column-major X, Y;
-  // m or n otherwise), so every load instruction reads whole cache lines
-  const bool ak = (sak == 1 && sam != 1), bk = (sbk == 1 && sbn != 1);
-  double an[4], bn[4];
-  auto load = [&](int k0) __attribute__((always_inline)) {
+  for (int s = 0; s < 4; ++s) u[s] = __float_as_uint(x[s]);
+  row_transpose(u);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = tid + e * 256;
-      const int mm = ak ? (idx >> 4) : (idx & 63), ka = ak ? (idx & 15) : (idx >> 6);
-      const int nn = bk ? (idx >> 4) : (idx & 63), kb2 = bk ? (idx & 15) : (idx >> 6);
-      const int gka = k0 + ka, gkb = k0 + kb2;
-      an[e] = (m0 + mm < M && gka < ke) ? (double)A[(int64_t)(m0 + mm) * sam + (int64_t)gka * sak]
-                                        : 0.0;
-      bn[e] = (n0 + nn < N && gkb < ke)
-                  ? (double)B[(int64_t)gkb * sbk + (int64_t)(n0 + nn) * sbn] * (wk ? wk[gkb] : 1.0)
-                  : 0.0;
-    }
-  };
-  auto store = [&]() __attribute__((always_inline)) {
+  for (int s = 0; s < 4; ++s) y[s] = (double)__uint_as_float(u[s]);
+}
+__device__ __forceinline__ void row_transpose(const double (&x)[4], double (&y)[4]) {
+  unsigned lo[4], hi[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = tid + e * 256;
-      const int mm = ak ? (idx >> 4) : (idx & 63), ka = ak ? (idx & 15) : (idx >> 6);
-      const int nn = bk ? (idx >> 4) : (idx & 63), kb2 = bk ? (idx & 15) : (idx >> 6);
-      As[ka][mm] = an[e];
-      Bs[kb2][nn] = bn[e];
-    }
-  };
-  const int fi = lane & 15, fk = lane >> 4;   // MFMA operand: row/column fi, k fk
-  if (kb < ke) load(kb);
-  for (int k0 = kb; k0 < ke; k0 += 16) {
-    store();
-    __syncthreads();
-    if (k0 + 16 < ke) load(k0 + 16);
-#pragma unroll
-    for (int kk = 0; kk < 16; kk += 4) {
-      double a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = As[kk + fk][wm + 16 * i + fi];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = Bs[kk + fk][wn + 16 * j + fi];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
+  for (int s = 0; s < 4; ++s) {
+    lo[s] = (unsigned)__double2loint(x[s]);
+    hi[s] = (unsigned)__double2hiint(x[s]);
   }
-  // FP64 16x16 result layout: lane (fk, fi) holds rows fk + 4 v of column fi,
-  // so acc[i][j][v] = C(m0 + wm + 16 i + fk + 4 v, n0 + wn + 16 j + fi)
+  row_transpose(lo);
+  row_transpose(hi);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int s = 0; s < 4; ++s) y[s] = __hiloint2double((int)hi[s], (int)lo[s]);
+}
+
+constexpr int gemm64_depth(int RB, int NB) { return RB * NB == 1 ? 4 : (RB * NB <= 4 ? 2 : 1); }
+
+struct GemmArgs {
+  int M, N, K, kchunk, MT, NT, NBT, S;   // NBT: 16-column blocks of a tile
+  int64_t sam, sak, sbk, sbn, scm, scn, split_stride;
+  double alpha, beta, ca;
+};
+
+template <typename TA, typename TB, bool AKC, bool BKC, int RB, bool NAT, bool FUSE, int NB>
+__device__ __forceinline__ void gemm64_unit(const GemmArgs& g, const TA* __restrict__ A,
+                                            const TA* __restrict__ A2, const TB* __restrict__ B,
+                                            double* __restrict__ C, const double* __restrict__ wk,
+                                            int m0, int n0, int z) {
+  // steps in flight: as many as the registers of two wavefronts per SIMD hold
+  constexpr int D = gemm64_depth(RB, NB);
+  const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
+  const int kb = z * g.kchunk, ke = min(g.K, kb + g.kchunk);
+  // rows and columns past the edge read the last one: their products are
+  // never stored.  m-contiguous A with RB = 2: a lane reads the row pair
+  // (m0 + 2 fi, m0 + 2 fi + 1), so block i's row fi is m0 + 2 fi + i
+  constexpr bool PAIR = !AKC && RB == 2;
+  const bool full = m0 + 16 * RB <= g.M;
+  int64_t ra[RB], cb[NB];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+  for (int i = 0; i < RB; ++i) {
+    const int m = PAIR ? m0 + 2 * fi + i : m0 + 16 * i + fi;
+    ra[i] = (int64_t)min(m, g.M - 1) * (AKC ? g.sam : 1);
+  }
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+    cb[j] = (int64_t)min(n0 + 16 * j + fi, g.N - 1) * (BKC ? g.sbn : 1);
+  d4 acc[RB][NB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = (d4)0.0;
+  // k offset of MFMA s in this lane: ascending over the MFMAs, or as a
+  // k-contiguous operand is read
+  const auto ko = [&](int s) __attribute__((always_inline)) {
+    return NAT ? 4 * s + fk : 4 * fk + s;
+  };
+  struct Stage {
+    TA a[RB][4], a2[FUSE ? RB : 1][4];
+    TB b[NB][4];
+    double w[4];
+  };
+  Stage st[D];
+  auto load_side_a = [&](const TA* P, TA (&x)[RB][4], int k0) __attribute__((always_inline)) {
+    if constexpr (AKC) {
+#pragma unroll
+      for (int i = 0; i < RB; ++i) load4(P + ra[i] + k0 + 4 * fk, x[i]);
+    } else if constexpr (PAIR) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const TA* p = P + (int64_t)(k0 + ko(s)) * g.sak;
+        if (full) {
+          load2(p + ra[0], x[0][s], x[1][s]);
+        } else {
+          x[0][s] = p[ra[0]];
+          x[1][s] = p[ra[1]];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < RB; ++i) x[i][s] = P[ra[i] + (int64_t)(k0 + ko(s)) * g.sak];
+    }
+  };
+  auto load = [&](Stage& t, int k0) __attribute__((always_inline)) {
+    load_side_a(A, t.a, k0);
+    if constexpr (FUSE) load_side_a(A2, t.a2, k0);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if constexpr (BKC) {
+        load4(B + cb[j] + k0 + 4 * fk, t.b[j]);
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) t.b[j][s] = B[cb[j] + (int64_t)(k0 + ko(s)) * g.sbk];
+      }
+    }
+    if (wk != nullptr) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) t.w[s] = wk[k0 + ko(s)];
+    }
+  };
+  // the last, partial 16 k: both operands are 0 past ke
+  auto load_tail = [&](Stage& t, int k0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int ka = k0 + (AKC ? 4 * fk + s : ko(s));
+      const int kb2 = k0 + (BKC ? 4 * fk + s : ko(s));
+      const int kw = k0 + ko(s);
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        const int64_t o = ra[i] + (int64_t)min(ka, ke - 1) * (AKC ? 1 : g.sak);
+        t.a[i][s] = ka < ke ? A[o] : (TA)0;
+        if constexpr (FUSE) t.a2[i][s] = ka < ke ? A2[o] : (TA)0;
+      }
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        t.b[j][s] = kb2 < ke ? B[cb[j] + (int64_t)min(kb2, ke - 1) * (BKC ? 1 : g.sbk)] : (TB)0;
+      t.w[s] = (wk != nullptr && kw < ke) ? wk[kw] : 0.0;
+    }
+  };
+  double a[RB][4], b[NB][4];
+  auto take = [&](const Stage& t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      TA x[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        x[s] = t.a[i][s];
+        if constexpr (FUSE) x[s] = fma(g.ca, (double)t.a2[i][s], (double)x[s]);
+      }
+      if constexpr (AKC && NAT) {
+        row_transpose(x, a[i]);
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) a[i][s] = (double)x[s];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if constexpr (BKC && NAT) {
+        row_transpose(t.b[j], b[j]);
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) b[j][s] = (double)t.b[j][s];
+      }
+      if (wk != nullptr) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) b[j][s] *= t.w[s];
+      }
+    }
+  };
+  auto products = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[j][s], a[i][s], acc[i][j], 0, 0, 0);
+  };
+  const int steps = ke > kb ? (ke - kb) / 16 : 0;
+#pragma unroll
+  for (int u = 0; u < D; ++u)
+    if (u < steps) load(st[u], kb + 16 * u);
+  for (int t = 0; t < steps; t += D) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      if (t + u < steps) {
+        take(st[u]);
+        if (t + u + D < steps) load(st[u], kb + 16 * (t + u + D));
+        products();
+      }
+    }
+  }
+  if (kb + 16 * steps < ke) {
+    load_tail(st[0], kb + 16 * steps);
+    take(st[0]);
+    products();
+  }
+  // FP64 16x16 result layout: lane (fk, fi) holds rows (n) fk + 4 v of column (m) fi
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    const int m = PAIR ? m0 + 2 * fi + i : m0 + 16 * i + fi;
+    if (m >= g.M) continue;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int gm = m0 + wm + 16 * i + fk + 4 * v, gn = n0 + wn + 16 * j + fi;
-        if (gm < M && gn < N) {
-          if (gridDim.z > 1) {
-            C[blockIdx.z * split_stride + (int64_t)gm * N + gn] = acc[i][j][v];
+        const int n = n0 + 16 * j + fk + 4 * v;
+        if (n < g.N) {
+          if (g.S > 1) {
+            C[z * g.split_stride + (int64_t)n * g.M + m] = acc[i][j][v];
           } else {
-            double* c = C + (int64_t)gm * scm + (int64_t)gn * scn;
-            *c = (beta == 0.0) ? alpha * acc[i][j][v] : fma(alpha, acc[i][j][v], beta * *c);
+            double* c = C + (int64_t)m * g.scm + (int64_t)n * g.scn;
+            *c = (g.beta == 0.0) ? g.alpha * acc[i][j][v]
+                                 : fma(g.alpha, acc[i][j][v], g.beta * *c);
           }
         }
       }
+  }
 }
 
-// C = alpha * sum_z ws[z] + beta C over the S split-K partials.  A workgroup
-// covers 16 outputs with 16 groups of lanes; group g adds the partials
-// z = g, g + 16, ... with eight loads in flight, the groups are combined in
-// LDS in a fixed order (for few outputs S is large: up to 1024).
+// With S > 1 the unit of K chunk z writes its raw sum to C + z*split_stride
+// (layout n*M + m) and k_split_reduce finishes.
+template <typename TA, typename TB, bool AKC, bool BKC, int RB, bool NAT, bool FUSE>
+__global__ __launch_bounds__(256, 2) void k_gemm64(GemmArgs g, const TA* __restrict__ A,
+                                                   const TA* __restrict__ A2,
+                                                   const TB* __restrict__ B,
+                                                   double* __restrict__ C,
+                                                   const double* __restrict__ wk) {
+  // workgroups go to the 8 XCDs in turn: give each XCD a contiguous range of
+  // units, so that the units that share operands share an L2
+  const int nwg = gridDim.x, per = nwg / 8, rem = nwg % 8;
+  const int x = blockIdx.x % 8, q = blockIdx.x / 8;
+  const int wg = x * per + min(x, rem) + q;
+  const int u = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
+  const int nt = u % g.NT, mt = (u / g.NT) % g.MT, z = u / (g.NT * g.MT);
+  if (z >= g.S) return;
+  const int m0 = mt * 16 * RB, n0 = nt * 16 * g.NBT;
+  const int nb = min(g.NBT, (g.N - n0 + 15) / 16);
+  if (nb == 4) gemm64_unit<TA, TB, AKC, BKC, RB, NAT, FUSE, 4>(g, A, A2, B, C, wk, m0, n0, z);
+  else if (nb == 3) gemm64_unit<TA, TB, AKC, BKC, RB, NAT, FUSE, 3>(g, A, A2, B, C, wk, m0, n0, z);
+  else if (nb == 2) gemm64_unit<TA, TB, AKC, BKC, RB, NAT, FUSE, 2>(g, A, A2, B, C, wk, m0, n0, z);
+  else gemm64_unit<TA, TB, AKC, BKC, RB, NAT, FUSE, 1>(g, A, A2, B, C, wk, m0, n0, z);
+}
+
+// C = alpha * sum_z ws[z] + beta C over the S split-K partials (layout
+// n*M + m).  A workgroup covers 16 outputs with 16 groups of lanes; group g
+// adds the partials z = g, g + 16, ... with eight loads in flight, the groups
+// are combined in LDS in a fixed order (for few outputs S is large: up to 1024).
 constexpr int kSrOut = 16;
 __global__ __launch_bounds__(256) void k_split_reduce(int M, int N, int S,
                                                       const double* __restrict__ ws,
@@ -148,7 +343,7 @@ __global__ __launch_bounds__(256) void k_split_reduce(int M, int N, int S,
     double s = 0.0;
 #pragma unroll
     for (int h = 0; h < G; ++h) s += part[h][o];
-    const int m = (int)(idx / N), n = (int)(idx % N);
+    const int n = (int)(idx / M), m = (int)(idx % M);
     double* c = C + (int64_t)m * scm + (int64_t)n * scn;
     *c = (beta == 0.0) ? alpha * s : fma(alpha, s, beta * *c);
   }
@@ -1281,38 +1476,155 @@ __global__ void k_eig_vectors(const double* __restrict__ V, int R, const int* __
 
 }  // namespace
 
+// Tile (16 RB rows, 16 NBT columns) and K split of k_gemm64.  A unit's step of
+// 16 k costs a SIMD its MFMAs (256 RB NBT cycles) or, where that is more, its
+// share of the CU's address unit, which four SIMDs use and which a 16 x 16
+// operand block holds for 64 cycles (k-contiguous FP32, 16 rows of 64 bytes)
+// to 128 (FP64); a unit alone on its SIMD waits for its
+// loads besides (about 1400 cycles for the steps in flight).  1024 SIMDs take
+// the units in turn, a unit starts with about 2500 cycles of latency, and a
+// split adds a launch and the partial sums' way through the caches.  The
+// cheapest shape that the partial-sum buffer holds is taken: 2000 x 100 x 20000
+// (A^T T, FP32 A) 187 us with 16 chunks of 32 x 64 tiles, 236 with 25 (a fourth
+// turn of the SIMDs for the last units); 6000 x 300 x 6000 418 us unsplit, 470
+// with 10 chunks.
+// Products of at most 64 rows or columns (the factors of small ranks) sum in
+// ascending k and split K by the count of 64 x 64 tiles, whatever the tile
+// here: PCG runs of 25 and more iterations carry a last-bit change of the
+// factor into the eighth digit of their iterates, and those of low-rank
+// factors are that long, so these keep one order of summation.
+struct GemmShape {
+  int RB, NBT, S, kchunk;
+  bool nat;
+};
+static GemmShape gemm64_shape(int M, int N, int K, double ta_a, double ta_b, size_t split_elems) {
+  const int nblk = (N + 15) / 16;
+  GemmShape best{1, std::min(kGemmNB, nblk), 1, std::max(16, (K + 15) / 16 * 16), true};
+  if (K <= 0) return best;
+  const bool fixed = std::min(M, N) <= 64;
+  int s_lo = 1, s_hi = 64;
+  if (fixed) {
+    const int tm = (M + 63) / 64, tn = (N + 63) / 64;
+    int S = 1;
+    if (K > 256 && split_elems > 0) {
+      S = std::min((K + 127) / 128, std::max(1, 1024 / (tm * tn)));
+      while (S > 1 && (size_t)S * M * N > split_elems) --S;
+    }
+    s_lo = s_hi = S;
+  }
+  double best_us = 1e300;
+  for (int RB = 1; RB <= 2; ++RB) {
+    const int64_t MT = (M + 16 * RB - 1) / (16 * RB);
+    for (int NB = 1; NB <= kGemmNB; NB *= 2) {
+      const int64_t NT = (nblk + NB - 1) / NB;
+      const double mfma = 256.0 * RB * NB;
+      const double busy = 1.12 * std::max(mfma, 256.0 * (ta_a * RB + ta_b * NB));
+      const double alone = std::max(busy, (mfma + 1400.0) / gemm64_depth(RB, NB));
+      int last_kc = -1;
+      for (int S = s_lo; S <= s_hi; ++S) {
+        if (!fixed && S > 1 && (size_t)S * M * N > split_elems) break;
+        const int kc = ((K + S - 1) / S + 15) / 16 * 16;
+        if (!fixed && S > 1 && kc < 64) break;
+        if (kc == last_kc) continue;
+        last_kc = kc;
+        const int Se = (K + kc - 1) / kc;
+        const double units = (double)MT * NT * Se;
+        const double w = units / 1024.0;
+        const double turns = w > 1.0 ? 0.5 * (std::ceil(0.98 * w) + w + 0.35) : 1.0;
+        double us = (turns * (kc / 16) * (units > 1024 ? busy : alone) + 2500.0) / 2400.0;
+        if (Se > 1) us += 4.0 + 2.0 * Se * 8.0 * (double)M * N / 3e6;
+        if (us < best_us) {
+          best_us = us;
+          best = GemmShape{RB, std::min(NB, nblk), Se, kc, fixed};
+        }
+      }
+    }
+  }
+  return best;
+}
+
 nys_status gemm64(hipStream_t st, int M, int N, int K, const void* A, bool a_f32, int64_t sam,
                   int64_t sak, const void* B, bool b_f32, int64_t sbk, int64_t sbn, double* C,
                   int64_t scm, int64_t scn, double alpha, double beta, double* split_ws,
-                  size_t split_ws_elems, const double* wk) {
+                  size_t split_ws_elems, const double* wk, const double* A2, double ca) {
   if (M <= 0 || N <= 0) return NYS_OK;
-  const int tm = (M + 63) / 64, tn = (N + 63) / 64;
-  // split K (chunks of >= 128) until about four workgroups per CU are busy
-  int S = 1;
-  if (K > 256 && split_ws != nullptr) {
-    S = std::min((K + 127) / 128, std::max(1, 1024 / (tm * tn)));
-    while (S > 1 && (size_t)S * M * N > split_ws_elems) --S;
+  if (scm != 1 && scn == 1) {
+    // row-major C: the kernel stores along m, so form C^T = B^T A^T
+    if (A2 != nullptr) return NYS_ERR_INVALID;
+    std::swap(M, N);
+    std::swap(A, B);
+    std::swap(a_f32, b_f32);
+    std::swap(sam, sbn);
+    std::swap(sak, sbk);
+    std::swap(scm, scn);
   }
-  int kchunk = (K + S - 1) / S;
-  kchunk = (kchunk + 15) / 16 * 16;
-  S = std::max(1, (K + kchunk - 1) / kchunk);
-  dim3 grid(tn, tm, S);
-  double* out = S > 1 ? split_ws : C;
-  const int64_t sstride = (int64_t)M * N;
-#define NYS_GEMM(TA, TB)                                                                     \
-  hipLaunchKernelGGL((k_gemm64<TA, TB>), grid, dim3(256), 0, st, M, N, K, kchunk,            \
-                     static_cast<const TA*>(A), sam, sak, static_cast<const TB*>(B), sbk, sbn, \
-                     out, scm, scn, sstride, alpha, beta, wk)
-  if (a_f32 && b_f32) NYS_GEMM(float, float);
-  else if (a_f32) NYS_GEMM(float, double);
-  else if (b_f32) NYS_GEMM(double, float);
-  else NYS_GEMM(double, double);
+  if ((sam != 1 && sak != 1) || (sbk != 1 && sbn != 1)) return NYS_ERR_INVALID;
+  // (a 1 x 1 B has both strides 1 and takes either form)
+  const bool akc = sak == 1, bkc = sbk == 1 && !(A2 != nullptr && sbn == 1);
+  const GemmShape sh = gemm64_shape(M, N, K, akc ? (a_f32 ? 1.0 : 2.0) : 1.0,
+                                    bkc ? (b_f32 ? 1.0 : 2.0) : 1.5,
+                                    split_ws != nullptr ? split_ws_elems : 0);
+  GemmArgs g;
+  g.M = M; g.N = N; g.K = K;
+  g.kchunk = sh.kchunk;
+  g.MT = (M + 16 * sh.RB - 1) / (16 * sh.RB);
+  g.NBT = sh.NBT;
+  g.NT = ((N + 15) / 16 + sh.NBT - 1) / sh.NBT;
+  g.S = sh.S;
+  g.sam = sam; g.sak = sak; g.sbk = sbk; g.sbn = sbn; g.scm = scm; g.scn = scn;
+  g.split_stride = (int64_t)M * N;
+  g.alpha = alpha; g.beta = beta; g.ca = ca;
+  const int64_t units = (int64_t)g.MT * g.NT * g.S;
+  if (units > (int64_t)1 << 30) return NYS_ERR_INVALID;
+  const dim3 grid((unsigned)((units + 3) / 4));
+  double* out = g.S > 1 ? split_ws : C;
+#define NYS_GEMM1(TA, TB, AK, BK, RBV, NT, FU)                                                    \
+  hipLaunchKernelGGL((k_gemm64<TA, TB, AK, BK, RBV, NT, FU>), grid, dim3(256), 0, st, g,          \
+                     static_cast<const TA*>(A), reinterpret_cast<const TA*>(A2),                  \
+                     static_cast<const TB*>(B), out, wk)
+  // without a k-contiguous operand there is one order
+#define NYS_GEMM(TA, TB, AK, BK, FU)                                                              \
+  do {                                                                                            \
+    constexpr bool kOne = !(AK) && !(BK);                                                         \
+    if (sh.nat || kOne) {                                                                         \
+      if (sh.RB == 2) NYS_GEMM1(TA, TB, AK, BK, 2, true, FU);                                     \
+      else NYS_GEMM1(TA, TB, AK, BK, 1, true, FU);                                                \
+    } else {                                                                                      \
+      if (sh.RB == 2) NYS_GEMM1(TA, TB, AK, BK, 2, kOne, FU);                                     \
+      else NYS_GEMM1(TA, TB, AK, BK, 1, kOne, FU);                                                \
+    }                                                                                             \
+  } while (0)
+  if (!a_f32 && !b_f32) {
+    if (A2 != nullptr) {
+      if (akc || bkc) return NYS_ERR_INVALID;
+      NYS_GEMM(double, double, false, false, true);
+    } else if (akc && bkc) {
+      NYS_GEMM(double, double, true, true, false);
+    } else if (akc) {
+      NYS_GEMM(double, double, true, false, false);
+    } else if (bkc) {
+      NYS_GEMM(double, double, false, true, false);
+    } else {
+      NYS_GEMM(double, double, false, false, false);
+    }
+  } else if (A2 != nullptr || !bkc) {
+    return NYS_ERR_INVALID;
+  } else if (a_f32 && b_f32) {   // T^T T, X X^T
+    if (!akc) return NYS_ERR_INVALID;
+    NYS_GEMM(float, float, true, true, false);
+  } else if (a_f32) {            // A Omega, A^T T
+    if (akc) NYS_GEMM(float, double, true, true, false);
+    else NYS_GEMM(float, double, false, true, false);
+  } else {
+    return NYS_ERR_INVALID;
+  }
 #undef NYS_GEMM
+#undef NYS_GEMM1
   if (hipGetLastError() != hipSuccess) return NYS_ERR_HIP;
-  if (S > 1) {
+  if (g.S > 1) {
     const int64_t tot = (int64_t)M * N;
-    hipLaunchKernelGGL(k_split_reduce, dim3((unsigned)((tot + kSrOut - 1) / kSrOut)), dim3(256), 0,
-                       st, M, N, S, split_ws, C, scm, scn, alpha, beta);
+    hipLaunchKernelGGL(k_split_reduce, dim3((unsigned)((tot + kSrOut - 1) / kSrOut)), dim3(256), 0, st,
+                       M, N, g.S, split_ws, C, scm, scn, alpha, beta);
     if (hipGetLastError() != hipSuccess) return NYS_ERR_HIP;
   }
   return NYS_OK;

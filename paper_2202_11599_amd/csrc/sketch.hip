@@ -739,15 +739,20 @@ struct CoreWs {
   size_t split_elems;
 };
 
-size_t core_split_elems(int64_t d, int r) {
-  return std::max<size_t>((size_t)16 * r * r, (size_t)4 * d * std::min(r, 64));
+// Doubles of the split-K partial sums.  From rank 65 on at least 8 MB and 32
+// (16 above rank 256) partials of an r x r product, which a product with few
+// tiles wants; where that does not fit a caller's workspace, the least (small).
+size_t core_split_elems(int64_t d, int r, bool small) {
+  const size_t least = std::max<size_t>((size_t)16 * r * r, (size_t)4 * d * std::min(r, 64));
+  if (small || r <= 64) return least;
+  return std::max<size_t>({least, (size_t)1 << 20, (size_t)(r <= 256 ? 32 : 16) * r * r});
 }
 
-size_t core_ws_bytes_of(int64_t d, int r) {
+size_t core_ws_bytes_of(int64_t d, int r, bool small = false) {
   const size_t rr = align_up(sizeof(double) * (size_t)r * r);
   const size_t dr = align_up(sizeof(double) * (size_t)d * r);
   const size_t jac = align_up(sizeof(double) * jacobi_ws_doubles(r));
-  const size_t split = align_up(sizeof(double) * core_split_elems(d, r));
+  const size_t split = align_up(sizeof(double) * core_split_elems(d, r, small));
   return 6 * rr + dr + jac + split + align_up(sizeof(double) * 1024) + 4096 + 4096;
 }
 
@@ -755,9 +760,13 @@ nys_status core_workspace(nys_ctx ctx, int64_t d, int r, CoreWs* w) {
   const size_t rr = align_up(sizeof(double) * (size_t)r * r);
   const size_t dr = align_up(sizeof(double) * (size_t)d * r);
   const size_t jac = align_up(sizeof(double) * jacobi_ws_doubles(r));
-  w->split_elems = core_split_elems(d, r);
+  bool small = false;
+  if (ctx->core_ws.reserve(core_ws_bytes_of(d, r)) != NYS_OK) {
+    small = true;
+    NYS_TRY(ctx->core_ws.reserve(core_ws_bytes_of(d, r, true)));
+  }
+  w->split_elems = core_split_elems(d, r, small);
   const size_t split = align_up(sizeof(double) * w->split_elems);
-  NYS_TRY(ctx->core_ws.reserve(core_ws_bytes_of(d, r)));
   char* p = static_cast<char*>(ctx->core_ws.ptr);
   auto take = [&](size_t b) { char* q = p; p += b; return reinterpret_cast<double*>(q); };
   w->GY = take(rr);
@@ -893,11 +902,19 @@ nys_status nys_core(nys_ctx ctx, nys_factor F, double test_mu, int* above) {
     nu *= 10.0;
   }
   NYS_TRY(trinv_upper(st, w.M, r, r, w.Cinv, r));
-  // B = (Y + nu Omega) C^-1 : two GEMMs into Bm (d x r col-major)
-  NYS_TRY(gemm64(st, (int)d, r, r, Y, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, 1.0, 0.0,
-                 w.split, w.split_elems));
-  NYS_TRY(gemm64(st, (int)d, r, r, Om, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, nu, 1.0,
-                 w.split, w.split_elems));
+  // B = Y_nu C^-1 into Bm (d x r col-major).  From rank 65 on Y_nu = Y + nu
+  // Omega is formed as Y is read (half the products: 0.6 ms instead of 1.0
+  // at 20000 x 800); up to 64 the two products are added, the order of
+  // summation that small ranks keep (see gemm64_shape)
+  if (r > 64) {
+    NYS_TRY(gemm64(st, (int)d, r, r, Y, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, 1.0, 0.0,
+                   w.split, w.split_elems, nullptr, Om, nu));
+  } else {
+    NYS_TRY(gemm64(st, (int)d, r, r, Y, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, 1.0, 0.0,
+                   w.split, w.split_elems));
+    NYS_TRY(gemm64(st, (int)d, r, r, Om, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, nu, 1.0,
+                   w.split, w.split_elems));
+  }
   // G = B^T B, eigendecomposition G = V Sigma^2 V^T
   NYS_TRY(gemm64(st, r, r, (int)d, w.Bm, false, d, 1, w.Bm, false, 1, d, w.G, r, 1, 1.0, 0.0,
                  w.split, w.split_elems));
@@ -1143,6 +1160,13 @@ Sk32Shape sk32_shape(int64_t n, int64_t d, int m, int num_cu, bool bf) {
   return s;
 }
 
+// Doubles for the split-K partials of T = A Omega in FP64: four copies of T, at
+// most 64 MB (20000 x 100 at 2000 columns: 250 us in three chunks, 285 in one).
+// None up to 64 columns, which keep the split that w.split allows.
+size_t t_split_elems(int64_t n, int m) {
+  return m <= 64 ? 0 : std::min<size_t>((size_t)4 * n * m, (size_t)1 << 23);
+}
+
 // Sketch one block of m new columns into F (columns r_old .. r_old+m-1).
 nys_status sketch_block(nys_ctx ctx, const nys_dense& A, const double* D, double c,
                         const double* omega, int m, nys_factor F) {
@@ -1202,11 +1226,17 @@ nys_status sketch_block(nys_ctx ctx, const nys_dense& A, const double* D, double
     hipLaunchKernelGGL(k_sym_y, dim3(blocks((int64_t)m * d)), dim3(256), 0, st, T + ldt * r0, ldt,
                        (int)d, m, Om, c, Y + d * r0);
   } else if (F->prec == NYS_F64) {
-    // T = A Omega (n x m, column-major) in FP64 tiles, Y = A^T (D o T) + c Omega
-    NYS_TRY(ctx->gemm_ws.reserve(sizeof(double) * n * m + 256));
+    // T = A Omega (n x m, column-major) in FP64 tiles, Y = A^T (D o T) + c Omega;
+    // T's split-K partials follow it (left out where a caller's workspace is short)
+    size_t tsplit = t_split_elems(n, m);
+    if (ctx->gemm_ws.reserve(sizeof(double) * (n * m + tsplit) + 256) != NYS_OK) {
+      tsplit = 0;
+      NYS_TRY(ctx->gemm_ws.reserve(sizeof(double) * n * m + 256));
+    }
     double* T = ctx->gemm_ws.as<double>();
     NYS_TRY(gemm64(st, (int)n, m, (int)d, A.data, a32, A.ld, 1, Om, false, 1, d, T, 1, n, 1.0, 0.0,
-                   w.split, w.split_elems));
+                   tsplit > w.split_elems ? T + n * m : w.split,
+                   std::max(tsplit, w.split_elems)));
     NYS_TRY_HIP(hipMemcpyAsync(Y + d * r0, Om, sizeof(double) * d * m, hipMemcpyDeviceToDevice, st));
     NYS_TRY(gemm64(st, (int)d, m, (int)n, A.data, a32, 1, A.ld, T, false, 1, n, Y + d * r0, 1, d,
                    1.0, c, w.split, w.split_elems, D));
@@ -1354,7 +1384,7 @@ nys_status sketch_round(nys_ctx ctx, const nys_dense* A, const double* D, double
 void sketch_ws_bytes(const nys_dense& A, int m, int r, int num_cu, size_t* tmp,
                      size_t* factor_out) {
   const int64_t n = A.n, d = A.d;
-  size_t g = sizeof(double) * (size_t)n * m + 256;                       // FP64 form
+  size_t g = sizeof(double) * ((size_t)n * m + t_split_elems(n, m)) + 256;   // FP64 form
   g = std::max(g, sizeof(double) * (size_t)(n + 2 * d) * m + 256);       // sparse form
   if (A.dtype == NYS_F32) {
     const Sk32Shape s = sk32_shape(n, d, m, num_cu, false);               // FP32 >= BF16

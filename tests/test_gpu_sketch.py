@@ -278,3 +278,28 @@ def test_sketch_fp64_ranks_at_block_edges(N, ctx, r):
     assert np.allclose(lam, f.lam, rtol=1e-9, atol=1e-12 * f.lam[0])
     assert np.linalg.norm(U.T @ U - np.eye(r)) < 1e-10
     F.close()
+
+
+@pytest.mark.parametrize("n,d,r,dtype,weights", [
+    (3, 40, 2, torch.float32, False),        # fewer rows than a tile, one short K step
+    (33, 65, 16, torch.float64, True),       # one row past a tile; odd widths
+    (1000, 129, 17, torch.float32, True),    # K remainders of 1 and 8, column tile of one block + 1
+    (4097, 251, 64, torch.float64, False),   # unaligned rows, a full column tile, split K
+    (2049, 513, 65, torch.float32, True),    # one column past a column tile
+])
+def test_sketch_fp64_product_edges(N, ctx, n, d, r, dtype, weights):
+    # edges of the FP64 products' tiles and K steps (16 k, 16 or 32 rows, 64
+    # columns); rounding of sums of at most 4097 terms, times the condition
+    # that the 1e-10 bar of the other FP64 sketches allows for
+    A = synth.decay_matrix(n, d, 0.6, seed=n).to(dtype)
+    om = synth.omega_raw(d, r, seed=n + 1)
+    D = torch.rand(n, dtype=torch.float64, generator=torch.Generator().manual_seed(n)) + 0.1 \
+        if weights else None
+    c = 0.2 if n < d else 0.0    # rank(A) < r otherwise
+    F = N.nys_sketch(ctx, A.to(DEV), om.to(DEV), D=None if D is None else D.to(DEV), c=c,
+                     prec=N.NYS_F64)
+    H, U, lam, inf = hhat(F, ctx)
+    f = ny.rand_nys_appx(A.double().numpy(), None if D is None else D.numpy(), c, om.numpy().T)
+    assert rel(H, f.dense()) < 1e-10
+    assert inf["nu"] == f.nu
+    F.close()
