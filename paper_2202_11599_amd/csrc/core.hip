@@ -11,12 +11,6 @@
 namespace nys {
 namespace {
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // ------------------------------------------------------------ FP64 GEMM
 // C(m,n) = alpha sum_k A(m,k) w_k B(k,n) + beta C(m,n), A(m,k) = A[m*sam + k*sak],
 // B(k,n) = B[k*sbk + n*sbn], C(m,n) = C[m*scm + n*scn], w_k = wk[k] or 1;

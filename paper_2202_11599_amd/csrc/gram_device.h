@@ -17,12 +17,6 @@ template <> struct Chunk<double> {
   static constexpr int N = 2;
 };
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 __device__ __forceinline__ double sigm(double t) {
   const double e = exp(-fabs(t));
   return t >= 0.0 ? 1.0 / (1.0 + e) : e / (1.0 + e);

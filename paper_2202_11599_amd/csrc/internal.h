@@ -130,6 +130,36 @@ __device__ __forceinline__ void publish_state(const int* done, PcgDev* note, int
     *note = h;
   }
 }
+
+// Sum over the wavefront, every lane gets it: the butterfly over lane distances
+// 32, 16, 8, 4, 2, 1, its exchanges in the vector ALU (row swaps and DPP
+// rotations) rather than through LDS permutes, which cost a round trip of the
+// LDS pipeline each.  After the step of distance 8 a row of 16 lanes repeats
+// after 8 lanes, so a rotation by 4 (then quad permutations) brings the value
+// of lane ^ 4 (^ 2, ^ 1).
+__device__ __forceinline__ double dpp_join(int lo, int hi) { return __hiloint2double(hi, lo); }
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  return dpp_join(__builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false),
+                  __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  {
+    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = dpp_join((int)l[0], (int)h[0]) + dpp_join((int)l[1], (int)h[1]);
+  }
+  {
+    const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = dpp_join((int)l[0], (int)h[0]) + dpp_join((int)l[1], (int)h[1]);
+  }
+  v += dpp_move<0x128>(v);   // row_ror:8
+  v += dpp_move<0x124>(v);   // row_ror:4
+  v += dpp_move<0x4e>(v);    // quad_perm [2, 3, 0, 1]
+  v += dpp_move<0xb1>(v);    // quad_perm [1, 0, 3, 2]
+  return v;
+}
 #endif
 // w^T y of PCG iteration k lives in wy[k % kWyRing]: iteration k reads entry
 // k and writes entry k + 1, and the kernels of one solve run in stream order,

@@ -22,7 +22,6 @@ namespace nys {
 namespace {
 
 using gram::sigm;
-using gram::wave_sum;
 
 constexpr int kTBlocks = 64;   // row blocks of the transpose
 constexpr int kColFlag = (int)0x80000000u;   // first entry of a column in the CSC copy

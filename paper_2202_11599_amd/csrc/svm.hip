@@ -24,11 +24,6 @@
 namespace nys {
 namespace {
 
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 __device__ __forceinline__ double wmin(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
@@ -45,7 +40,7 @@ __device__ __forceinline__ double wmax(double v) {
 enum RedOp { kSum, kMin, kMax };
 template <RedOp OP, int NW = 16>
 __device__ double block_reduce(double v, double* sh) {
-  v = OP == kSum ? wsum(v) : (OP == kMin ? wmin(v) : wmax(v));
+  v = OP == kSum ? wave_sum(v) : (OP == kMin ? wmin(v) : wmax(v));
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -67,7 +62,7 @@ __global__ __launch_bounds__(256) void k_rownorm2(const float* __restrict__ X, i
     const double v = X[i * ldx + k];
     s = fma(v, v, s);
   }
-  s = wsum(s);
+  s = wave_sum(s);
   if (lane == 0) sq[i] = s;
 }
 
@@ -104,7 +99,7 @@ constexpr int kSvmNS = 8;   // scalars of the projection pass
 template <int NV, int NW>
 __device__ void block_sums(double (&v)[NV], double* sh) {
 #pragma unroll
-  for (int k = 0; k < NV; ++k) v[k] = wsum(v[k]);
+  for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) {
 #pragma unroll

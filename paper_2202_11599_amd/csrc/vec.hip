@@ -13,12 +13,6 @@
 namespace nys {
 namespace {
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // a[t] + a[t + step] + ... (indices below n) with four loads in flight: four
 // running sums, combined in a fixed order
 __device__ __forceinline__ double strided_sum(const double* __restrict__ a, int n, int t,
