@@ -1,16 +1,18 @@
 // Batched NysADMM for many independent lasso problems (a regularisation
 // path: one A per instance, its gamma changing between calls).  All
 // instances advance in lockstep:
-//   * the matvec pair of every instance runs in ONE persistent launch per
-//     d-bucket, over a list of (instance, row range) tiles; instances whose
-//     PCG has converged skip their tiles;
+//   * the matvec pair of every instance runs over a list of (instance, row
+//     range) tiles: one launch for all instances of up to 2048 FP32 / 1024
+//     FP64 columns (k_brows), one per bucket of row widths for the wider ones
+//     (k_bgram); instances whose PCG has converged skip their tiles;
 //   * the d-vector kernels run over (instance, block) item lists;
 //   * the iteration index lives on the device (PcgDev::k), so a chunk of PCG
 //     iterations is captured once into a hipGraph and replayed until every
 //     instance has converged;
-//   * the launch shape of each bucket (waves, chunks, rows per group, rows per
-//     tile, workgroups per CU) is picked by timing candidates on the batch
-//     itself the first time it is seen (autotune, cached in the context).
+//   * the launch shape of each bucket of wide instances (waves, chunks, rows
+//     per group, rows per tile, workgroups per CU) is picked by timing
+//     candidates on the batch itself the first time it is seen (autotune,
+//     cached in the context).
 // Per instance the arithmetic is that of the single-problem path: FP64
 // products and sums of the stored A, the same PCG recurrences and tests.
 #include <algorithm>
@@ -25,24 +27,39 @@
 
 namespace nys {
 
-struct BInst {
-  const void* A;
-  int64_t n, ld;
-  int d, aligned;
-  double rho, rho_eff, gamma, tol_rel, tol_abs;
-  const void* U;
-  int r, u32, active, max_iter;
-  const double* lam;
-  double lam_s;
-  double *x, *z, *u;                    // caller state
-  const double* b;                      // response (A^T b pass)
-  double *w, *p, *rhs, *cvec, *wy, *atb;
-  double *ypart, *qpart;
-  int G, ldy;
-  double *wwpart, *rrpart, *pppart, *part;
-  int nred, nvec, nbp, pad;
-  PcgDev* st;
-};
+// An instance record, as the host fills it (P(T) = T*) and as the kernels read
+// it (pointers to global memory, the same layout): a pointer that is read from
+// memory is otherwise a generic one, and generic (flat) loads count as LDS
+// accesses too, so that every wait for an LDS read waits for all loads in
+// flight as well.
+#define NYS_BINST(P)                                              \
+  P(const void) A;                                                \
+  int64_t n, ld;                                                  \
+  int d, aligned;                                                 \
+  double rho, rho_eff, gamma, tol_rel, tol_abs;                   \
+  P(const void) U;                                                \
+  int r, u32, active, max_iter;                                   \
+  P(const double) lam;                                            \
+  double lam_s;                                                   \
+  P(double) x; P(double) z; P(double) u;      /* caller state */  \
+  P(const double) b;                 /* response (A^T b pass) */  \
+  P(double) w; P(double) p; P(double) rhs; P(double) cvec;        \
+  P(double) wy; P(double) atb; P(double) ypart; P(double) qpart;  \
+  int G, ldy;                                                     \
+  P(double) wwpart; P(double) rrpart; P(double) pppart;           \
+  P(double) part;                                                 \
+  int nred, nvec, nbp, f64;                                       \
+  P(PcgDev) st;
+#define NYS_HOST_PTR(T) T*
+#if defined(__HIP_DEVICE_COMPILE__)
+#define NYS_GLOBAL_PTR(T) __attribute__((address_space(1))) T*
+#else
+#define NYS_GLOBAL_PTR(T) T*
+#endif
+struct BInst { NYS_BINST(NYS_HOST_PTR) };
+struct BInstD { NYS_BINST(NYS_GLOBAL_PTR) };
+#undef NYS_BINST
+static_assert(sizeof(BInst) == sizeof(BInstD), "one layout");
 
 struct BTile {
   int inst, slot;
@@ -68,7 +85,7 @@ __device__ __forceinline__ double wave_max(double v) {
 // vecsel: 0 -> x (PCG init / true residual), 1 -> p (iteration), 2 -> none (A^T b)
 template <typename T, int WAVES, int CPL, int R, bool ALIGNED>
 __global__ __launch_bounds__(WAVES * 64, (WAVES >= 4 ? 2 : 1)) void k_bgram(
-    const BInst* __restrict__ insts, const BTile* __restrict__ tiles, int ntiles, int mode,
+    const BInstD* __restrict__ insts, const BTile* __restrict__ tiles, int ntiles, int mode,
     int vecsel, int skip_done) {
   constexpr int NT = WAVES * 64;
   constexpr int VN = Chunk<T>::N;
@@ -78,10 +95,10 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES >= 4 ? 2 : 1)) void k_bgram(
   int buf = 0;
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const BTile tl = tiles[t];
-    const BInst& I = insts[tl.inst];
+    const BInstD& I = insts[tl.inst];
     if (!I.active) continue;
     if (skip_done && I.st->done) continue;
-    const T* A = static_cast<const T*>(I.A);
+    const T* A = ((const T*)I.A);
     const int d = I.d;
     const double* p = vecsel == 0 ? I.x : (vecsel == 1 ? I.p : nullptr);
     const double* aux = (mode == kModeTOnly) ? I.b : nullptr;
@@ -124,62 +141,271 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES >= 4 ? 2 : 1)) void k_bgram(
   }
 }
 
-__device__ double bsum1024(const double* __restrict__ a, int n, double* sh) {
+// The matvec pair of the narrow instances (d up to 512 chunks of 16 bytes: 2048
+// FP32, 1024 FP64 columns), all of them in one launch, one workgroup of 8
+// wavefronts per tile of rows.  A batch of a few small instances has few tiles,
+// so the rows of a tile are worked on side by side: a block of 32 / W rows (64
+// KB; W = 1, 2 or 4 by the row width) is loaded by the 8 wavefronts, each of
+// which forms the dots of its rows alone (no barrier between rows), and staged
+// in LDS; then every thread adds the block's rows in order into its own
+// columns of y while the next block is on its way.  One barrier pair per 64 KB
+// and 128 KB in flight per CU (two workgroups).  Plain loads: a batch that fits
+// the memory-side cache is read from there (non-temporal ones: 15.3 instead of
+// 13.8 ms for the call below; 2 to 5% either way where it does not fit).
+// Order of summation: that of k_bgram with W wavefronts (two for aligned rows
+// of up to 512 chunks / 4) and two chunks per lane (dot: lane chains over the
+// chunks of virtual wavefront w, butterfly, then w ascending; y: rows ascending
+// within the tile), bit for bit: the PCG runs of low-rank factors carry a
+// last-bit change into the eighth digit of their iterates.
+// Measured on 8 instances of 2000..12000 x 300..1500 (203 MB), 10 ADMM
+// iterations (184 passes): 13.8 ms, against 36.9 with one launch of k_bgram per
+// row-width bucket (about 180 us per pass: a tile's 128 rows went through one
+// group of wavefronts 4 rows at a time); 8 of 32000 x 1000: 5.5 TB/s.
+constexpr int kBrT = 512;             // threads per workgroup
+constexpr int kBrRowBytes = 8192;     // widest row
+constexpr int kBrLds = 65536;         // bytes of one staged block of rows
+inline bool brows_ok(const nys_dense& A) {
+  return A.d * (A.dtype == NYS_F64 ? 8 : 4) <= kBrRowBytes;
+}
+
+template <typename T, int W>
+__device__ __forceinline__ void brows_tile(const BInstD& I, const BTile& tl, int mode,
+                                           const double* __restrict__ p,
+                                           const double* __restrict__ aux, char* lds,
+                                           double (*ts)[32]) {
+  constexpr int VN = Chunk<T>::N;
+  constexpr int RPW = 4 / W;            // rows per wavefront and block
+  constexpr int BR = 8 * RPW;           // rows per block
+  constexpr int LDP = W * 128 * VN;     // LDS pitch: the columns W covers
+  constexpr int CP = W * VN >= 4 ? W * VN / 4 : 1;   // columns of y per thread
+  static_assert(BR * LDP * (int)sizeof(T) == kBrLds, "one staged block");
+  // rows may start at any element boundary
+  typedef T VU __attribute__((ext_vector_type(VN), aligned(sizeof(T))));
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const T* A = ((const T*)I.A);
+  const int d = I.d;
+  const bool aligned = I.aligned != 0, tonly = mode == kModeTOnly;
+  T* rows = reinterpret_cast<T*>(lds);
+  // first column of chunk m of virtual wavefront w (a lane's column plus a
+  // uniform offset)
+  const int cl = lane * VN;
+  auto off = [&](int w, int m) __attribute__((always_inline)) {
+    return (aligned ? w + m * W : w * 2 + m) * 64 * VN;
+  };
+  double pr[W][2][VN];
+#pragma unroll
+  for (int w = 0; w < W; ++w)
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const int c = cl + off(w, m);
+#pragma unroll
+      for (int v = 0; v < VN; ++v) pr[w][m][v] = (p != nullptr && c + v < d) ? p[c + v] : 0.0;
+    }
+  VU a[RPW][W][2];
+  double av[RPW];
+  auto load = [&](int64_t base) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      const int64_t rr = base + wv * RPW + i;
+      const bool ok = rr < tl.r1;
+      const T* arow = A + rr * I.ld;
+      av[i] = (aux != nullptr && ok) ? aux[rr] : 0.0;
+#pragma unroll
+      for (int w = 0; w < W; ++w)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const int c = cl + off(w, m);
+          VU x = (VU)(T)0;
+          if (ok && c < d) {
+            if (c + VN <= d) {
+              x = *reinterpret_cast<const VU*>(arow + c);
+            } else {
+#pragma unroll
+              for (int v = 0; v < VN; ++v) x[v] = c + v < d ? arow[c + v] : (T)0;
+            }
+          }
+          a[i][w][m] = x;
+        }
+    }
+  };
+  double y[CP], q = 0.0;
+#pragma unroll
+  for (int c = 0; c < CP; ++c) y[c] = 0.0;
+  load(tl.r0);
+  int buf = 0;
+  for (int64_t base = tl.r0; base < tl.r1; base += BR, buf ^= 1) {
+    double t[RPW];
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) t[i] = 0.0;
+    if (!tonly) {
+#pragma unroll
+      for (int w = 0; w < W; ++w)
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+          double acc = 0.0;
+#pragma unroll
+          for (int m = 0; m < 2; ++m) {
+            // aligned rows of one virtual wavefront: a sum per chunk
+            if (W == 1 && m == 1 && aligned) {
+              t[i] += wave_sum(acc);
+              acc = 0.0;
+            }
+#pragma unroll
+            for (int v = 0; v < VN; ++v) acc = fma((double)a[i][w][m][v], pr[w][m][v], acc);
+          }
+          t[i] += wave_sum(acc);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      const int r = wv * RPW + i;
+      if (lane == 0) ts[buf][r] = tonly ? av[i] : t[i];   // 0 past the tile's rows
+#pragma unroll
+      for (int w = 0; w < W; ++w)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+          *reinterpret_cast<typename Chunk<T>::V*>(rows + r * LDP + off(w, m) + cl) = a[i][w][m];
+    }
+    __syncthreads();
+    if (base + BR < tl.r1) load(base + BR);
+#pragma unroll 4
+    for (int r = 0; r < BR; ++r) {
+      const double s = ts[buf][r];
+#pragma unroll
+      for (int c = 0; c < CP; ++c) {
+        const int j = tid + kBrT * c;
+        if (LDP >= kBrT || j < LDP) y[c] = fma(s, (double)rows[r * LDP + j], y[c]);
+      }
+      if (!tonly) q = fma(s, s, q);
+    }
+    __syncthreads();
+  }
+  double* yp = I.ypart + (int64_t)tl.slot * I.ldy;
+#pragma unroll
+  for (int c = 0; c < CP; ++c) {
+    const int j = tid + kBrT * c;
+    if (j < d) yp[j] = y[c];
+  }
+  if (tid == 0) I.qpart[tl.slot] = q;
+}
+
+__global__ __launch_bounds__(kBrT, 4) void k_brows(
+    const BInstD* __restrict__ insts, const BTile* __restrict__ tiles, int ntiles, int mode,
+    int vecsel, int skip_done) {
+  __shared__ __attribute__((aligned(16))) char lds[kBrLds];
+  __shared__ double ts[2][32];
+  const int t = blockIdx.x;
+  if (t >= ntiles) return;
+  const BTile tl = tiles[t];
+  const BInstD& I = insts[tl.inst];
+  if (!I.active) return;
+  if (skip_done && I.st->done) return;
+  const double* p = vecsel == 0 ? I.x : (vecsel == 1 ? I.p : nullptr);
+  const double* aux = (mode == kModeTOnly) ? I.b : nullptr;
+  if (!I.f64) {
+    if (I.d <= 512) brows_tile<float, 1>(I, tl, mode, p, aux, lds, ts);
+    else if (I.d <= 1024) brows_tile<float, 2>(I, tl, mode, p, aux, lds, ts);
+    else brows_tile<float, 4>(I, tl, mode, p, aux, lds, ts);
+  } else {
+    if (I.d <= 256) brows_tile<double, 1>(I, tl, mode, p, aux, lds, ts);
+    else if (I.d <= 512) brows_tile<double, 2>(I, tl, mode, p, aux, lds, ts);
+    else brows_tile<double, 4>(I, tl, mode, p, aux, lds, ts);
+  }
+}
+
+// Sums of two arrays over a 1024-thread block in a fixed order; av and bv are
+// the thread's first entries (0 past the end), loaded ahead by the caller.
+__device__ void bsum1024x2(const double* __restrict__ a, int na, double av,
+                           const double* __restrict__ b, int nb, double bv, double (*sh)[16],
+                           double* sa, double* sb) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  double s = 0.0;
-  for (int i = tid; i < n; i += 1024) s += a[i];
+  double s = av, t = bv;
+  for (int i = tid + 1024; i < na; i += 1024) s += a[i];
+  for (int i = tid + 1024; i < nb; i += 1024) t += b[i];
   s = wave_sum(s);
+  t = wave_sum(t);
+  if (lane == 0) {
+    sh[0][wv] = s;
+    sh[1][wv] = t;
+  }
   __syncthreads();
-  if (lane == 0) sh[wv] = s;
-  __syncthreads();
-  double r = 0.0;
-  for (int i = 0; i < 16; ++i) r += sh[i];
-  __syncthreads();
-  return r;
+  double r = 0.0, u = 0.0;
+  for (int i = 0; i < 16; ++i) {
+    r += sh[0][i];
+    u += sh[1][i];
+  }
+  *sa = r;
+  *sb = u;
 }
 
 // op 0 iterate, 1 init (w = rhs - H x), 2 true residual, 3 plain (-> atb),
-// 4 init from the carried residual w (no partials: only the norms of w and rhs)
-__global__ __launch_bounds__(1024) void k_breduce(const BInst* __restrict__ insts,
-                                                  const BItem* __restrict__ items, int op) {
+// 4 init from the carried residual w (no partials: only the norms of w and rhs).
+// k4: iteration index modulo kWyRing (op 0).  The loads of a step (partial
+// sums, scalars' partials, vector entries) are issued together.
+__global__ __launch_bounds__(1024) void k_breduce(const BInstD* __restrict__ insts,
+                                                  const BItem* __restrict__ items, int op,
+                                                  int k4) {
   const BItem it = items[blockIdx.x];
-  const BInst& I = insts[it.inst];
+  const BInstD& I = insts[it.inst];
   if (!I.active) return;
   if (op == 0 && I.st->done) return;
   constexpr int S = 16;
   __shared__ double part[S][64];
-  __shared__ double sh[16];
+  __shared__ double sh[2][16];
   const int tid = threadIdx.x, lane = tid & 63, grp = tid >> 6;
   const int64_t j = (int64_t)it.blk * 64 + lane;
   const int d = I.d;
+  const bool in = j < d;
+  double qv = 0.0, pv0 = 0.0, wyk = 0.0, pj = 0.0, xj = 0.0, wj = 0.0, rj = 0.0;
+  if (op == 0) {
+    if (tid < I.G) qv = I.qpart[tid];
+    if (tid < I.nvec) pv0 = I.pppart[tid];
+    wyk = I.wy[k4];
+  }
+  if (grp == 0 && in && op != 3) {
+    pj = op == 0 ? I.p[j] : (op == 4 ? 0.0 : I.x[j]);
+    if (op == 0) xj = I.x[j];
+    if (op == 0 || op == 4) wj = I.w[j];
+    if (op != 0) rj = I.rhs[j];
+  }
   double acc = 0.0;
-  if (j < d && op != 4)
-    for (int g = grp; g < I.G; g += S) acc += I.ypart[(int64_t)g * I.ldy + j];
+  if (in && op != 4) {
+    // eight partials in flight, added in order
+    const double* yp = I.ypart + j;
+    const int G = I.G, ldy = I.ldy;
+    for (int g = grp; g < G; g += 8 * S) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = yp[(int64_t)min(g + u * S, G - 1) * ldy];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc = g + u * S < G ? acc + v[u] : acc;
+    }
+  }
   part[grp][lane] = acc;
   double alpha = 0.0;
-  const int k = I.st->k;
   if (op == 0) {
-    const double q = bsum1024(I.qpart, I.G, sh);
-    const double pp = bsum1024(I.pppart, I.nvec, sh);
+    double q, pp;
+    bsum1024x2(I.qpart, I.G, qv, I.pppart, I.nvec, pv0, sh, &q, &pp);
     const double pv = q + I.rho_eff * pp;
     if (!(pv > 0.0)) {
       if (it.blk == 0 && tid == 0) {
         I.st->flags |= (pv != pv) ? kFlagNonfinite : kFlagBreakdown;
-        I.st->iters = k;
+        I.st->iters = I.st->k;
         I.st->done = 1;
       }
       return;
     }
-    alpha = I.wy[k & (kWyRing - 1)] / pv;
+    alpha = wyk / pv;
+  } else {
+    __syncthreads();
   }
-  __syncthreads();
   if (grp != 0) return;
   double ww = 0.0, rr = 0.0;
-  if (j < d && op == 4) {
-    const double wj = I.w[j], r = I.rhs[j];
+  if (in && op == 4) {
     ww = wj * wj;
-    rr = r * r;
-  } else if (j < d) {
+    rr = rj * rj;
+  } else if (in) {
     double sum = 0.0;
 #pragma unroll
     for (int i = 0; i < S; ++i) sum += part[i][lane];
@@ -187,20 +413,17 @@ __global__ __launch_bounds__(1024) void k_breduce(const BInst* __restrict__ inst
       I.atb[j] = sum;
       return;
     }
-    const double* pv_src = (op == 0) ? I.p : I.x;
-    const double pj = pv_src[j];
     const double v = sum + I.rho_eff * pj;
     if (op == 0) {
-      I.x[j] += alpha * pj;
-      const double wj = I.w[j] - alpha * v;
-      I.w[j] = wj;
-      ww = wj * wj;
+      I.x[j] = xj + alpha * pj;
+      const double wn = wj - alpha * v;
+      I.w[j] = wn;
+      ww = wn * wn;
     } else {
-      const double r = I.rhs[j];
-      const double wj = r - v;
-      I.w[j] = wj;
-      ww = wj * wj;
-      rr = r * r;
+      const double wn = rj - v;
+      I.w[j] = wn;
+      ww = wn * wn;
+      rr = rj * rj;
     }
   }
   if (op == 3) return;
@@ -212,9 +435,10 @@ __global__ __launch_bounds__(1024) void k_breduce(const BInst* __restrict__ inst
   }
 }
 
-__device__ double bsum256(const double* __restrict__ a, int n, double* sh4) {
-  double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) s += a[i];
+// sum of a[0..n) over a 256-thread block, v the thread's first entry
+__device__ double bsum256(const double* __restrict__ a, int n, double v, double* sh4) {
+  double s = v;
+  for (int i = threadIdx.x + 256; i < n; i += 256) s += a[i];
   s = wave_sum(s);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sh4[threadIdx.x >> 6] = s;
@@ -224,57 +448,88 @@ __device__ double bsum256(const double* __restrict__ a, int n, double* sh4) {
   return r;
 }
 
-// mode 0: iteration test + dots, 1: init test + dots, 3: true residual norm
+// mode 0: iteration test + dots, 1: init test + dots, 3: true residual norm.
+// Mode 0 ends the iteration's count too: the instance's k advances, and an
+// instance at max_iter stops (its p is not needed any more).
 template <typename UT>
-__device__ void bdot_body(const BInst& I, int blk, int mode) {
+__device__ void bdot_body(const BInstD& I, int blk, int mode) {
   __shared__ double sh4[4];
   const int tid = threadIdx.x;
-  if (mode == 0 || mode == 1) {
-    if (I.st->done) return;
-    const double ww = bsum256(I.wwpart, I.nred, sh4);
-    double thr2;
-    bool zero_rhs = false;
-    if (mode == 1) {
-      const double rr = bsum256(I.rrpart, I.nred, sh4);
-      thr2 = fmax(I.tol_abs * I.tol_abs, I.tol_rel * I.tol_rel * rr);
-      zero_rhs = (rr == 0.0);
-      if (blk == 0 && tid == 0) {
-        I.st->rr = rr;
-        I.st->thr2 = thr2;
-      }
-    } else {
-      thr2 = I.st->thr2;
-    }
-    const bool bad = !(ww == ww) || (ww > 1.7e308);
-    if (blk == 0 && tid == 0) I.st->ww = ww;
-    if (zero_rhs || bad || ww <= thr2) {
-      if (blk == 0 && tid == 0) {
-        if (bad) I.st->flags |= kFlagNonfinite;
-        if (zero_rhs) I.st->flags |= kFlagZeroRhs;
-        I.st->iters = (mode == 1) ? 0 : I.st->k + 1;
-        I.st->done = 1;
-      }
-      return;
-    }
-  } else {
-    const double ww = bsum256(I.wwpart, I.nred, sh4);
+  if ((mode == 0 || mode == 1) && I.st->done) return;
+  const double wv = tid < I.nred ? I.wwpart[tid] : 0.0;
+  const double rv = (mode == 1 && tid < I.nred) ? I.rrpart[tid] : 0.0;
+  if (mode == 3) {
+    const double ww = bsum256(I.wwpart, I.nred, wv, sh4);
     if (blk == 0 && tid == 0) I.st->true_rr = ww;
     return;
   }
+  const double thr2_old = I.st->thr2;
+  // this wavefront's column of U^T w, eight terms in flight, one chain
   const int lane = tid & 63;
   const int col = blk * 4 + (tid >> 6);
-  if (col >= I.r) return;
-  const UT* u = static_cast<const UT*>(I.U) + (int64_t)col * I.d;
   double acc = 0.0;
-  for (int64_t j = lane; j < I.d; j += 64) acc = fma((double)u[j], I.w[j], acc);
-  acc = wave_sum(acc);
-  if (lane == 0) I.cvec[col] = acc;
+  if (col < I.r) {
+    const UT* u = ((const UT*)I.U) + (int64_t)col * I.d;
+    const double* w = I.w;
+    const int d = I.d;
+    for (int j0 = lane; j0 < d; j0 += 8 * 64) {
+      UT uv[8];
+      double wj[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int j = min(j0 + 64 * e, d - 1);
+        uv[e] = u[j];
+        wj[e] = w[j];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const double f = fma((double)uv[e], wj[e], acc);
+        acc = j0 + 64 * e < d ? f : acc;
+      }
+    }
+    acc = wave_sum(acc);
+  }
+  const double ww = bsum256(I.wwpart, I.nred, wv, sh4);
+  double thr2;
+  bool zero_rhs = false;
+  if (mode == 1) {
+    const double rr = bsum256(I.rrpart, I.nred, rv, sh4);
+    thr2 = fmax(I.tol_abs * I.tol_abs, I.tol_rel * I.tol_rel * rr);
+    zero_rhs = (rr == 0.0);
+    if (blk == 0 && tid == 0) {
+      I.st->rr = rr;
+      I.st->thr2 = thr2;
+    }
+  } else {
+    thr2 = thr2_old;
+  }
+  const bool bad = !(ww == ww) || (ww > 1.7e308);
+  const bool stop = zero_rhs || bad || ww <= thr2;
+  if (blk == 0 && tid == 0) {
+    PcgDev* st = I.st;
+    st->ww = ww;
+    if (stop) {
+      if (bad) st->flags |= kFlagNonfinite;
+      if (zero_rhs) st->flags |= kFlagZeroRhs;
+      st->iters = (mode == 1) ? 0 : st->k + 1;
+      st->done = 1;
+    } else if (mode == 0) {
+      const int k = st->k + 1;
+      st->k = k;
+      if (k >= I.max_iter) {
+        st->iters = k;
+        st->done = 1;
+      }
+    }
+  }
+  if (stop) return;
+  if (col < I.r && lane == 0) I.cvec[col] = acc;
 }
 
-__global__ __launch_bounds__(256) void k_bdot(const BInst* __restrict__ insts,
+__global__ __launch_bounds__(256) void k_bdot(const BInstD* __restrict__ insts,
                                               const BItem* __restrict__ items, int mode) {
   const BItem it = items[blockIdx.x];
-  const BInst& I = insts[it.inst];
+  const BInstD& I = insts[it.inst];
   if (!I.active) return;
   if (I.u32)
     bdot_body<float>(I, it.blk, mode);
@@ -282,13 +537,43 @@ __global__ __launch_bounds__(256) void k_bdot(const BInst* __restrict__ insts,
     bdot_body<double>(I, it.blk, mode);
 }
 
-// mode 0: p = y + beta p, wy[k+1]; mode 1: p = y, wy[0]
+// Sum of x^2 over the wavefront, in lanes 0..31: the first exchange's addition
+// is fused with the lane's own square (x_l^2 + the rounded square of lane
+// l + 32), the rest is wave_sum's tree.
+__device__ __forceinline__ double wave_sum_sq(double x) {
+  const double p = x * x;
+  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(p), __double2loint(p), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(p), __double2hiint(p), false, false);
+  double v = fma(x, x, dpp_join((int)l[1], (int)h[1]));
+  const auto l2 = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto h2 = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  v = dpp_join((int)l2[0], (int)h2[0]) + dpp_join((int)l2[1], (int)h2[1]);
+  v += dpp_move<0x128>(v);
+  v += dpp_move<0x124>(v);
+  v += dpp_move<0x4e>(v);
+  v += dpp_move<0xb1>(v);
+  return v;
+}
+
+// mode 0: p = y + beta p, wy[k+1]; mode 1: p = y, wy[0].  k4: iteration index
+// modulo kWyRing (mode 0).
 template <typename UT>
-__device__ void bupdate_body(const BInst& I, int blk, int mode) {
+__device__ void bupdate_body(const BInstD& I, int blk, int mode, int k4) {
   __shared__ double g[1024];
   __shared__ double sh4[4];
   const int tid = threadIdx.x;
-  const int r = I.r;
+  const int r = I.r, d = I.d;
+  const int64_t j = (int64_t)blk * 256 + tid;
+  const bool in = j < d;
+  const double wv = tid < I.nred ? I.wwpart[tid] : 0.0;
+  const double wyk = mode == 0 ? I.wy[k4] : 0.0;
+  const double wj = in ? I.w[j] : 0.0, pold = (in && mode == 0) ? I.p[j] : 0.0;
+  // the first 16 rank terms of U, loaded with the rest
+  constexpr int NU = 16;
+  const UT* u = ((const UT*)I.U) + (in ? j : 0);
+  UT uv[NU];
+#pragma unroll
+  for (int t = 0; t < NU; ++t) uv[t] = u[(int64_t)min(t, r - 1) * d];
   double sc = 0.0;
   for (int i = tid; i < r; i += 256) {
     const double s = (I.lam_s + I.rho) / (I.lam[i] + I.rho) - 1.0;
@@ -296,68 +581,67 @@ __device__ void bupdate_body(const BInst& I, int blk, int mode) {
     g[i] = s * ci;
     sc += s * ci * ci;
   }
-  const double ww = bsum256(I.wwpart, I.nred, sh4);
+  const double ww = bsum256(I.wwpart, I.nred, wv, sh4);
   sc = wave_sum(sc);
   if ((tid & 63) == 0) sh4[tid >> 6] = sc;
   __syncthreads();
   const double wy_new = ww + (((sh4[0] + sh4[1]) + sh4[2]) + sh4[3]);
-  const int k = I.st->k;
-  const int64_t j = (int64_t)blk * 256 + tid;
   double pj = 0.0;
-  if (j < I.d) {
-    double y = I.w[j];
-    const UT* u = static_cast<const UT*>(I.U) + j;
-    for (int i = 0; i < r; ++i) y = fma((double)u[(int64_t)i * I.d], g[i], y);
-    pj = (mode == 0) ? y + (wy_new / I.wy[k & (kWyRing - 1)]) * I.p[j] : y;
+  if (in) {
+    // one chain over the rank index, the next terms loaded ahead of it
+    double y = wj;
+    for (int i0 = 0; i0 < r; i0 += NU) {
+      UT un[NU];
+#pragma unroll
+      for (int t = 0; t < NU; ++t) un[t] = u[(int64_t)min(i0 + NU + t, r - 1) * d];
+#pragma unroll
+      for (int t = 0; t < NU; ++t) {
+        const double f = fma((double)uv[t], g[min(i0 + t, r - 1)], y);
+        y = i0 + t < r ? f : y;
+      }
+#pragma unroll
+      for (int t = 0; t < NU; ++t) uv[t] = un[t];
+    }
+    pj = (mode == 0) ? y + (wy_new / wyk) * pold : y;
     I.p[j] = pj;
   }
-  double pp = wave_sum(pj * pj);
+  const double pp = wave_sum_sq(pj);
   __syncthreads();
   if ((tid & 63) == 0) sh4[tid >> 6] = pp;
   __syncthreads();
   if (tid == 0) {
     I.pppart[blk] = ((sh4[0] + sh4[1]) + sh4[2]) + sh4[3];
-    if (blk == 0) I.wy[mode == 1 ? 0 : (k + 1) & (kWyRing - 1)] = wy_new;
+    if (blk == 0) I.wy[mode == 1 ? 0 : (k4 + 1) & (kWyRing - 1)] = wy_new;
   }
 }
 
-__global__ __launch_bounds__(256) void k_bupdate(const BInst* __restrict__ insts,
-                                                 const BItem* __restrict__ items, int mode) {
+__global__ __launch_bounds__(256) void k_bupdate(const BInstD* __restrict__ insts,
+                                                 const BItem* __restrict__ items, int mode,
+                                                 int k4) {
   const BItem it = items[blockIdx.x];
-  const BInst& I = insts[it.inst];
+  const BInstD& I = insts[it.inst];
   if (!I.active || I.st->done) return;
   if (I.u32)
-    bupdate_body<float>(I, it.blk, mode);
+    bupdate_body<float>(I, it.blk, mode, k4);
   else
-    bupdate_body<double>(I, it.blk, mode);
+    bupdate_body<double>(I, it.blk, mode, k4);
 }
 
-// End of a PCG iteration: advance k of every running instance, stop those at
-// max_iter, count the ones still running.
-__global__ __launch_bounds__(256) void k_btick(const BInst* __restrict__ insts, int count,
-                                               int* __restrict__ running) {
+// Number of instances still running, at the end of a chunk of iterations
+__global__ __launch_bounds__(256) void k_bcount(const BInstD* __restrict__ insts, int count,
+                                                int* __restrict__ running) {
   __shared__ int cnt;
   if (threadIdx.x == 0) cnt = 0;
   __syncthreads();
-  for (int q = threadIdx.x; q < count; q += 256) {
-    const BInst& I = insts[q];
-    if (!I.active || I.st->done) continue;
-    const int k = I.st->k + 1;
-    I.st->k = k;
-    if (k >= I.max_iter) {
-      I.st->iters = k;
-      I.st->done = 1;
-    } else {
-      atomicAdd(&cnt, 1);
-    }
-  }
+  for (int q = threadIdx.x; q < count; q += 256)
+    if (insts[q].active && !insts[q].st->done) atomicAdd(&cnt, 1);
   __syncthreads();
   if (threadIdx.x == 0) *running = cnt;
 }
 
 // Reset the PCG state of every instance (done, k, flags) without a memset,
 // so the sequence can live in a captured graph.
-__global__ void k_breset(const BInst* __restrict__ insts, int count) {
+__global__ void k_breset(const BInstD* __restrict__ insts, int count) {
   const int q = blockIdx.x * 256 + threadIdx.x;
   if (q >= count) return;
   PcgDev* s = insts[q].st;
@@ -371,10 +655,10 @@ __global__ void k_breset(const BInst* __restrict__ insts, int count) {
 
 // rhs = rho (z - u) + A^T b for active instances; carry: the PCG residual
 // w = rhs - H_rho x of the last solve follows the change of rhs (x unchanged)
-__global__ __launch_bounds__(256) void k_brhs(const BInst* __restrict__ insts,
+__global__ __launch_bounds__(256) void k_brhs(const BInstD* __restrict__ insts,
                                               const BItem* __restrict__ items, int carry) {
   const BItem it = items[blockIdx.x];
-  const BInst& I = insts[it.inst];
+  const BInstD& I = insts[it.inst];
   if (!I.active) return;
   const int64_t j = (int64_t)it.blk * 256 + threadIdx.x;
   if (j < I.d) {
@@ -385,10 +669,10 @@ __global__ __launch_bounds__(256) void k_brhs(const BInst* __restrict__ insts,
 }
 
 // z = S_{gamma/rho}(x + u), u += x - z, with the kNS residual partials per block
-__global__ __launch_bounds__(256) void k_bprox(const BInst* __restrict__ insts,
+__global__ __launch_bounds__(256) void k_bprox(const BInstD* __restrict__ insts,
                                                const BItem* __restrict__ items) {
   const BItem it = items[blockIdx.x];
-  const BInst& I = insts[it.inst];
+  const BInstD& I = insts[it.inst];
   if (!I.active) return;
   const int64_t j = (int64_t)it.blk * 256 + threadIdx.x;
   double v[kNS] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -426,10 +710,10 @@ __global__ __launch_bounds__(256) void k_bprox(const BInst* __restrict__ insts,
 }
 
 // per-instance scalars out[q*kNS + s] from the prox partials
-__global__ __launch_bounds__(256) void k_bscalars(const BInst* __restrict__ insts, int count,
+__global__ __launch_bounds__(256) void k_bscalars(const BInstD* __restrict__ insts, int count,
                                                   double* __restrict__ out) {
   const int q = blockIdx.x;
-  const BInst& I = insts[q];
+  const BInstD& I = insts[q];
   __shared__ double sh[4];
   for (int s = 0; s < kNS; ++s) {
     const bool mx = (s == 6 || s == 7);
@@ -455,6 +739,7 @@ __global__ __launch_bounds__(256) void k_bscalars(const BInst* __restrict__ inst
 struct Bucket {
   int f64 = 0, waves = 4, cpl = 2, rows = 4, aligned = 1;
   int per_cu = 2;
+  bool narrow = false;      // k_brows: rows of at most kBrRowBytes, any type and alignment
   int64_t tile_rows = 256;
   std::vector<int> insts;
   BTile* tiles = nullptr;   // device (inside the batch buffer)
@@ -466,19 +751,20 @@ struct Batch {
   int count = 0;
   std::vector<BInst> h;
   DevBuf dev;             // BInst array, tiles, items, per-instance storage
-  BInst* insts = nullptr;
+  BInstD* insts = nullptr;
   BItem *it64 = nullptr, *itdot = nullptr, *it256 = nullptr;
   int n64 = 0, ndot = 0, n256 = 0;
   std::vector<Bucket> buckets;
   int* running = nullptr;
   double* scal = nullptr;
+  PcgDev* states = nullptr;   // count states, one copy reads them all
   hipGraphExec_t graph = nullptr;
   int graph_iters = 0;
   std::string key;
 };
 
 template <typename T, int W, int C, int RR>
-nys_status launch_bg(const Bucket& b, const BInst* insts, int mode, int vecsel, int skip,
+nys_status launch_bg(const Bucket& b, const BInstD* insts, int mode, int vecsel, int skip,
                      hipStream_t st) {
   if (b.aligned) {
     hipLaunchKernelGGL((k_bgram<T, W, C, RR, true>), dim3(b.grid), dim3(W * 64), 0, st, insts,
@@ -494,7 +780,7 @@ nys_status launch_bg(const Bucket& b, const BInst* insts, int mode, int vecsel, 
 }
 
 template <typename T>
-nys_status launch_bg_t(const Bucket& b, const BInst* insts, int mode, int vecsel, int skip,
+nys_status launch_bg_t(const Bucket& b, const BInstD* insts, int mode, int vecsel, int skip,
                        hipStream_t st) {
 #define NYS_BC(W, C, RR) \
   if (b.waves == W && b.cpl == C && b.rows == RR) return launch_bg<T, W, C, RR>(b, insts, mode, vecsel, skip, st);
@@ -531,7 +817,12 @@ nys_status bgram(const Batch& B, int mode, int vecsel, int skip, hipStream_t st,
   std::vector<const Bucket*> bs;
   for (const Bucket& b : B.buckets)
     if (b.ntiles > 0) bs.push_back(&b);
-  auto launch = [&](const Bucket& b, hipStream_t s) {
+  auto launch = [&](const Bucket& b, hipStream_t s) -> nys_status {
+    if (b.narrow) {
+      hipLaunchKernelGGL(k_brows, dim3(b.grid), dim3(kBrT), 0, s, B.insts, b.tiles, b.ntiles, mode,
+                         vecsel, skip);
+      return hipGetLastError() == hipSuccess ? NYS_OK : NYS_ERR_HIP;
+    }
     return b.f64 ? launch_bg_t<double>(b, B.insts, mode, vecsel, skip, s)
                  : launch_bg_t<float>(b, B.insts, mode, vecsel, skip, s);
   };
@@ -554,25 +845,25 @@ nys_status bgram(const Batch& B, int mode, int vecsel, int skip, hipStream_t st,
   return NYS_OK;
 }
 
-nys_status pcg_iteration(nys_ctx ctx, const Batch& B, hipStream_t st) {
+// iteration k with k % kWyRing == k4
+nys_status pcg_iteration(nys_ctx ctx, const Batch& B, hipStream_t st, int k4) {
   NYS_TRY(bgram(B, kModeHess, 1, 1, st, ctx));
-  hipLaunchKernelGGL(k_breduce, dim3(B.n64), dim3(1024), 0, st, B.insts, B.it64, 0);
+  hipLaunchKernelGGL(k_breduce, dim3(B.n64), dim3(1024), 0, st, B.insts, B.it64, 0, k4);
   hipLaunchKernelGGL(k_bdot, dim3(B.ndot), dim3(256), 0, st, B.insts, B.itdot, 0);
-  hipLaunchKernelGGL(k_bupdate, dim3(B.n256), dim3(256), 0, st, B.insts, B.it256, 0);
-  hipLaunchKernelGGL(k_btick, dim3(1), dim3(256), 0, st, B.insts, B.count, B.running);
+  hipLaunchKernelGGL(k_bupdate, dim3(B.n256), dim3(256), 0, st, B.insts, B.it256, 0, k4);
   return hipGetLastError() == hipSuccess ? NYS_OK : NYS_ERR_HIP;
 }
 
 nys_status bpcg_init(nys_ctx ctx, const Batch& B, hipStream_t st, bool carry) {
   hipLaunchKernelGGL(k_breset, dim3((B.count + 255) / 256), dim3(256), 0, st, B.insts, B.count);
   if (carry) {
-    hipLaunchKernelGGL(k_breduce, dim3(B.n64), dim3(1024), 0, st, B.insts, B.it64, 4);
+    hipLaunchKernelGGL(k_breduce, dim3(B.n64), dim3(1024), 0, st, B.insts, B.it64, 4, 0);
   } else {
     NYS_TRY(bgram(B, kModeHess, 0, 0, st, ctx));
-    hipLaunchKernelGGL(k_breduce, dim3(B.n64), dim3(1024), 0, st, B.insts, B.it64, 1);
+    hipLaunchKernelGGL(k_breduce, dim3(B.n64), dim3(1024), 0, st, B.insts, B.it64, 1, 0);
   }
   hipLaunchKernelGGL(k_bdot, dim3(B.ndot), dim3(256), 0, st, B.insts, B.itdot, 1);
-  hipLaunchKernelGGL(k_bupdate, dim3(B.n256), dim3(256), 0, st, B.insts, B.it256, 1);
+  hipLaunchKernelGGL(k_bupdate, dim3(B.n256), dim3(256), 0, st, B.insts, B.it256, 1, 0);
   return hipGetLastError() == hipSuccess ? NYS_OK : NYS_ERR_HIP;
 }
 
@@ -643,7 +934,7 @@ size_t inst_bytes(int64_t n, int64_t d) {
   return 5 * au(sizeof(double) * d) + au(sizeof(double) * 1024) + au(sizeof(double) * kWyRing) +
          au(sizeof(double) * (size_t)G * ldy) + au(sizeof(double) * G) +
          3 * au(sizeof(double) * ((d + 63) / 64)) + au(sizeof(double) * ((d + 255) / 256)) +
-         au(sizeof(double) * kNS * ((d + 255) / 256)) + au(sizeof(PcgDev));
+         au(sizeof(double) * kNS * ((d + 255) / 256));
 }
 
 // tiling, tile and item lists; bucket the instances by row width.
@@ -661,6 +952,10 @@ nys_status batch_build(nys_ctx ctx, int count, const nys_problem* P, const nys_a
   std::map<std::pair<int, int>, std::vector<int>> groups;   // (f64|aligned, cover class)
   for (int q = 0; q < count; ++q) {
     const nys_dense& A = P[q].A;
+    if (brows_ok(A)) {
+      groups[{-1, 0}].push_back(q);
+      continue;
+    }
     const int vn = A.dtype == NYS_F64 ? 2 : 4;
     const int esize = vn == 2 ? 8 : 4;
     const int aligned = ((uintptr_t)A.data % 16 == 0) && ((A.ld * esize) % 16 == 0);
@@ -693,10 +988,14 @@ nys_status batch_build(nys_ctx ctx, int count, const nys_problem* P, const nys_a
   const size_t items_off = bytes;
   bytes += au(sizeof(BItem) * n64) + au(sizeof(BItem) * ndot) + au(sizeof(BItem) * n256);
   const size_t misc_off = bytes;
-  bytes += au(sizeof(int)) + au(sizeof(double) * kNS * count);
+  bytes += au(sizeof(int)) + au(sizeof(double) * kNS * count) + au(sizeof(PcgDev) * count);
   NYS_TRY(B->dev.reserve(bytes));
   char* base = static_cast<char*>(B->dev.ptr);
-  B->insts = reinterpret_cast<BInst*>(base);
+  B->running = reinterpret_cast<int*>(base + misc_off);
+  B->scal = reinterpret_cast<double*>(base + misc_off + au(sizeof(int)));
+  B->states = reinterpret_cast<PcgDev*>(base + misc_off + au(sizeof(int)) +
+                                        au(sizeof(double) * kNS * count));
+  B->insts = reinterpret_cast<BInstD*>(base);
   for (int q = 0; q < count; ++q) {
     const nys_dense& A = P[q].A;
     const int64_t d = A.d, n = A.n;
@@ -711,6 +1010,7 @@ nys_status batch_build(nys_ctx ctx, int count, const nys_problem* P, const nys_a
     I.d = (int)d;
     const int esize = A.dtype == NYS_F64 ? 8 : 4;
     I.aligned = ((uintptr_t)A.data % 16 == 0) && ((A.ld * esize) % 16 == 0);
+    I.f64 = A.dtype == NYS_F64 ? 1 : 0;
     I.rho = O[q].rho;
     I.rho_eff = O[q].rho + P[q].c;
     I.gamma = P[q].gamma;
@@ -746,7 +1046,7 @@ nys_status batch_build(nys_ctx ctx, int count, const nys_problem* P, const nys_a
     (void)take(au(sizeof(double) * I.nred));
     I.pppart = take(au(sizeof(double) * I.nvec));
     I.part = take(au(sizeof(double) * kNS * I.nbp));
-    I.st = reinterpret_cast<PcgDev*>(take(au(sizeof(PcgDev))));
+    I.st = B->states + q;
   }
   // items
   std::vector<BItem> it64, itdot, it256;
@@ -763,8 +1063,6 @@ nys_status batch_build(nys_ctx ctx, int count, const nys_problem* P, const nys_a
   B->n64 = n64;
   B->ndot = ndot;
   B->n256 = n256;
-  B->running = reinterpret_cast<int*>(base + misc_off);
-  B->scal = reinterpret_cast<double*>(base + misc_off + au(sizeof(int)));
   hipStream_t st = ctx->stream;
   NYS_TRY_HIP(hipMemcpyAsync(B->it64, it64.data(), sizeof(BItem) * n64, hipMemcpyHostToDevice, st));
   NYS_TRY_HIP(hipMemcpyAsync(B->itdot, itdot.data(), sizeof(BItem) * ndot, hipMemcpyHostToDevice, st));
@@ -775,8 +1073,6 @@ nys_status batch_build(nys_ctx ctx, int count, const nys_problem* P, const nys_a
   B->buckets.clear();
   for (auto& g : groups) {
     Bucket b;
-    b.f64 = (g.first.first & 2) ? 1 : 0;
-    b.aligned = g.first.first & 1;
     b.insts = g.second;
     int d_max = 0;
     int64_t finest_tiles = 0;
@@ -784,6 +1080,20 @@ nys_status batch_build(nys_ctx ctx, int count, const nys_problem* P, const nys_a
       d_max = std::max(d_max, B->h[q].d);
       finest_tiles += (P[q].A.n + kFinest - 1) / kFinest;
     }
+    if (g.first.first < 0) {
+      // the finest tiles until they fill the device eight times over (two
+      // workgroups per CU), then longer ones: fewer partial sums to write and
+      // add (a sixteenth of A's bytes each way at 128 rows)
+      b.narrow = true;
+      b.tile_rows = kFinest;
+      while (finest_tiles * kFinest / b.tile_rows > 16 * (int64_t)ctx->num_cu) b.tile_rows *= 2;
+      b.tiles = tiles_dev + tile_cursor;
+      tile_cursor += (size_t)finest_tiles;
+      B->buckets.push_back(b);
+      continue;
+    }
+    b.f64 = (g.first.first & 2) ? 1 : 0;
+    b.aligned = g.first.first & 1;
     std::vector<Bucket> c = bucket_candidates(b, d_max, ctx->num_cu);
     if (c.empty()) return NYS_ERR_INVALID;
     b = c[0];
@@ -799,6 +1109,19 @@ nys_status upload_tiles(nys_ctx ctx, Bucket* b, const std::vector<BInst>& h, int
   std::vector<BTile> t;
   make_tiles(*b, h, &t);
   b->ntiles = (int)t.size();
+  if (b->narrow) {
+    // One workgroup is bound by what a CU can keep in flight (about 20 GB/s),
+    // so the largest tiles go first.  When all tiles fit the device at once (two
+    // per CU), the second ones of the CUs go smallest first, to the CUs that
+    // hold the largest (8 instances of 2000..12000 x 300..1500: 18.6 -> 15.3 ms).
+    auto bytes = [&](const BTile& x) {
+      return (x.r1 - x.r0) * (int64_t)h[x.inst].d * (h[x.inst].f64 ? 2 : 1);
+    };
+    std::stable_sort(t.begin(), t.end(),
+                     [&](const BTile& x, const BTile& y) { return bytes(x) > bytes(y); });
+    if ((int)t.size() > num_cu && (int)t.size() <= 2 * num_cu)
+      std::reverse(t.begin() + num_cu, t.end());
+  }
   // one workgroup per tile: the dispatcher hands tiles to CUs as they free
   // up, which balances tiles of uneven width and skipped (converged) ones
   b->grid = std::max(1, b->ntiles);
@@ -816,6 +1139,11 @@ nys_status batch_tune(nys_ctx ctx, Batch* B) {
   NYS_TRY_HIP(hipEventCreate(&e0));
   NYS_TRY_HIP(hipEventCreate(&e1));
   for (Bucket& bk : B->buckets) {
+    if (bk.narrow) {
+      NYS_TRY(upload_tiles(ctx, &bk, B->h, ctx->num_cu));
+      for (int q : bk.insts) B->h[q].G = (int)((B->h[q].n + bk.tile_rows - 1) / bk.tile_rows);
+      continue;
+    }
     int d_max = 0;
     for (int q : bk.insts) d_max = std::max(d_max, B->h[q].d);
     std::string key = "batch|" + std::to_string(bk.f64) + "|" + std::to_string(bk.aligned);
@@ -878,7 +1206,8 @@ nys_status batch_tune(nys_ctx ctx, Batch* B) {
   return NYS_OK;
 }
 
-constexpr int kGraphIters = 4;
+// a replayed chunk starts at an iteration that is a multiple of the ring of w^T y
+constexpr int kGraphIters = kWyRing;
 
 nys_status batch_graph(nys_ctx ctx, Batch* B) {
   if (B->graph != nullptr) return NYS_OK;
@@ -887,7 +1216,13 @@ nys_status batch_graph(nys_ctx ctx, Batch* B) {
   hipGraph_t g = nullptr;
   NYS_TRY_HIP(hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
   nys_status s = NYS_OK;
-  for (int i = 0; i < kGraphIters && s == NYS_OK; ++i) s = pcg_iteration(ctx, *B, ctx->cap_stream);
+  for (int i = 0; i < kGraphIters && s == NYS_OK; ++i)
+    s = pcg_iteration(ctx, *B, ctx->cap_stream, i);
+  if (s == NYS_OK) {
+    hipLaunchKernelGGL(k_bcount, dim3(1), dim3(256), 0, ctx->cap_stream, B->insts, B->count,
+                       B->running);
+    if (hipGetLastError() != hipSuccess) s = NYS_ERR_HIP;
+  }
   hipError_t e = hipStreamEndCapture(ctx->cap_stream, &g);
   if (s != NYS_OK) return s;
   NYS_TRY_HIP(e);
@@ -937,13 +1272,13 @@ nys_status batch_pcg(nys_ctx ctx, Batch* B, int max_iter, std::vector<PcgDev>* s
       NYS_TRY_HIP(hipEventRecord(e1, st));
       ctx->prof_used += 2;
     }
-    hipLaunchKernelGGL(k_breduce, dim3(B->n64), dim3(1024), 0, st, B->insts, B->it64, 2);
+    hipLaunchKernelGGL(k_breduce, dim3(B->n64), dim3(1024), 0, st, B->insts, B->it64, 2, 0);
     hipLaunchKernelGGL(k_bdot, dim3(B->ndot), dim3(256), 0, st, B->insts, B->itdot, 3);
   }
   NYS_TRY_HIP(hipGetLastError());
   states->resize(B->count);
-  for (int q = 0; q < B->count; ++q)
-    NYS_TRY_HIP(hipMemcpyAsync(&(*states)[q], B->h[q].st, sizeof(PcgDev), hipMemcpyDeviceToHost, st));
+  NYS_TRY_HIP(hipMemcpyAsync(states->data(), B->states, sizeof(PcgDev) * B->count,
+                             hipMemcpyDeviceToHost, st));
   NYS_TRY_HIP(hipStreamSynchronize(st));
   return NYS_OK;
 }
@@ -960,7 +1295,7 @@ size_t batch_workspace_bytes(int count, int64_t n, int64_t d, int r) {
   return au(sizeof(BInst) * count) + (size_t)count * inst_bytes(n, d) +
          au(sizeof(BTile) * std::max<size_t>(tiles, 1)) + au(sizeof(BItem) * n64) +
          au(sizeof(BItem) * ndot) + au(sizeof(BItem) * n256) + au(sizeof(int)) +
-         au(sizeof(double) * kNS * count);
+         au(sizeof(double) * kNS * count) + au(sizeof(PcgDev) * count);
 }
 
 // Lockstep NysADMM over `count` least-squares problems (see batched.hip header).
@@ -1003,7 +1338,7 @@ nys_status admm_solve_batched(nys_ctx ctx, int count, const nys_problem* P,
   if (s == NYS_OK) {
     s = bgram(B, kModeTOnly, 2, 0, st);
     if (s == NYS_OK)
-      hipLaunchKernelGGL(k_breduce, dim3(B.n64), dim3(1024), 0, st, B.insts, B.it64, 3);
+      hipLaunchKernelGGL(k_breduce, dim3(B.n64), dim3(1024), 0, st, B.insts, B.it64, 3, 0);
   }
   std::vector<double> sc((size_t)kNS * count);
   std::vector<PcgDev> pst;

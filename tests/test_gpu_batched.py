@@ -151,3 +151,45 @@ def test_batched_true_residual_cadence(N, ctx):
             assert 0.0 < i.true_res_max <= 1e-10 * (1 + 1e-6)
     for f in F:
         f.close()
+
+
+@pytest.mark.parametrize("shapes", [
+    # row widths at the edges of the one-launch pair's classes (256, 512, 1024,
+    # 2048 FP32 and 128, 256, 512, 1024 FP64 columns), aligned and not, row
+    # counts at the edges of its tiles (128) and blocks (8, 16, 32)
+    [(1, 3, torch.float32), (127, 512, torch.float32), (128, 513, torch.float32),
+     (129, 511, torch.float32), (300, 1024, torch.float32), (257, 1025, torch.float32)],
+    [(700, 2048, torch.float32), (513, 2047, torch.float32), (200, 256, torch.float64),
+     (161, 257, torch.float64), (385, 513, torch.float64), (260, 1024, torch.float64)],
+    # with instances past it (wide buckets) in the same batch
+    [(400, 2049, torch.float32), (300, 1025, torch.float64), (250, 90, torch.float32)],
+])
+def test_batched_pair_width_and_row_edges(N, ctx, shapes):
+    # the first ADMM step solves (A^T A + rho I) x = A^T b; with a factor whose
+    # lambda is 0 the preconditioner is the identity, so x rests on the pair
+    # alone.  ||A|| = 1 and rho = 0.5: condition 3, so a residual of 1e-13 and
+    # the rounding of sums of at most 2049 terms leave x within 1e-12.
+    g = torch.Generator().manual_seed(17)
+    probs, facs, keep = [], [], []
+    for n, d, dt in shapes:
+        A = torch.randn(n, d, generator=g, dtype=torch.float64)
+        A = (A / torch.linalg.matrix_norm(A, 2)).to(dt)
+        b = torch.randn(n, generator=g, dtype=torch.float64)
+        U = torch.zeros(1, d, dtype=torch.float64)
+        U[0, 0] = 1.0
+        facs.append(N.nys_factor_import(ctx, U.to(DEV), [0.0]))   # P = identity
+        keep.append((A, b, A.to(DEV), b.to(DEV), U.to(DEV)))
+        probs.append(N.problem(keep[-1][2], keep[-1][3], 1e9))    # z stays 0
+    rho = 0.5
+    opts = [N.admm_opts(rho, 1, k[4], factor=f, max_iter=1,   # the test matrix stays unused
+                        pcg=N.pcg_opts(tol=1e-13, max_iter=200)) for f, k in zip(facs, keep)]
+    st = [N.State(k[0].shape[1], DEV) for k in keep]
+    N.admm_solve(ctx, probs, opts, st, allow=(N.NYS_OK, N.NYS_ERR_MAXITER))
+    for (A, b, *_), s in zip(keep, st):
+        A = A.double()
+        x = torch.linalg.solve(A.T @ A + rho * torch.eye(A.shape[1], dtype=torch.float64), A.T @ b)
+        e = float((s.x.cpu() - x).norm() / x.norm())
+        print(f"[batched edges] {tuple(A.shape)}: rel x error {e:.2e}", flush=True)
+        assert e < 1e-12
+    for f in facs:
+        f.close()
