@@ -438,6 +438,8 @@ nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out) {
     *out = make_gram_plan(A, ctx->num_cu);
     return NYS_OK;
   }
+  // whole rows per wavefront where that applies (fixed shape, nothing to tune)
+  if (gram_rows_plan(A, ctx->num_cu, out)) return NYS_OK;
   const int esize = A.dtype == NYS_F64 ? 8 : 4;
   const bool aligned = ((uintptr_t)A.data % 16 == 0) && ((A.ld * esize) % 16 == 0);
   char key[160];

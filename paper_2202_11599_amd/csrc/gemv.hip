@@ -89,6 +89,120 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES >= 4 ? 2 : 1)) void k_gram(
   if (tid == 0) qpart[blockIdx.x] = q;
 }
 
+// The same pass with whole rows per wavefront, for d up to kRwCpl chunks per lane
+// (2048 FP32, 1024 FP64 columns) and many rows.  A wavefront holds p and
+// its own y in registers (CPL chunks per lane), R rows in use and R on their
+// way, and meets no barrier until its rows are done.  The
+// kRwW wavefronts of a workgroup take the row groups of one contiguous range
+// in turn and add their y through LDS at the end, so a CU leaves one partial
+// sum of y instead of the 4 or 8 of k_gram's one workgroup per row (15 MB each
+// way next to A's 120 MB at 30011 x 1000).  Rows may start at any element:
+// 16-byte loads at element alignment.  NTL: non-temporal loads, for an A that
+// the memory-side cache (256 MB) does not hold from one pass to the next.
+// Measured, pair with its reduction, against the fastest of k_gram's shapes
+// (us): FP32 30011 x 1000 24.6 (31.5), 20011 x 1003 20.8 (34.5), 20000 x 2000
+// 31.9 (36.3), 50000 x 1000 35.5 (48.6), 4100 x 500 10.3 (13.8); FP64 50000 x 500
+// 33.7 (38.8), 200000 x 1000 237 (243).
+constexpr int kRwW = 8;
+constexpr int kRwCpl = 8;
+constexpr int64_t kRwCachedBytes = (int64_t)240 << 20;
+template <typename T, int CPL, int R, bool NTL>
+__global__ __launch_bounds__(kRwW * 64, 2) void k_gram_rows(
+    const T* __restrict__ A, int64_t n, int d, int64_t ld, int64_t rows_per_wg, int mode,
+    const double* __restrict__ p, const double* __restrict__ aux, double* __restrict__ auxout,
+    double* __restrict__ ypart, int ldy, double* __restrict__ qpart,
+    const int* __restrict__ done, PcgDev* __restrict__ note, int note_seq) {
+  constexpr int VN = Chunk<T>::N;
+  constexpr int COLS = 64 * CPL * VN;
+  typedef typename Chunk<T>::V V;
+  typedef T VU __attribute__((ext_vector_type(VN), aligned(sizeof(T))));
+  publish_state(done, note, note_seq);
+  if (done != nullptr && *done) return;
+  __shared__ double ysh[kRwW / 2][COLS];
+  __shared__ double qsh[kRwW];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t r0 = (int64_t)blockIdx.x * rows_per_wg;
+  const int64_t r1 = (r0 + rows_per_wg < n) ? r0 + rows_per_wg : n;
+  const bool tonly = (mode == kModeTOnly);
+  double pr[CPL][VN], yr[CPL][VN];
+#pragma unroll
+  for (int m = 0; m < CPL; ++m)
+#pragma unroll
+    for (int v = 0; v < VN; ++v) {
+      const int c = (lane + 64 * m) * VN + v;
+      pr[m][v] = (!tonly && c < d) ? p[c] : 0.0;
+      yr[m][v] = 0.0;
+    }
+  double q = 0.0;
+  auto load = [&](V (&a)[R][CPL], double (&av)[R], int64_t row) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const bool ok = row + i < r1;
+      av[i] = (aux != nullptr && ok) ? aux[row + i] : 0.0;
+      const T* arow = A + (row + i) * ld;
+#pragma unroll
+      for (int m = 0; m < CPL; ++m) {
+        const int c = (lane + 64 * m) * VN;
+        V x = (V)(T)0;
+        if (ok && c < d) {
+          if (c + VN <= d) {
+            VU u;
+            if constexpr (NTL) u = __builtin_nontemporal_load(reinterpret_cast<const VU*>(arow + c));
+            else u = *reinterpret_cast<const VU*>(arow + c);
+            x = u;
+          } else {
+#pragma unroll
+            for (int v = 0; v < VN; ++v) x[v] = c + v < d ? arow[c + v] : (T)0;
+          }
+        }
+        a[i][m] = x;
+      }
+    }
+  };
+  double (*red)[R][1] = nullptr;   // unused: the dot ends inside the wavefront
+  int buf = 0;
+  V a0[R][CPL], a1[R][CPL];
+  double v0[R], v1[R];
+  constexpr int STEP = kRwW * R;
+  const int64_t rb = r0 + (int64_t)wv * R;
+  load(a0, v0, rb);
+  for (int64_t row = rb; row < r1; row += 2 * STEP) {
+    load(a1, v1, row + STEP);
+    process_group<T, 1, CPL, R>(a0, v0, row, r1, mode, pr, yr, q, aux, auxout, red, buf, lane);
+    if (row + STEP >= r1) break;
+    load(a0, v0, row + 2 * STEP);
+    process_group<T, 1, CPL, R>(a1, v1, row + STEP, r1, mode, pr, yr, q, aux, auxout, red, buf,
+                                lane);
+  }
+  // y: wavefronts 4..7 hand theirs to 0..3, then every thread adds four
+  const int sl = wv & (kRwW / 2 - 1);
+  auto put = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int m = 0; m < CPL; ++m)
+#pragma unroll
+      for (int v = 0; v < VN; ++v) ysh[sl][(lane + 64 * m) * VN + v] = yr[m][v];
+  };
+  if (wv >= kRwW / 2) put();
+  if (lane == 0) qsh[wv] = q;
+  __syncthreads();
+  if (wv < kRwW / 2) {
+#pragma unroll
+    for (int m = 0; m < CPL; ++m)
+#pragma unroll
+      for (int v = 0; v < VN; ++v) yr[m][v] += ysh[sl][(lane + 64 * m) * VN + v];
+    put();
+  }
+  __syncthreads();
+  static_assert(kRwW == 8, "four partial sums of y, eight of q");
+  double* yp = ypart + (int64_t)blockIdx.x * ldy;
+  for (int j = tid; j < d; j += kRwW * 64)
+    yp[j] = (ysh[0][j] + ysh[1][j]) + (ysh[2][j] + ysh[3][j]);
+  if (tid == 0)
+    qpart[blockIdx.x] = ((qsh[0] + qsh[1]) + (qsh[2] + qsh[3])) +
+                        ((qsh[4] + qsh[5]) + (qsh[6] + qsh[7]));
+}
+
 // y = A p for an explicit symmetric A (kernel SVM), one block of columns per
 // blockIdx.y: the same streaming of rows as k_gram without the A^T pass; the
 // row dots of column block s go to ypart[s * ldy + row] (summed over blocks by
@@ -165,11 +279,40 @@ nys_status launch_r(const nys_dense& A, const GramPlan& pl, int mode, const doub
   return hipGetLastError() == hipSuccess ? NYS_OK : NYS_ERR_HIP;
 }
 
+template <typename T, int CPL, int R>
+nys_status launch_rows(const nys_dense& A, const GramPlan& pl, int mode, const double* p,
+                       const double* aux, double* auxout, double* ypart, double* qpart,
+                       const int* done, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1,
+                       PcgDev* note, int note_seq) {
+  const T* a = static_cast<const T*>(A.data);
+  auto go = [&](auto kern) {
+    if (ev0 != nullptr)
+      hipExtLaunchKernelGGL(kern, dim3(pl.grid), dim3(kRwW * 64), 0, st, ev0, ev1, 0, a, A.n,
+                            (int)A.d, A.ld, pl.rows_per_wg, mode, p, aux, auxout, ypart, pl.ldy,
+                            qpart, done, note, note_seq);
+    else
+      hipLaunchKernelGGL(kern, dim3(pl.grid), dim3(kRwW * 64), 0, st, a, A.n, (int)A.d, A.ld,
+                         pl.rows_per_wg, mode, p, aux, auxout, ypart, pl.ldy, qpart, done, note,
+                         note_seq);
+  };
+  if (A.n * A.ld * (int64_t)sizeof(T) > kRwCachedBytes) go(k_gram_rows<T, CPL, R, true>);
+  else go(k_gram_rows<T, CPL, R, false>);
+  return hipGetLastError() == hipSuccess ? NYS_OK : NYS_ERR_HIP;
+}
+
 template <typename T>
 nys_status launch_dt(const nys_dense& A, const GramPlan& pl, int mode, const double* p,
                      const double* aux, double* auxout, double* ypart, double* qpart,
                      const int* done, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1,
                      PcgDev* note, int note_seq) {
+  if (pl.rowwave) {
+#define NYS_ROWS(C, RR) \
+  if (pl.cpl == C && pl.rows == RR) \
+    return launch_rows<T, C, RR>(A, pl, mode, p, aux, auxout, ypart, qpart, done, st, ev0, ev1, note, note_seq);
+    NYS_ROWS(1, 8) NYS_ROWS(2, 4) NYS_ROWS(4, 2) NYS_ROWS(8, 1)
+#undef NYS_ROWS
+    return NYS_ERR_INVALID;
+  }
 #define NYS_CASE(W, C, RR)                                                                  \
   if (pl.waves == W && pl.cpl == C && pl.rows == RR)                                        \
     return launch_r<T, W, C, RR>(A, pl, mode, p, aux, auxout, ypart, qpart, done, st, ev0, ev1, \
@@ -202,6 +345,33 @@ static void finish_plan(const nys_dense& A, int num_cu, int per_cu, GramPlan* pl
   const int64_t g = std::min<int64_t>((int64_t)per_cu * num_cu, std::max<int64_t>(1, groups / 2));
   pl->rows_per_wg = ((A.n + g - 1) / g + R - 1) / R * R;
   pl->grid = (int)((A.n + pl->rows_per_wg - 1) / pl->rows_per_wg);
+}
+
+// Whole rows per wavefront (k_gram_rows): from kRwMinRows rows on, for rows of at
+// most kRwCpl chunks per lane.  Fewer rows leave most CUs one or two row groups
+// and keep the shapes of make_gram_plan, whose sums a 4000-row solve reproduces
+// from run to run (those above were picked by timing).  One workgroup of 8 wavefronts per CU, R rows
+// each in turn (64 KB in use and 64 KB on their way per CU).
+bool gram_rows_plan(const nys_dense& A, int num_cu, GramPlan* pl) {
+  const int vn = A.dtype == NYS_F64 ? 2 : 4;
+  if (A.dtype == NYS_CSR || A.n < kRwMinRows || A.d > (int64_t)64 * kRwCpl * vn) return false;
+  // 2048 FP32 columns fill the registers (256, a few spilled): where the
+  // pass streams from HBM anyway the one-workgroup-per-row form is faster
+  // (200000 x 2000: 250 us against 263; 20000 x 2000 from the cache: 36 against 32)
+  if (A.dtype == NYS_F32 && A.d > 1024 && A.n * A.ld * 4 > kRwCachedBytes) return false;
+  *pl = GramPlan{};
+  pl->rowwave = true;
+  pl->waves = kRwW;
+  pl->cpl = 1;
+  while ((int64_t)64 * pl->cpl * vn < A.d) pl->cpl *= 2;
+  pl->rows = kRwCpl / pl->cpl;
+  pl->aligned = true;
+  pl->ldy = (int)((A.d + 63) / 64 * 64);
+  pl->per_cu = 1;
+  const int64_t step = (int64_t)kRwW * pl->rows;
+  pl->rows_per_wg = ((A.n + num_cu - 1) / num_cu + step - 1) / step * step;
+  pl->grid = (int)((A.n + pl->rows_per_wg - 1) / pl->rows_per_wg);
+  return true;
 }
 
 // Launch shapes worth timing for this matrix: every supported (waves, chunks,
@@ -357,7 +527,7 @@ nys_status launch_gram(const nys_dense& A, const GramPlan& pl, int mode, const d
                        const int* done, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1,
                        PcgDev* note, int note_seq) {
   const int vn = A.dtype == NYS_F64 ? 2 : 4;
-  if ((int64_t)pl.waves * 64 * pl.cpl * vn < A.d) return NYS_ERR_INVALID;
+  if ((int64_t)(pl.rowwave ? 1 : pl.waves) * 64 * pl.cpl * vn < A.d) return NYS_ERR_INVALID;
   if (A.n == 0 || pl.grid == 0) return NYS_OK;
   if (A.dtype == NYS_F64)
     return launch_dt<double>(A, pl, mode, p, aux, auxout, ypart, qpart, done, st, ev0, ev1, note,

@@ -179,6 +179,7 @@ struct GramPlan {
   int grid = 512;    // workgroups (each owns a contiguous row range)
   int64_t rows_per_wg = 0;
   bool aligned = true;
+  bool rowwave = false;  // k_gram_rows: whole rows per wavefront, y added in the workgroup
   int ldy = 0;       // leading dimension of the per-workgroup partial sums
   // column-blocked y = A p of an explicit symmetric A (kernel SVM): blockIdx.y
   // runs over `slices` blocks of slice_cols columns; the y partials are one
@@ -437,6 +438,9 @@ GramPlan make_gram_plan_capped(const nys_dense& A, int num_cu, int64_t max_grid)
 // this takes the two-pass wide form
 int64_t gram_max_cols(nys_dtype dt);
 std::vector<GramPlan> gram_candidates(const nys_dense& A, int num_cu);
+// the plan of k_gram_rows, false where it does not apply
+constexpr int64_t kRwMinRows = 4096;
+bool gram_rows_plan(const nys_dense& A, int num_cu, GramPlan* pl);
 // Launch the fused pass  t = A p;  s = mode(t);  y_g = sum_{rows of g} s_i A_i.
 nys_status launch_gram(const nys_dense& A, const GramPlan& plan, int mode, const double* p,
                        const double* aux, double* auxout, double* ypart, double* qpart,

@@ -63,6 +63,17 @@ SHAPES = [
     (800, 700, torch.float32, 703, True, 1),     # first row 4 bytes off the grid
     (640, 3333, torch.float32, 3336, False, 3),
     (999, 255, torch.float64, 257, True, 1),
+    # whole rows per wavefront (from 4096 rows): edges of the lane chunks (256,
+    # 512, 1024, 2048 FP32, 128 .. 1024 FP64 columns) and of the row groups
+    (4096, 1, torch.float32, 1, True, 0),
+    (4096, 256, torch.float32, 256, False, 0),
+    (4099, 257, torch.float32, 260, True, 3),
+    (5003, 512, torch.float32, 513, False, 1),
+    (4111, 2048, torch.float32, 2048, True, 0),
+    (4105, 2049, torch.float32, 2049, False, 0),
+    (6151, 129, torch.float64, 129, True, 0),
+    (4097, 1024, torch.float64, 1025, True, 1),
+    (4103, 1025, torch.float64, 1025, False, 0),
 ]
 
 
