@@ -302,20 +302,36 @@ nys_status validate_dense(const nys_dense* A) {
   return NYS_OK;
 }
 
-nys_status check_vector(nys_ctx ctx, const double* v, int64_t n, int kind) {
+nys_status check_begin(nys_ctx ctx, const double* v, int64_t n, int kind, VecCheck* c) {
+  *c = VecCheck{};
   if (v == nullptr || n <= 0) return NYS_OK;
-  NYS_TRY(ctx->check.reserve(256));
-  int* flag = ctx->check.as<int>();
-  NYS_TRY_HIP(hipMemsetAsync(flag, 0, sizeof(int), ctx->stream));
-  NYS_TRY(launch_check_vec(v, n, kind, flag, ctx->stream));
-  NYS_TRY_HIP(hipMemcpyAsync(ctx->host_pinned, flag, sizeof(int), hipMemcpyDeviceToHost,
-                             ctx->stream));
-  NYS_TRY_HIP(hipStreamSynchronize(ctx->stream));
+  // sequence numbers are unique per context: stale slot contents never match
+  ctx->poll_seq = (ctx->poll_seq % 1000000000) + 1;
+  c->seq = (unsigned)ctx->poll_seq;
+  return launch_check_vec(v, n, kind,
+                          reinterpret_cast<unsigned long long*>(
+                              static_cast<char*>(ctx->host_pinned_dev) + kCheckSlotOffset),
+                          c->seq, &c->grid, ctx->stream);
+}
+
+nys_status check_end(nys_ctx ctx, const VecCheck& c) {
+  const auto* slots = reinterpret_cast<const volatile unsigned long long*>(
+      static_cast<char*>(ctx->host_pinned) + kCheckSlotOffset);
   int bits = 0;
-  std::memcpy(&bits, ctx->host_pinned, sizeof(int));
+  for (int g = 0; g < c.grid; ++g) {
+    int b = 0;
+    NYS_TRY(wait_word(ctx->stream, slots + g, c.seq, &b));
+    bits |= b;
+  }
   if (bits & kCheckNonfinite) return NYS_ERR_NONFINITE;
   if (bits & kCheckBad) return NYS_ERR_INVALID;
   return NYS_OK;
+}
+
+nys_status check_vector(nys_ctx ctx, const double* v, int64_t n, int kind) {
+  VecCheck c;
+  NYS_TRY(check_begin(ctx, v, n, kind, &c));
+  return check_end(ctx, c);
 }
 
 // Carves the PCG workspace out of the context buffers.
@@ -798,7 +814,6 @@ nys_status nys_ctx_destroy(nys_ctx ctx) {
   ctx->core_ws.release();
   ctx->admm_ws.release();
   ctx->svm_ws.release();
-  ctx->check.release();
   pool_unregister_stream(ctx->device, ctx->stream);
   if (ctx->host_pinned) (void)hipHostFree(ctx->host_pinned);
   for (hipEvent_t e : ctx->prof_ev) (void)hipEventDestroy(e);
@@ -897,7 +912,6 @@ nys_status nys_ctx_set_workspace(nys_ctx ctx, void* dev_ptr, size_t bytes) {
   ctx->core_ws.release();
   ctx->admm_ws.release();
   ctx->svm_ws.release();
-  ctx->check.release();
   ctx->atb_key = AtbKey{};
   ctx->atb_next_k = -1;
   ctx->hx_key = AtbKey{};
@@ -947,13 +961,13 @@ nys_status nys_workspace_query(nys_ctx ctx, const nys_dense* A, int r_max, int c
                                 align_up(sizeof(double) * pl.tmp_doubles()));
   }
   total += 2 * part + align_up(sizeof(double) * d);
-  // PCG vectors and scalars, H_rho x, the argument-check flag
+  // PCG vectors and scalars, H_rho x
   const size_t nv = align_up(sizeof(double) * d);
   total += 3 * nv + align_up(sizeof(double) * kCvecDoubles) +
            align_up(sizeof(double) * kWyRing);
   total += align_up(sizeof(PcgDev)) + 4 * align_up(sizeof(double) * (size_t)nblk(d, kRedBlock)) +
            align_up(sizeof(double) * (size_t)nblk(d, vec_block(d)));
-  total += nv + 256;
+  total += nv;
   // ADMM vectors
   total += admm_ws_bytes(n, d);
   // sketch temporaries and the factors alive at once: one per instance when
@@ -1070,12 +1084,20 @@ nys_status nys_hessian_apply(nys_ctx ctx, const nys_dense* A, const double* D, d
   if (!(rho + c >= 0.0)) return NYS_ERR_INVALID;
   NYS_TRY_HIP(hipSetDevice(ctx->device));
   nys::CtxScope ctx_scope(ctx);
-  NYS_TRY(check_vector(ctx, D, A->n, 0));
+  // D's check runs before the pass over A and is waited for while that runs;
+  // v is only written after it
+  VecCheck chk;
+  NYS_TRY(check_begin(ctx, D, A->n, 0, &chk));
   GramPlan pl;
-  NYS_TRY(ctx_gram_plan(ctx, *A, &pl));
   PcgWs ws;
-  NYS_TRY(pcg_workspace(ctx, pl, A->d, 1, &ws));
-  NYS_TRY(ctx_gram(ctx, *A, pl, kModeHess, p, D, nullptr, ws.ypart, ws.qpart, nullptr));
+  auto pass = [&]() -> nys_status {
+    NYS_TRY(ctx_gram_plan(ctx, *A, &pl));
+    NYS_TRY(pcg_workspace(ctx, pl, A->d, 1, &ws));
+    return ctx_gram(ctx, *A, pl, kModeHess, p, D, nullptr, ws.ypart, ws.qpart, nullptr);
+  };
+  const nys_status passed = pass();
+  NYS_TRY(check_end(ctx, chk));
+  NYS_TRY(passed);
   NYS_TRY(launch_reduce_update(3, ws.ypart, pl.ny(), pl.ldy, ws.qpart, A->d, rho + c, p, nullptr,
                                v, nullptr, nullptr, 0, nullptr, 0, nullptr, nullptr, ws.st,
                                ctx->stream, pl.nq()));

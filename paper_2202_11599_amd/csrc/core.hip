@@ -1675,16 +1675,11 @@ size_t jacobi_ws_doubles(int r) {
   return 2 * (size_t)R * R + (size_t)R * R + 2 * (size_t)np * kJP * kJP + 2 * (size_t)R + 128;
 }
 
-// Eigendecomposition of the symmetric r x r matrix G (row-major, ld) by block
-// Jacobi.  Outputs: sig2 (r, descending) and W (r x r row-major, ldw) with
-// W(:, c) = v_c / sqrt(sig2_c).  ws must hold jacobi_ws_doubles(r) doubles;
-// counters (>= max_sweeps ints) and host_flag are scratch.  Returns
-// NYS_ERR_NOT_CONVERGED if a sweep still rotated after max_sweeps.
 // Wait until the device has written sequence number seq into the slot; once
 // the slot has stayed unwritten for a few milliseconds the stream is queried
 // (PollPace) so that a failed or drained stream ends the wait with an error.
-nys_status wait_jacobi_slot(hipStream_t st, const volatile unsigned long long* slot, unsigned seq,
-                            int* val) {
+nys_status wait_word(hipStream_t st, const volatile unsigned long long* slot, unsigned seq,
+                     int* val) {
   PollPace pace;
   for (long n = 1;; ++n) {
     unsigned long long v = *slot;
@@ -1706,6 +1701,11 @@ nys_status wait_jacobi_slot(hipStream_t st, const volatile unsigned long long* s
   }
 }
 
+// Eigendecomposition of the symmetric r x r matrix G (row-major, ld) by block
+// Jacobi.  Outputs: sig2 (r, descending) and W (r x r row-major, ldw) with
+// W(:, c) = v_c / sqrt(sig2_c).  ws must hold jacobi_ws_doubles(r) doubles;
+// counters (>= max_sweeps ints) and host_flag are scratch.  Returns
+// NYS_ERR_NOT_CONVERGED if a sweep still rotated after max_sweeps.
 nys_status jacobi_eig(hipStream_t st, const double* G, int r, int ld, double* ws, int* counters,
                       int max_sweeps, void* host_pinned, void* host_pinned_dev, int* poll_seq,
                       double* sig2, double* W, int ldw, int* sweeps_out, const double* V0,
@@ -1772,7 +1772,7 @@ nys_status jacobi_eig(hipStream_t st, const double* G, int r, int ld, double* ws
       ++enq;
     }
     int flag = 1;
-    NYS_TRY(wait_jacobi_slot(st, slots_h + (s % 4), seqs[s], &flag));
+    NYS_TRY(wait_word(st, slots_h + (s % 4), seqs[s], &flag));
     ++sweeps;
     if (flag == 0) {
       converged = true;

@@ -279,8 +279,17 @@ nys_status ctx_gram(nys_ctx ctx, const nys_dense& A, const GramPlan& plan, int m
                     const double* p, const double* aux, double* auxout, double* ypart,
                     double* qpart, const int* done, PcgDev* note = nullptr, int note_seq = 0);
 nys_status validate_dense(const nys_dense* A);
-// Device check of a caller's n-vector (kind as launch_check_vec); synchronises.
-// NYS_ERR_NONFINITE for NaN/Inf, NYS_ERR_INVALID for a broken rule.
+// Device check of a caller's n-vector (kind as launch_check_vec), in two parts:
+// check_begin enqueues it on the context's stream, check_end waits for its
+// result (NYS_ERR_NONFINITE for NaN/Inf, NYS_ERR_INVALID for a broken rule).
+// Work enqueued between them must write nothing that the caller owns.  Every
+// begun check is ended before the call returns; check_vector does both.
+struct VecCheck {
+  int grid = 0;        // workgroups that report, 0: nothing to wait for
+  unsigned seq = 0;
+};
+nys_status check_begin(nys_ctx ctx, const double* v, int64_t n, int kind, VecCheck* c);
+nys_status check_end(nys_ctx ctx, const VecCheck& c);
 nys_status check_vector(nys_ctx ctx, const double* v, int64_t n, int kind);
 nys_status pcg_workspace(nys_ctx ctx, const GramPlan& pl, int64_t d, int max_iter, PcgWs* ws);
 nys_status read_pcg_state(nys_ctx ctx, const PcgWs& ws, PcgDev* out);
@@ -311,6 +320,10 @@ nys_status gemm64(hipStream_t st, int M, int N, int K, const void* A, bool a_f32
 nys_status chol_upper(hipStream_t st, double* M, int r, int ld, int* fail);
 nys_status trinv_upper(hipStream_t st, const double* Cm, int r, int ld, double* Z, int ldz);
 nys_status power_iter(hipStream_t st, const double* G, int r, int ld, int iters, double* out);
+// Wait for sequence number seq in the upper half of a pinned 8-byte slot that a
+// kernel of the stream writes; *val = its lower half
+nys_status wait_word(hipStream_t st, const volatile unsigned long long* slot, unsigned seq,
+                     int* val);
 int jacobi_pad(int r);
 size_t jacobi_ws_doubles(int r);
 // V0 (may be NULL): r x r column-major orthonormal start basis (the
@@ -360,6 +373,9 @@ struct AtbKey {
 constexpr size_t kPinnedBytes = 65536;     // pinned readback area of a context
 constexpr size_t kPollOffset = 61440;      // PCG polling slots (4 x 64 bytes) in it
 constexpr size_t kJacSlotOffset = kPollOffset + 512;   // eigensolver sweep slots (4 x 8 bytes)
+constexpr size_t kCheckSlotOffset = kPollOffset + 1024;   // argument check slots (8 bytes each)
+constexpr int kCheckGrid = 256;
+static_assert(kCheckSlotOffset + 8 * kCheckGrid <= kPinnedBytes, "slots in the pinned area");
 
 struct nys_ctx_s {
   int device = 0;
@@ -372,11 +388,10 @@ struct nys_ctx_s {
   nys::DevBuf core_ws;   // FP64 core temporaries
   nys::DevBuf admm_ws;   // ADMM vectors (A^T b, rhs, weights, ...)
   nys::DevBuf svm_ws;    // kernel SVM vectors (rhs, H z, scalars)
-  nys::DevBuf check;     // flag word of the argument checks
   std::shared_ptr<nys::Arena> arena;   // caller's workspace (nys_ctx_set_workspace), or none
   void* host_pinned = nullptr;  // pinned readback area of kPinnedBytes
   void* host_pinned_dev = nullptr;  // the same memory as seen from the device
-  int poll_seq = 0;              // last sequence number of a PCG state slot write
+  int poll_seq = 0;              // last sequence number of a pinned slot's write
   AtbKey atb_key;                // which (A, b) the cached A^T b in admm_ws belongs to
   int64_t atb_next_k = -1;       // ... valid for the ADMM step with this counter
   nys::DevBuf hx;                // H_rho x of the last solve (lasso ADMM sequence)
@@ -575,11 +590,13 @@ nys_status launch_u_c(const double* U, int64_t d, int r, const double* c, double
                       hipStream_t stream);
 nys_status launch_dot(const double* a, const double* b, int64_t d, double* out,
                       hipStream_t stream);
-// flags |= kCheck* bits of the caller vector v (n entries): kind 0 weights
-// (v >= 0), kind 1 labels (v in {0, 1}); NaN/Inf set kCheckNonfinite
+// The kCheck* bits of the caller vector v (n entries): kind 0 weights
+// (v >= 0), kind 1 labels (v in {0, 1}); NaN/Inf set kCheckNonfinite.  Each of
+// the *grid <= kCheckGrid workgroups writes (seq << 32) | bits to its slot.
 constexpr int kCheckBad = 1;
 constexpr int kCheckNonfinite = 2;
-nys_status launch_check_vec(const double* v, int64_t n, int kind, int* flags, hipStream_t stream);
+nys_status launch_check_vec(const double* v, int64_t n, int kind, unsigned long long* slots,
+                            unsigned seq, int* grid, hipStream_t stream);
 // mode 0: PCG iteration k test + dots, 1: PCG init (threshold from ||rhs||) test + dots,
 // 2: dots only, 3: store sum(wwpart) into st->true_rr
 nys_status launch_precond_dot(const void* U, bool u32, int64_t d, int r, const double* w,

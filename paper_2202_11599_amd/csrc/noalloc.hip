@@ -24,7 +24,7 @@ namespace {
 // then the scalar slots
 constexpr size_t kPartBytes = size_t(16) << 20;
 constexpr size_t kQBytes = size_t(32) << 10;    // up to 4096 workgroups
-constexpr size_t kSlotBytes = 256;              // p^T v (double) and the check flag (int)
+constexpr size_t kSlotBytes = 256;              // p^T v (double)
 constexpr size_t kScratchBytes = kPartBytes + kQBytes + kSlotBytes;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -32,10 +32,6 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_mu;
 void* g_scratch[kMaxDevices] = {};
-
-__global__ void k_clear_flag(int* flag) {
-  if (threadIdx.x == 0) *flag = 0;
-}
 
 void* scratch_of(int device) {
   if (device < 0 || device >= kMaxDevices) return nullptr;
@@ -75,20 +71,9 @@ nys_status nys_hessian_apply_noalloc(nys_ctx ctx, const nys_dense* A, const doub
   double* ypart = reinterpret_cast<double*>(base);
   double* qpart = reinterpret_cast<double*>(base + kPartBytes);
   double* pv_dev = reinterpret_cast<double*>(base + kPartBytes + kQBytes);
-  int* flag = reinterpret_cast<int*>(base + kPartBytes + kQBytes + 64);
   hipStream_t st = ctx->stream;
 
-  if (D != nullptr) {
-    // D >= 0 and finite, as nys_hessian_apply checks it (synchronises)
-    hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(64), 0, st, flag);
-    NYS_TRY(launch_check_vec(D, A->n, 0, flag, st));
-    NYS_TRY_HIP(hipMemcpyAsync(ctx->host_pinned, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-    NYS_TRY_HIP(hipStreamSynchronize(st));
-    int bits = 0;
-    std::memcpy(&bits, ctx->host_pinned, sizeof(int));
-    if (bits & kCheckNonfinite) return NYS_ERR_NONFINITE;
-    if (bits & kCheckBad) return NYS_ERR_INVALID;
-  }
+  NYS_TRY(check_vector(ctx, D, A->n, 0));   // as nys_hessian_apply checks it (waits for it)
 
   // the heuristic launch shape (the autotuner would allocate), with at most as
   // many workgroups as the scratch holds partial rows for

@@ -149,3 +149,24 @@ def test_svm_maxiter_counted(N, ctx):
     o = N.svm_opts(1.0, 0, pcg=N.pcg_opts(tol=1e-14, max_iter=2), max_iter=5)
     info = N.svm_solve(ctx, H, bd, 1.0, o, st)
     assert info.iters == 5 and info.maxiter_solves == 5 and info.status == N.NYS_ERR_MAXITER
+
+
+@pytest.mark.parametrize("n", [1, 1024, 1025, 256 * 1024 + 1, 4 * 256 * 1024 + 3])
+def test_weight_check_reaches_every_entry(N, ctx, n):
+    """The first, middle and last weight at the edges of the check's workgroups
+    and of its rounds; a refused call leaves its output as it was."""
+    A = torch.ones((n, 3), dtype=torch.float32, device=DEV)
+    p = torch.ones(3, dtype=torch.float64, device=DEV)
+    D = torch.ones(n, dtype=torch.float64, device=DEV)
+    for at in sorted({0, n // 2, n - 1}):
+        for bad, want in ((-1.0, N.NYS_ERR_INVALID), (float("nan"), N.NYS_ERR_NONFINITE)):
+            out = torch.full((3,), 7.0, dtype=torch.float64, device=DEV)
+            D[at] = bad
+            got = status_of(N, lambda: N.nys_hessian_apply(ctx, A, p, rho=0.0, D=D, out=out))
+            D[at] = 1.0
+            torch.cuda.synchronize()
+            assert got == want and bool((out == 7.0).all()), (n, at, bad)
+    out = torch.zeros(3, dtype=torch.float64, device=DEV)
+    N.nys_hessian_apply(ctx, A, p, rho=0.0, D=D, out=out)
+    torch.cuda.synchronize()
+    assert bool((out == 3.0 * n).all())   # whole numbers: exact
