@@ -583,25 +583,35 @@ nys_status pcg_run(nys_ctx ctx, const nys_dense& A, const double* D, double c, d
   const double* lam = F ? F->lam.as<double>() : nullptr;
   const double lam_s = (F && r > 0) ? F->lam_host[r - 1] : 0.0;
 
+  // three launches an iteration where U^T w fits the partial reduction
+  const int fb = ws.rj == kRedBlock && pl.ldy % 2 == 0 ? fused_dot_block(d, r) : 0;
+  const bool fuse = fb > 0;
+  if (fuse) {   // no more ||w||^2 partials than pcg_workspace made room for
+    ws.rj = fb;
+    ws.nred = nblk(d, fb);
+  }
+  const FusedDot fdot{U, u32, r, (r + 1) / 2 * 2, ws.nred, ws.cvec};
+
   int total_iters = 0, restarts = 0;
   PcgDev h{};
   nys_status status = NYS_OK;
   double true_rr = -1.0;
   for (;;) {
     NYS_TRY(launch_zero_state(ws.st, st));
-    // w0 = rhs - H_rho x0 ; y0 = P^-1 w0 ; p0 = y0
+    // w0 = rhs - H_rho x0 ; y0 = P^-1 w0 ; p0 = y0 (the judge may still change w0)
+    const FusedDot* dot0 = fuse && !(x_alt != nullptr && restarts == 0) ? &fdot : nullptr;
     const AtbKey key{A.data, D, A.n, d, A.ld, x};
     if (hx_tag >= 0 && restarts == 0 && ctx->hx_tag == hx_tag && ctx->hx_key == key &&
         ctx->hx_rho == rho && ctx->hx_c == c) {
       // H_rho x0 from the previous solve's true-residual pass (x0 unchanged)
       NYS_TRY(launch_reduce_update(1, ws.ypart, 0, pl.ldy, ws.qpart, d, 1.0, ctx->hx.as<double>(),
                                    nullptr, ws.w, rhs, ws.wy, 0, nullptr, 0, ws.wwpart, ws.rrpart,
-                                   ws.st, st, -1, false, ws.rj));
+                                   ws.st, st, -1, false, ws.rj, dot0));
     } else {
       NYS_TRY(ctx_gram(ctx, A, pl, kModeHess, x, D, nullptr, ws.ypart, ws.qpart, nullptr));
       NYS_TRY(launch_reduce_update(1, ws.ypart, pl.ny(), pl.ldy, ws.qpart, d, rho_eff, x, nullptr,
                                    ws.w, rhs, ws.wy, 0, nullptr, 0, ws.wwpart, ws.rrpart, ws.st,
-                                   st, pl.nq()));
+                                   st, pl.nq(), false, ws.rj, dot0));
     }
     ctx->hx_key = AtbKey{};
     if (x_alt != nullptr && restarts == 0) {
@@ -610,13 +620,15 @@ nys_status pcg_run(nys_ctx ctx, const nys_dense& A, const double* D, double c, d
       NYS_TRY(ctx_gram(ctx, A, pl, kModeHess, x_alt, D, nullptr, ws.ypart, ws.qpart, nullptr));
       NYS_TRY(launch_reduce_update(1, ws.ypart, pl.ny(), pl.ldy, ws.qpart, d, rho_eff, x_alt,
                                    nullptr, ws.w2, rhs, ws.wy, 0, nullptr, 0, ws.wwpart2,
-                                   ws.rrpart2, ws.st, st, pl.nq()));
+                                   ws.rrpart2, ws.st, st, pl.nq(), false, ws.rj));
       NYS_TRY(launch_judge(ws.wwpart, ws.wwpart2, ws.nred, x, x_alt, ws.w, ws.w2, d, ws.st, st));
     }
-    NYS_TRY(launch_precond_dot(U, u32, d, r, ws.w, ws.cvec, ws.st, ws.wwpart, ws.nred,
-                               ws.rrpart, -1, 1, tol_rel, tol_abs, st));
+    if (dot0 == nullptr)
+      NYS_TRY(launch_precond_dot(U, u32, d, r, ws.w, ws.cvec, ws.st, ws.wwpart, ws.nred,
+                                 ws.rrpart, -1, 1, tol_rel, tol_abs, st));
     NYS_TRY(launch_precond_update(U, u32, d, r, lam, lam_s, rho, ws.cvec, ws.w, ws.p, ws.wy, 0,
-                                  ws.wwpart, ws.nred, ws.pppart, ws.st, 1, st));
+                                  ws.wwpart, ws.nred, ws.pppart, ws.st, 1, st, nullptr, 0, false,
+                                  nullptr, dot0, ws.rrpart, tol_rel, tol_abs));
     // Iterations are enqueued `ahead` at a time beyond the last state the host
     // has read: the state after each iteration reaches a pinned host slot with
     // a sequence number (copied there by the first thread of the next
@@ -642,10 +654,11 @@ nys_status pcg_run(nys_ctx ctx, const nys_dense& A, const double* D, double c, d
         NYS_TRY(launch_pcg_scalar(0, ws.qpart, pl.nq(), ws.pppart, ws.nvec, rho_eff, ws.st, st));
       NYS_TRY(launch_reduce_update(0, ws.ypart, pl.ny(), pl.ldy, ws.qpart, d, rho_eff, ws.p, x,
                                    ws.w, nullptr, ws.wy, k, ws.pppart, ws.nvec, ws.wwpart, nullptr,
-                                   ws.st, st, pl.nq(), pre));
+                                   ws.st, st, pl.nq(), pre, ws.rj, fuse ? &fdot : nullptr));
       if (pre) NYS_TRY(launch_pcg_scalar(1, ws.wwpart, ws.nred, nullptr, 0, 0.0, ws.st, st));
-      NYS_TRY(launch_precond_dot(U, u32, d, r, ws.w, ws.cvec, ws.st, ws.wwpart, ws.nred, nullptr,
-                                 k, 0, tol_rel, tol_abs, st, pre));
+      if (!fuse)
+        NYS_TRY(launch_precond_dot(U, u32, d, r, ws.w, ws.cvec, ws.st, ws.wwpart, ws.nred, nullptr,
+                                   k, 0, tol_rel, tol_abs, st, pre));
       // sequence numbers are unique per context, so a late write from an
       // earlier solve's queued iteration can never be taken for this one
       const int seq = ctx->poll_seq = (ctx->poll_seq % 1000000000) + 1;
@@ -656,7 +669,7 @@ nys_status pcg_run(nys_ctx ctx, const nys_dense& A, const double* D, double c, d
       if (pre) NYS_TRY(launch_c_reduce(ws.cvec, d, r, lam, lam_s, rho, gvec, ws.st, st));
       NYS_TRY(launch_precond_update(U, u32, d, r, lam, lam_s, rho, ws.cvec, ws.w, ws.p, ws.wy, k,
                                     ws.wwpart, ws.nred, ws.pppart, ws.st, 0, st, nullptr, seq,
-                                    pre, pre ? gvec : nullptr));
+                                    pre, pre ? gvec : nullptr, fuse ? &fdot : nullptr));
       return NYS_OK;
     };
     int it = 0, consumed = 0;
@@ -719,7 +732,7 @@ nys_status pcg_run(nys_ctx ctx, const nys_dense& A, const double* D, double c, d
     NYS_TRY(ctx_gram(ctx, A, pl, kModeHess, x, D, nullptr, ws.ypart, ws.qpart, nullptr));
     NYS_TRY(launch_reduce_update(2, ws.ypart, pl.ny(), pl.ldy, ws.qpart, d, rho_eff, x, hx_out,
                                  ws.w, rhs, ws.wy, 0, nullptr, 0, ws.wwpart, nullptr, ws.st, st,
-                                 pl.nq()));
+                                 pl.nq(), false, ws.rj));
     if (hx_tag >= 0) {
       ctx->hx_key = key;
       ctx->hx_rho = rho;

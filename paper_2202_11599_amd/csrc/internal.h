@@ -560,14 +560,40 @@ inline int nblk(int64_t d, int b) { return (int)((d + b - 1) / b); }
 //   op 2 (true):    w = rhs - v  (true residual, FP64 accumulation); v -> x if x != NULL
 //   op 3 (plain):   w = v
 //   op 4 (carry):   x = rhs - w  (H_rho x from the recursive residual; ypart unused)
+// c = U^T w formed by the partial reduction (op 0 and 1): its `parts`
+// workgroups leave partials of ldc entries (ldc = r rounded up to even), which
+// are added, and ||w||^2 tested, by launch_precond_update.
+struct FusedDot {
+  const void* U = nullptr;
+  bool u32 = false;
+  int r = 0, ldc = 0, parts = 0;
+  double* cpart = nullptr;
+};
+// Columns per workgroup of that reduction; 0: a launch of its own for U^T w.
+// Every workgroup of the update reads all partials, so they are bounded, and
+// from 1025 columns on there are half as many.  Microseconds of an iteration
+// with four launches, with 16 and with 32 columns per workgroup:
+//   5000 x 1000 rank  50   22.0  19.9  20.7
+//   5000 x 2000 rank 100   28.0  27.3  26.1
+//   4000 x 8000 rank  60   51.2   -    47.8
+//   5000 x 4000 rank 400   42.6   -    45.2   (50000 entries: four launches)
+constexpr int kRedBlockWide = 32;
+constexpr int kFusedDotMax = 16384;
+inline int fused_dot_block(int64_t d, int r) {
+  const int ldc = (r + 1) / 2 * 2;
+  const int b = d > 1024 ? kRedBlockWide : kRedBlock;
+  return d <= kPreReduceDim && ldc <= 512 && (int64_t)nblk(d, b) * ldc <= kFusedDotMax ? b : 0;
+}
+static_assert(kFusedDotMax <= (int)kCvecDoubles, "partials in cvec");
 nys_status launch_reduce_update(int op, const double* ypart, int G, int ldy, const double* qpart,
                                 int64_t d, double rho_eff, const double* p, double* x, double* w,
                                 const double* rhs, double* wy, int k, const double* pppart,
                                 int npp, double* wwpart, double* rrpart, PcgDev* st,
                                 hipStream_t stream, int Gq = -1,   // Gq: q partials (-1: G)
                                 bool pre = false,                  // alpha from st->pv
-                                int rj = 0);  // columns per workgroup (0: red_block(G)); the
+                                int rj = 0,   // columns per workgroup (0: red_block(G)); the
                                               // ||w||^2 partials number nblk(d, rj)
+                                const FusedDot* dot = nullptr);
 // *slot = *st with k = seq (one thread): publish_state for an iteration that
 // no matvec launch follows
 nys_status launch_zero_state(PcgDev* st, hipStream_t stream);
@@ -607,9 +633,11 @@ nys_status launch_precond_dot(const void* U, bool u32, int64_t d, int r, const d
 nys_status launch_precond_update(const void* U, bool u32, int64_t d, int r, const double* lam,
                                  double lam_s, double rho, const double* cvec, const double* w,
                                  double* p, double* wy, int k, const double* wwpart, int nww,
-                                 double* pppart, const PcgDev* st, int mode, hipStream_t stream,
+                                 double* pppart, PcgDev* st, int mode, hipStream_t stream,
                                  PcgDev* host_slot = nullptr, int seq = 0, bool pre = false,
-                                 const double* gpre = nullptr);
+                                 const double* gpre = nullptr, const FusedDot* dot = nullptr,
+                                 const double* rrpart = nullptr, double tol_rel = 0.0,
+                                 double tol_abs = 0.0);
 // large d: g_i = s_i c_i (c summed from its slices) and sum_i s_i c_i^2 into
 // gout[0, r) and gout[1024], once per iteration, for launch_precond_update
 nys_status launch_c_reduce(const double* cvec, int64_t d, int r, const double* lam, double lam_s,

@@ -7,6 +7,7 @@
 // barrier.  Kernels of an iteration return at once when PcgDev::done is set,
 // so the host can enqueue several iterations between convergence checks.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -93,16 +94,60 @@ __device__ __forceinline__ double slice_sum(const double* __restrict__ c, int ns
   return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
 }
 
+// sum over quads of lanes, every lane of the quad gets it
+__device__ __forceinline__ double quad_sum(double v) {
+  v += dpp_move<0xb1>(v);   // quad_perm [1, 0, 3, 2]
+  v += dpp_move<0x4e>(v);   // quad_perm [2, 3, 0, 1]
+  return v;
+}
+
+// The stopping test on ||w||^2 (mode 0: after iteration k; mode 1: before the
+// first, with the threshold from ||rhs||^2); lead, one thread of the grid,
+// records the outcome.  True: the iteration ends here.
+__device__ __forceinline__ bool pcg_stops(int mode, int k, double ww, double rr, double tol_rel,
+                                          double tol_abs, PcgDev* __restrict__ st, bool lead) {
+  double thr2;
+  bool zero_rhs = false;
+  if (mode == 1) {
+    thr2 = fmax(tol_abs * tol_abs, tol_rel * tol_rel * rr);
+    zero_rhs = (rr == 0.0);
+    if (lead) {
+      st->rr = rr;
+      st->thr2 = thr2;
+    }
+  } else {
+    thr2 = st->thr2;
+  }
+  const bool bad = !(ww == ww) || (ww > 1.7e308);
+  if (lead) st->ww = ww;
+  if (!(zero_rhs || bad || ww <= thr2)) return false;
+  if (lead) {
+    if (bad) st->flags |= kFlagNonfinite;
+    if (zero_rhs) st->flags |= kFlagZeroRhs;
+    st->iters = (mode == 1) ? 0 : k + 1;
+    st->done = 1;
+  }
+  return true;
+}
+
 // 256 threads: RJ lanes x (256 / RJ) slices of the workgroup partials, each
 // lane summing VW adjacent columns; the slices are combined in a fixed order
 // through LDS.
-template <int RJ, int VW>
+// UT other than void (op 0 and 1): the workgroup also leaves its columns'
+// share of c = U^T w in cpart[blockIdx.x * ldc + i] (i < ldc, ldc = r rounded
+// up to even), which k_precond_update adds in workgroup order after testing
+// ||w||^2.  That takes the launch of k_precond_dot out of the iteration, whose
+// kernels are a launch's latency long (5 us each at 2000 columns); the entries
+// of U are loaded with the first loads, four lanes to a row of 16 columns.
+template <int RJ, int VW, typename UT>
 __global__ __launch_bounds__(256) void k_reduce_update(
     int op, const double* __restrict__ ypart, int G, int ldy, const double* __restrict__ qpart,
     int64_t d, double rho_eff, const double* __restrict__ p, double* __restrict__ x,
     double* __restrict__ w, const double* __restrict__ rhs, double* __restrict__ wy, int k,
     const double* __restrict__ pppart, int npp, double* __restrict__ wwpart,
-    double* __restrict__ rrpart, PcgDev* __restrict__ st, int Gq, int pre) {
+    double* __restrict__ rrpart, PcgDev* __restrict__ st, int Gq, int pre,
+    const UT* __restrict__ U, int r, double* __restrict__ cpart, int ldc) {
+  constexpr bool DOT = !std::is_void_v<UT>;
   constexpr int S = 256 / RJ;
   constexpr int CW = RJ * VW;   // columns per workgroup
   __shared__ double part[S][CW];
@@ -119,6 +164,25 @@ __global__ __launch_bounds__(256) void k_reduce_update(
   pre_load(qpart, (op == 0 && !pre) ? Gq : 0, qv);
   pre_load(pppart, (op == 0 && !pre) ? npp : 0, pv4);
   const double wyk = (op == 0) ? wy[k & (kWyRing - 1)] : 0.0;
+  // rows ui, ui + 64 of U at this thread's columns uq + 4 t; an index past the
+  // end reads the last row or column, dropped later (w is 0 there)
+  constexpr int UN = DOT ? CW / 4 : 1;
+  const int ui = tid >> 2, uq = tid & 3;
+  [[maybe_unused]] double u0[2][UN];
+  auto u_load = [&](int i, double (&u)[UN]) {
+    if constexpr (DOT) {
+      const int ic = i < r ? i : r - 1;
+#pragma unroll
+      for (int t = 0; t < UN; ++t) {
+        const int64_t c = (int64_t)blockIdx.x * CW + uq + 4 * t;
+        u[t] = (double)U[(int64_t)ic * d + (c < d ? c : d - 1)];
+      }
+    }
+  };
+  if (DOT && r > 0) {
+    u_load(ui, u0[0]);
+    u_load(ui + 64, u0[1]);
+  }
   if (op == 0 && st->done) return;
   double pj = 0.0, xj = 0.0, wj = 0.0, rj = 0.0;
   if (own) {
@@ -214,6 +278,7 @@ __global__ __launch_bounds__(256) void k_reduce_update(
 
   const int64_t j = jf;
   double ww = 0.0, rr = 0.0;
+  [[maybe_unused]] double wnew = 0.0;
   if (own) {
     double sum = 0.0;
 #pragma unroll
@@ -222,11 +287,11 @@ __global__ __launch_bounds__(256) void k_reduce_update(
     if (op == 0) {
       x[j] = xj + alpha * pj;
       const double wn = wj - alpha * v;
-      w[j] = wn;
+      w[j] = wnew = wn;
       ww = wn * wn;
     } else if (op == 1 || op == 2) {
       const double wn = rj - v;
-      w[j] = wn;
+      w[j] = wnew = wn;
       ww = wn * wn;
       rr = rj * rj;
       if (op == 2 && x != nullptr) x[j] = v;   // keep H_rho x for the next solve's w0
@@ -237,6 +302,29 @@ __global__ __launch_bounds__(256) void k_reduce_update(
     }
   }
   if (op >= 3) return;
+  if constexpr (DOT) {
+    __shared__ double wl[CW];
+    if (tid < CW) wl[tid] = own ? wnew : 0.0;
+    __syncthreads();
+    double wq[UN];
+#pragma unroll
+    for (int t = 0; t < UN; ++t) wq[t] = wl[uq + 4 * t];
+    double* co = cpart + (int64_t)blockIdx.x * ldc;
+    for (int i = ui, n = 0; i < ldc; i += 64, ++n) {
+      double u[UN];
+      if (n < 2) {
+#pragma unroll
+        for (int t = 0; t < UN; ++t) u[t] = n == 0 ? u0[0][t] : u0[1][t];
+      } else {
+        u_load(i, u);
+      }
+      double c = 0.0;
+#pragma unroll
+      for (int t = 0; t < UN; ++t) c = fma(u[t], wq[t], c);
+      c = quad_sum(c);
+      if (uq == 0) co[i] = i < r ? c : 0.0;
+    }
+  }
   __syncthreads();
   ww = block_sum_value(ww, sh4);
   __syncthreads();
@@ -305,32 +393,14 @@ __global__ __launch_bounds__(256) void k_precond_dot(
   }
   if (mode == 0 || mode == 1) {
     const double ww = (pre && mode == 0) ? st->wwn : pre_sum(wwpart, nww, wv, sh4);
-    double thr2;
-    bool zero_rhs = false;
+    double rr = 0.0;
     if (mode == 1) {
       __syncthreads();
-      const double rr = pre_sum(rrpart, nww, rv, sh4);
-      thr2 = fmax(tol_abs * tol_abs, tol_rel * tol_rel * rr);
-      zero_rhs = (rr == 0.0);
-      if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
-        st->rr = rr;
-        st->thr2 = thr2;
-      }
-    } else {
-      thr2 = st->thr2;
+      rr = pre_sum(rrpart, nww, rv, sh4);
     }
-    const bool bad = !(ww == ww) || (ww > 1.7e308);
-    const bool lead = blockIdx.x == 0 && blockIdx.y == 0 && tid == 0;
-    if (lead) st->ww = ww;
-    if (zero_rhs || bad || ww <= thr2) {
-      if (lead) {
-        if (bad) st->flags |= kFlagNonfinite;
-        if (zero_rhs) st->flags |= kFlagZeroRhs;
-        st->iters = (mode == 1) ? 0 : k + 1;
-        st->done = 1;
-      }
+    if (pcg_stops(mode, k, ww, rr, tol_rel, tol_abs, st,
+                  blockIdx.x == 0 && blockIdx.y == 0 && tid == 0))
       return;
-    }
   } else if (mode == 3) {
     const double ww = pre_sum(wwpart, nww, wv, sh4);
     if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) st->true_rr = ww;
@@ -344,13 +414,16 @@ __global__ __launch_bounds__(256) void k_precond_dot(
 // mode 0: p = y + beta p (beta = (w^T y)/wy[k]), wy[k+1] = w^T y
 // mode 1: p = y, wy[0] = w^T y
 // mode 2: p (output) = y, standalone apply
-template <typename UT, int NU, int VJ>
+// FUSED (modes 0 and 1, after the reduction that leaves U^T w): c comes as nsl
+// workgroup partials of ldc entries, and ||w||^2 is tested here.
+template <typename UT, int NU, int VJ, bool FUSED>
 __global__ __launch_bounds__(256) void k_precond_update(
     const UT* __restrict__ U, int64_t d, int r, const double* __restrict__ lam, double lam_s,
     double rho, const double* __restrict__ cvec, const double* __restrict__ w,
     double* __restrict__ p, double* __restrict__ wy, int k, const double* __restrict__ wwpart,
-    int nww, double* __restrict__ pppart, const PcgDev* __restrict__ st, int mode,
-    PcgDev* __restrict__ host_slot, int seq, int nsl, int pre, const double* __restrict__ gpre) {
+    int nww, double* __restrict__ pppart, PcgDev* __restrict__ st, int mode,
+    PcgDev* __restrict__ host_slot, int seq, int nsl, int pre, const double* __restrict__ gpre,
+    int ldc, const double* __restrict__ rrpart, double tol_rel, double tol_abs) {
   // host_slot (pinned host memory, may be NULL): receives the state at the end
   // of the iteration, read by the host once the kernel has completed.
   // gpre (may be NULL): g and sum s c^2 already reduced by k_c_reduce
@@ -373,7 +446,16 @@ __global__ __launch_bounds__(256) void k_precond_update(
     if (mode == 0) pold = p[j];
   }
   const double wyk = (mode == 0) ? wy[k & (kWyRing - 1)] : 0.0;
-  if (mode != 2 && st->done) {
+  [[maybe_unused]] double rv[4];
+  if constexpr (FUSED) {
+    // the lead thread of this very launch may set done: one reading for the
+    // whole workgroup
+    __shared__ int done;
+    pre_load(rrpart, mode == 1 ? nww : 0, rv);
+    if (tid == 0) done = st->done;
+    __syncthreads();
+    if (done) return;
+  } else if (mode != 2 && st->done) {
     if (host_slot != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {
       PcgDev h = *st;
       h.k = seq;              // sequence number the host waits for
@@ -394,7 +476,44 @@ __global__ __launch_bounds__(256) void k_precond_update(
     }
   }
   double sc = 0.0;
-  if (gpre != nullptr) {
+  if constexpr (FUSED) {
+    // pairs of entries of c, the partials dealt to 256 / (ldc / 2) groups of
+    // threads, sixteen 16-byte loads of a thread in flight (an index past nsl
+    // reads the last partial and adds nothing); the groups in a fixed order
+    __shared__ double2 cp[256];
+    const int np = ldc >> 1, ng = np > 0 ? 256 / np : 1;
+    const int pi = np > 0 ? tid % np : 0, gi = np > 0 ? tid / np : ng;
+    double2 a = make_double2(0.0, 0.0);
+    if (gi < ng) {
+      for (int s0 = gi; s0 < nsl; s0 += 16 * ng) {
+        double2 v[16];
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+          const int sl2 = s0 + t * ng;
+          v[t] = *reinterpret_cast<const double2*>(
+              cvec + (int64_t)(sl2 < nsl ? sl2 : nsl - 1) * ldc + 2 * pi);
+        }
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+          const bool in = s0 + t * ng < nsl;
+          a.x += in ? v[t].x : 0.0;
+          a.y += in ? v[t].y : 0.0;
+        }
+      }
+    }
+    cp[tid] = a;
+    __syncthreads();
+    for (int i = tid; i < r; i += 256) {
+      double ci = 0.0;
+      for (int h = 0; h < ng; ++h) {
+        const double2 v = cp[h * np + (i >> 1)];
+        ci += (i & 1) ? v.y : v.x;
+      }
+      const double s = (lam_s + rho) / (lam[i] + rho) - 1.0;
+      g[i] = s * ci;
+      sc += s * ci * ci;
+    }
+  } else if (gpre != nullptr) {
     for (int i = tid; i < r; i += 256) g[i] = gpre[i];
   } else {
     for (int i = tid; i < r; i += 256) {
@@ -407,6 +526,14 @@ __global__ __launch_bounds__(256) void k_precond_update(
   double wy_new = 0.0;
   if (mode != 2) {
     const double ww = (pre && mode == 0) ? st->wwn : pre_sum(wwpart, nww, wv, sh4);
+    if constexpr (FUSED) {
+      double rr = 0.0;
+      if (mode == 1) {
+        __syncthreads();
+        rr = pre_sum(rrpart, nww, rv, sh4);
+      }
+      if (pcg_stops(mode, k, ww, rr, tol_rel, tol_abs, st, blockIdx.x == 0 && tid == 0)) return;
+    }
     __syncthreads();
     wy_new = ww + (gpre != nullptr ? gpre[1024] : block_sum_value(sc, sh4));
   } else {
@@ -676,24 +803,38 @@ nys_status launch_reduce_update(int op, const double* ypart, int G, int ldy, con
                                 int64_t d, double rho_eff, const double* p, double* x, double* w,
                                 const double* rhs, double* wy, int k, const double* pppart,
                                 int npp, double* wwpart, double* rrpart, PcgDev* st,
-                                hipStream_t stream, int Gq, bool pre, int rj) {
+                                hipStream_t stream, int Gq, bool pre, int rj, const FusedDot* dot) {
   if (rj == 0) rj = red_block(G);
   // the wide form reads column pairs: rows of even length, 16-byte aligned
   const bool wide = (ldy % 2 == 0) && (reinterpret_cast<uintptr_t>(ypart) % 16 == 0);
-  if (rj == 256)
-    hipLaunchKernelGGL((k_reduce_update<256, 1>), dim3(nblk(d, 256)), dim3(256), 0, stream, op,
-                       ypart, G, ldy, qpart, d, rho_eff, p, x, w, rhs, wy, k, pppart, npp, wwpart,
-                       rrpart, st, Gq < 0 ? G : Gq, pre ? 1 : 0);
-  else if (rj == kRedBlock && wide)
-    hipLaunchKernelGGL((k_reduce_update<kRedBlock / 2, 2>), dim3(nblk(d, kRedBlock)), dim3(256),
-                       0, stream, op, ypart, G, ldy, qpart, d, rho_eff, p, x, w, rhs, wy, k,
-                       pppart, npp, wwpart, rrpart, st, Gq < 0 ? G : Gq, pre ? 1 : 0);
-  else if (rj == kRedBlock)
-    hipLaunchKernelGGL((k_reduce_update<kRedBlock, 1>), dim3(nblk(d, kRedBlock)), dim3(256), 0,
-                       stream, op, ypart, G, ldy, qpart, d, rho_eff, p, x, w, rhs, wy, k, pppart,
-                       npp, wwpart, rrpart, st, Gq < 0 ? G : Gq, pre ? 1 : 0);
-  else
+  auto go = [&](auto kern, int cw, const auto* U) {
+    hipLaunchKernelGGL(kern, dim3(nblk(d, cw)), dim3(256), 0, stream, op, ypart, G, ldy, qpart, d,
+                       rho_eff, p, x, w, rhs, wy, k, pppart, npp, wwpart, rrpart, st,
+                       Gq < 0 ? G : Gq, pre ? 1 : 0, U, dot ? dot->r : 0,
+                       dot ? dot->cpart : nullptr, dot ? dot->ldc : 0);
+  };
+  const void* none = nullptr;
+  auto go_dot = [&](const auto* U) {
+    using T = std::remove_const_t<std::remove_pointer_t<decltype(U)>>;
+    if (rj == kRedBlock) go(k_reduce_update<kRedBlock / 2, 2, T>, kRedBlock, U);
+    else go(k_reduce_update<kRedBlockWide / 2, 2, T>, kRedBlockWide, U);
+  };
+  if (dot != nullptr) {
+    if ((rj != kRedBlock && rj != kRedBlockWide) || !wide || (op != 0 && op != 1))
+      return NYS_ERR_INVALID;
+    if (dot->u32) go_dot(static_cast<const float*>(dot->U));
+    else go_dot(static_cast<const double*>(dot->U));
+  } else if (rj == 256) {
+    go(k_reduce_update<256, 1, void>, 256, none);
+  } else if (rj == kRedBlock && wide) {
+    go(k_reduce_update<kRedBlock / 2, 2, void>, kRedBlock, none);
+  } else if (rj == kRedBlockWide && wide) {
+    go(k_reduce_update<kRedBlockWide / 2, 2, void>, kRedBlockWide, none);
+  } else if (rj == kRedBlock) {
+    go(k_reduce_update<kRedBlock, 1, void>, kRedBlock, none);
+  } else {
     return NYS_ERR_INVALID;
+  }
   return hipGetLastError() == hipSuccess ? NYS_OK : NYS_ERR_HIP;
 }
 
@@ -741,12 +882,16 @@ nys_status launch_c_reduce(const double* cvec, int64_t d, int r, const double* l
 nys_status launch_precond_update(const void* U, bool u32, int64_t d, int r, const double* lam,
                                  double lam_s, double rho, const double* cvec, const double* w,
                                  double* p, double* wy, int k, const double* wwpart, int nww,
-                                 double* pppart, const PcgDev* st, int mode, hipStream_t stream,
-                                 PcgDev* host_slot, int seq, bool pre, const double* gpre) {
+                                 double* pppart, PcgDev* st, int mode, hipStream_t stream,
+                                 PcgDev* host_slot, int seq, bool pre, const double* gpre,
+                                 const FusedDot* dot, const double* rrpart, double tol_rel,
+                                 double tol_abs) {
   if (r > 1024) return NYS_ERR_INVALID;
+  if (dot != nullptr && (pre || mode == 2 || dot->ldc > 512 || dot->parts < 1))
+    return NYS_ERR_INVALID;
   const int vj = vec_block(d);
   const int grid = nblk(d, vj);
-  const int nsl = dot_slices(d);
+  const int nsl = dot != nullptr ? dot->parts : dot_slices(d);
   // eight rank terms per lane in flight up to rank 64 (every term in one
   // group); sixteen up to rank 256, where the pass is latency bound and the
   // lane's terms fit two groups; eight above, where U streams from HBM and
@@ -756,27 +901,23 @@ nys_status launch_precond_update(const void* U, bool u32, int64_t d, int r, cons
   auto go = [&](auto kern, const auto* u) {
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, stream, u, d, r, lam, lam_s, rho, cvec, w,
                        p, wy, k, wwpart, nww, pppart, st, mode, host_slot, seq, nsl, pre ? 1 : 0,
-                       gpre);
+                       gpre, dot ? dot->ldc : 0, rrpart, tol_rel, tol_abs);
   };
-  if (u32) {
-    const float* u = static_cast<const float*>(U);
-    if (vj == kVecBlock) {
-      if (wide) go(k_precond_update<float, 16, kVecBlock>, u);
-      else go(k_precond_update<float, 8, kVecBlock>, u);
+  auto pick = [&](const auto* u) {
+    using T = std::remove_const_t<std::remove_pointer_t<decltype(u)>>;
+    if (dot != nullptr) {
+      if (wide) go(k_precond_update<T, 16, kVecBlock, true>, u);
+      else go(k_precond_update<T, 8, kVecBlock, true>, u);
+    } else if (vj == kVecBlock) {
+      if (wide) go(k_precond_update<T, 16, kVecBlock, false>, u);
+      else go(k_precond_update<T, 8, kVecBlock, false>, u);
     } else {
-      if (wide) go(k_precond_update<float, 16, kVecBlockWide>, u);
-      else go(k_precond_update<float, 8, kVecBlockWide>, u);
+      if (wide) go(k_precond_update<T, 16, kVecBlockWide, false>, u);
+      else go(k_precond_update<T, 8, kVecBlockWide, false>, u);
     }
-  } else {
-    const double* u = static_cast<const double*>(U);
-    if (vj == kVecBlock) {
-      if (wide) go(k_precond_update<double, 16, kVecBlock>, u);
-      else go(k_precond_update<double, 8, kVecBlock>, u);
-    } else {
-      if (wide) go(k_precond_update<double, 16, kVecBlockWide>, u);
-      else go(k_precond_update<double, 8, kVecBlockWide>, u);
-    }
-  }
+  };
+  if (u32) pick(static_cast<const float*>(U));
+  else pick(static_cast<const double*>(U));
   return hipGetLastError() == hipSuccess ? NYS_OK : NYS_ERR_HIP;
 }
 

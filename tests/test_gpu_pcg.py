@@ -251,6 +251,40 @@ def test_pcg_edge_cases(N, ctx):
     assert e.value.status == N.NYS_ERR_INVALID
 
 
+@pytest.mark.parametrize("d,r", [(2, 1), (15, 0), (17, 2), (513, 495), (1000, 65), (1024, 256),
+                                 (1024, 257), (1025, 1), (2000, 129), (2016, 260)])
+def test_pcg_iterates_over_ranks_and_columns(N, ctx, d, r):
+    """Five iterations against the oracle's at the edges of the partial
+    reduction that forms U^T w: 16 and 32 columns per workgroup, odd ranks,
+    ranks of several passes, the largest number of partials and one rank more,
+    rank 0.  A^T A / n + I and the preconditioner have condition numbers below
+    10 each, so an iterate's rounding error stays below 5 d eps 100 = 1e-10
+    relative for the widest."""
+    n = 4000
+    rng = np.random.default_rng(1000 * d + r)
+    A = rng.standard_normal((n, d)) / np.sqrt(n)
+    rhs = rng.standard_normal(d)
+    rho = 1.0
+    F, precond = None, None
+    if r > 0:
+        U, _ = np.linalg.qr(rng.standard_normal((d, r)))
+        lam = np.sort(rng.uniform(0.0, 9.0, r))[::-1].copy()
+        F = N.nys_factor_import(ctx, torch.from_numpy(U.T.copy()).to(DEV), lam, 1e-12)
+        precond = lambda w: ny.precond_inverse_apply(U, lam, rho, w)
+    m = min(5, d)
+    ora = pc.nys_pcg(pc.subproblem_matvec(A, None, 0.0, rho), rhs, np.zeros(d), precond, 1e-14,
+                     max_iter=m)
+    x = torch.zeros(d, dtype=torch.float64, device=DEV)
+    info = N.pcg_solve(ctx, torch.from_numpy(A).to(DEV), torch.from_numpy(rhs).to(DEV), x, rho, F,
+                       opts=N.pcg_opts(tol=1e-14, max_iter=m, true_residual=False),
+                       allow=(N.NYS_OK, N.NYS_ERR_MAXITER))
+    err = np.linalg.norm(x.cpu().numpy() - ora.x) / np.linalg.norm(ora.x)
+    print(f"[pcg iterates] d={d} r={r} iters {info.iters} / {ora.iters} err {err:.1e}", flush=True)
+    assert abs(info.iters - ora.iters) <= 1 and err <= 1e-10
+    if F is not None:
+        F.close()
+
+
 def test_pcg_deterministic(N, ctx):
     A64 = synth.decay_matrix(5000, 700, 0.8, seed=12)
     A = A64.to(torch.float32).to(DEV)
