@@ -888,43 +888,50 @@ __device__ __forceinline__ double2 jac_rotation(double apq, double app, double a
   return make_double2(c, theta < 0.0 ? -s : s);
 }
 
-// (x00 x01; x10 x11) <- J_a^T X J_b for the rotations ra (rows) and rb (columns)
+// (x00 x01; x10 x11) <- J_a^T X J_b for the rotations ra (rows) and rb
+// (columns), with no test: a rotation (1, 0) leaves finite entries as they are
+// (c x - s y = x and s x + c y = y with c = 1, s = 0), so every rotation of a
+// step is applied without diverging on which ones are idle.  The order of the
+// roundings is written out: results do not depend on where this is inlined.
 __device__ __forceinline__ void blk_rotate(double2 ra, double2 rb, double& x00, double& x01,
                                            double& x10, double& x11) {
-  if (ra.y != 0.0) {
-    const double c = ra.x, s = ra.y;
-    const double y00 = c * x00 - s * x10, y01 = c * x01 - s * x11;
-    const double y10 = s * x00 + c * x10, y11 = s * x01 + c * x11;
-    x00 = y00; x01 = y01; x10 = y10; x11 = y11;
-  }
-  if (rb.y != 0.0) {
-    const double c = rb.x, s = rb.y;
-    const double y00 = c * x00 - s * x01, y01 = s * x00 + c * x01;
-    const double y10 = c * x10 - s * x11, y11 = s * x10 + c * x11;
-    x00 = y00; x01 = y01; x10 = y10; x11 = y11;
-  }
+  const double y00 = fma(ra.x, x00, -(ra.y * x10)), y01 = fma(ra.x, x01, -(ra.y * x11));
+  const double y10 = fma(ra.y, x00, ra.x * x10), y11 = fma(ra.y, x01, ra.x * x11);
+  x00 = fma(rb.x, y00, -(rb.y * y01));
+  x01 = fma(rb.y, y00, rb.x * y01);
+  x10 = fma(rb.x, y10, -(rb.y * y11));
+  x11 = fma(rb.y, y10, rb.x * y11);
 }
 
-// The same with no test: a rotation (1, 0) leaves finite entries unchanged
-// bit for bit (c x - s y = x and s x + c y = y with c = 1, s = 0), so the
-// cross steps apply every rotation without diverging on which ones are idle.
-__device__ __forceinline__ void blk_rotate_all(double2 ra, double2 rb, double& x00, double& x01,
-                                               double& x10, double& x11) {
-  {
-    const double c = ra.x, s = ra.y;
-    const double y00 = c * x00 - s * x10, y01 = c * x01 - s * x11;
-    const double y10 = s * x00 + c * x10, y11 = s * x01 + c * x11;
-    x00 = y00; x01 = y01; x10 = y10; x11 = y11;
-  }
-  {
-    const double c = rb.x, s = rb.y;
-    const double y00 = c * x00 - s * x01, y01 = s * x00 + c * x01;
-    const double y10 = c * x10 - s * x11, y11 = s * x10 + c * x11;
-    x00 = y00; x01 = y01; x10 = y10; x11 = y11;
-  }
+// The same for the rotation lanes of the cross steps: a diagonal block (diag,
+// x01 = x10 on entry, x01 and x10 not used afterwards) or the block next to it.
+__device__ __forceinline__ void blk_rotate_lane(bool diag, double2 ra, double2 rb, double& x00,
+                                                double& x01, double& x10, double& x11) {
+  const double cx = ra.x * x01, sx = ra.y * x00;
+  const double y00 = fma(ra.x, x00, -(ra.y * x10));
+  const double y01n = fma(ra.x, x01, -(ra.y * x11)), y01d = fma(-ra.y, x11, cx);
+  const double y10n = fma(ra.x, x10, sx), y10d = fma(ra.y, x00, cx);
+  const double y01 = diag ? y01d : y01n, y10 = diag ? y10d : y10n;
+  const double y11 = fma(ra.x, x11, ra.y * x01);
+  x00 = fma(rb.x, y00, -(rb.y * y01));
+  x01 = fma(rb.y, y00, rb.x * y01);
+  x10 = fma(rb.x, y10, -(rb.y * y11));
+  x11 = fma(rb.x, y11, rb.y * y10);
 }
 
-__device__ __forceinline__ int rr16(int x, int st) { return x == 0 ? 0 : ((x - 1 + st) % 15) + 1; }
+// v of the first (H = 0) or second row of 16 lanes of a pair of rows, in both
+template <int H>
+__device__ __forceinline__ double row_swap(double v) {
+  const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return dpp_join((int)l[H], (int)h[H]);
+}
+
+// st < 15
+__device__ __forceinline__ int rr16(int x, int st) {
+  const int v = x + st;
+  return x == 0 ? 0 : (v > 15 ? v - 15 : v);
+}
 
 // Positions p < q of rotation k (0..15) at step st of a visit.  INTRA steps:
 // rotations 0..7 pair positions of the first block (round-robin over its 16
@@ -949,94 +956,48 @@ __device__ __forceinline__ void step_pair(int k, int st, int* p, int* q) {
 
 // The 2x2 block of rotations (ka, kb), ka <= kb, of the step, and its mirror.
 // S stays exactly symmetric: the block and its transpose get the same values,
-// and the rotated pair's off-diagonal entry is set to zero.
+// and a rotated pair's off-diagonal entry is set to zero.
 template <bool INTRA>
 __device__ __forceinline__ void upd_block(double (&S)[kJP][kJP + 1], const double2* C, int st,
                                           int ka, int kb) {
   const double2 ra = C[ka], rb = C[kb];
-  if (ra.y == 0.0 && rb.y == 0.0) return;
   int p, q, p2, q2;
   step_pair<INTRA>(ka, st, &p, &q);
   step_pair<INTRA>(kb, st, &p2, &q2);
   double x00 = S[p][p2], x01 = S[p][q2], x10 = S[q][p2], x11 = S[q][q2];
+  const double off = x01;
   blk_rotate(ra, rb, x00, x01, x10, x11);
-  if (ka == kb) {
-    S[p][p] = x00;
-    S[q][q] = x11;
-    S[p][q] = 0.0;
-    S[q][p] = 0.0;
-  } else {
-    S[p][p2] = x00; S[p][q2] = x01; S[q][p2] = x10; S[q][q2] = x11;
-    S[p2][p] = x00; S[q2][p] = x01; S[p2][q] = x10; S[q2][q] = x11;
-  }
-}
-
-// upd_block for a cross step's off-diagonal block (ka < kb), every rotation
-// applied (see blk_rotate_all)
-__device__ __forceinline__ void upd_block_cross(double (&S)[kJP][kJP + 1], const double2* C,
-                                                int st, int ka, int kb) {
-  const double2 ra = C[ka], rb = C[kb];
-  int p, q, p2, q2;
-  step_pair<false>(ka, st, &p, &q);
-  step_pair<false>(kb, st, &p2, &q2);
-  double x00 = S[p][p2], x01 = S[p][q2], x10 = S[q][p2], x11 = S[q][q2];
-  blk_rotate_all(ra, rb, x00, x01, x10, x11);
+  if (INTRA && ka == kb) x01 = x10 = (ra.y != 0.0) ? 0.0 : off;
   S[p][p2] = x00; S[p][q2] = x01; S[q][p2] = x10; S[q][q2] = x11;
   S[p2][p] = x00; S[q2][p] = x01; S[p2][q] = x10; S[q2][q] = x11;
 }
 
-// Q <- Q J over the 16 rotations of the step: two (row, rotation) pairs per thread
-template <bool INTRA>
-__device__ __forceinline__ void upd_q(double (&Q)[kJP][kJP + 1], const double2* C, int st,
-                                      int tid) {
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int e = tid + kJT * h;
-    const int i = e >> 4, k = e & (kJB - 1);
-    const double2 r = C[k];
-    if (r.y != 0.0) {
-      int p, q;
-      step_pair<INTRA>(k, st, &p, &q);
-      const double qp = Q[i][p], qv = Q[i][q];
-      Q[i][p] = r.x * qp - r.y * qv;
-      Q[i][q] = r.y * qp + r.x * qv;
-    }
-  }
-}
-static_assert(kJP * kJB == 2 * kJT, "two (row, rotation) pairs per thread");
-
-// The same over the threads t = 0 .. 191 of wavefronts 1-3 (pairs t, t + 192,
-// t + 384): every load of the step is issued before the first store (the
-// pairs touch disjoint entries of Q).
+// Q <- Q J over the 16 intra rotations of the step, by the threads t of
+// wavefronts 1-3: (row, rotation) pairs t, t + 192, t + 384, which touch
+// disjoint entries
 constexpr int kJQT = kJT - 64;
-constexpr int kJQN = (kJP * kJB + kJQT - 1) / kJQT;
-__device__ __forceinline__ void upd_q_cross(double (&Q)[kJP][kJP + 1], const double2* C, int st,
+__device__ __forceinline__ void upd_q_intra(double (&Q)[kJP][kJP + 1], const double2* C, int st,
                                             int t) {
-  double2 r[kJQN];
-  double qp[kJQN], qv[kJQN];
-  int row[kJQN], pp[kJQN], qq[kJQN];
+  constexpr int N = (kJP * kJB + kJQT - 1) / kJQT;
+  static_assert(kJQT % kJB == 0, "a thread's pairs have one rotation");
+  int p, q;
+  step_pair<true>(t & (kJB - 1), st, &p, &q);
+  const double2 r = C[t & (kJB - 1)];
+  double qp[N], qv[N];
 #pragma unroll
-  for (int h = 0; h < kJQN; ++h) {
-    const int e = t + kJQT * h;
-    const int k = e & (kJB - 1);
-    row[h] = e >> 4;
-    step_pair<false>(k, st, &pp[h], &qq[h]);
-    r[h] = (e < kJP * kJB) ? C[k] : make_double2(1.0, 0.0);
-  }
-  // every rotation applied (see blk_rotate_all); only the pairs past the 512
-  // of the step are left out
-#pragma unroll
-  for (int h = 0; h < kJQN; ++h) {
-    if (t + kJQT * h < kJP * kJB) {
-      qp[h] = Q[row[h]][pp[h]];
-      qv[h] = Q[row[h]][qq[h]];
+  for (int h = 0; h < N; ++h) {
+    const int i = (t + kJQT * h) >> 4;
+    if (i < kJP) {
+      qp[h] = Q[i][p];
+      qv[h] = Q[i][q];
     }
   }
 #pragma unroll
-  for (int h = 0; h < kJQN; ++h) {
-    if (t + kJQT * h < kJP * kJB) {
-      Q[row[h]][pp[h]] = r[h].x * qp[h] - r[h].y * qv[h];
-      Q[row[h]][qq[h]] = r[h].y * qp[h] + r[h].x * qv[h];
+  for (int h = 0; h < N; ++h) {
+    const int i = (t + kJQT * h) >> 4;
+    if (i < kJP) {
+      Q[i][p] = fma(r.x, qp[h], -(r.y * qv[h]));
+      Q[i][q] = fma(r.y, qp[h], r.x * qv[h]);
     }
   }
 }
@@ -1232,19 +1193,129 @@ __device__ __forceinline__ void form_pair(const double* __restrict__ Hin,
   }
 }
 
+// The rotations of one visit: S (formed, all threads past a barrier) is
+// rotated in place and Q, the identity on entry, takes their product.  FIRST:
+// the intra-block pairs first.  kJT threads, tid their index; every thread of
+// the workgroup calls it (several groups of kJT may, each with its own S, Q
+// and cs).
+//
+// A step's length is a chain of latencies: LDS reads, the rotation (two
+// reciprocal square roots), LDS writes, a barrier.  In the cross steps it is
+// that of wavefront 0: lanes 0..15 rotate the diagonal block of their rotation
+// k and lanes 16..31 the block (k, k + 1) (k = 15: (0, 15)) with the same
+// instructions, two moves between lanes bring the next step's a_kq and a_qq
+// together, and the next rotation is formed before the step's one barrier.
+// Wavefronts 1 and 2 update the other 104 blocks, 1-3 the columns of Q, which
+// stay in registers for the visit.
+// Sketches with and before this form: 20000 x 2000 rank 100 2046 / 2208 us,
+// 100000 x 4000 rank 200 6361 / 6679 us.
+__device__ __forceinline__ void jacobi_visit(bool FIRST, double (&S)[kJP][kJP + 1],
+                                             double (&Q)[kJP][kJP + 1], double2 (&cs)[2][kJB],
+                                             int tid, double tol, double floor_abs,
+                                             bool& rotated) {
+  const int lane = tid & 63, wv = tid >> 6, k = tid & (kJB - 1);
+  if (FIRST) {
+    int gka = 0, gkb = 0;
+    const bool gblk = wv > 0 && tid - 64 < kJU;
+    if (gblk) upper_block(tid - 64, &gka, &gkb);
+    for (int st = 0; st < kJB; ++st) {
+      // the rotations of step st next to Q's update of step st - 1
+      if (wv == 0) {
+        if (tid < kJB && st < kJB - 1) {
+          int p, q;
+          step_pair<true>(tid, st, &p, &q);
+          cs[st & 1][tid] = jac_rotation(S[p][q], S[p][p], S[q][q], tol, floor_abs, &rotated);
+        }
+      } else if (st > 0) {
+        upd_q_intra(Q, cs[(st - 1) & 1], st - 1, tid - 64);
+      }
+      __syncthreads();
+      if (st < kJB - 1) {
+        if (gblk) upd_block<true>(S, cs[st & 1], st, gka, gkb);
+        __syncthreads();
+      }
+    }
+  }
+  // cross steps
+  const bool diag = tid < kJB, lanes = tid < 2 * kJB, last = k == kJB - 1;
+  int ka = k, kb = k;
+  const bool blk = wv > 0 && tid < 64 + kJOther;
+  if (blk) other_block(tid - 64, &ka, &kb);
+  if (lanes && !diag) {
+    ka = last ? 0 : k;
+    kb = last ? k : k + 1;
+  }
+  // rows 4 (qg + u) + lane / 16 of Q: column k, and column 16 + (k + st) mod 16,
+  // which moves one lane down the row of lanes from step to step
+  const int qg = wv == 3 ? 4 : 2 * (wv - 1);
+  double qa[4], qb[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    qa[u] = qb[u] = 0.0;
+    if (wv == 3 || (wv > 0 && u < 2)) {
+      const int i = 4 * (qg + u) + (lane >> 4);
+      qa[u] = Q[i][k];
+      qb[u] = Q[i][kJB + k];
+    }
+  }
+  auto q_turn = [&](const double2* C) __attribute__((always_inline)) {
+    const double2 r = C[k];
+    auto turn = [&](int u) __attribute__((always_inline)) {
+      const double a = qa[u], b = qb[u];
+      qa[u] = fma(r.x, a, -(r.y * b));
+      qb[u] = dpp_move<0x12f>(fma(r.x, b, r.y * a));   // row_ror:15
+    };
+    turn(0);
+    turn(1);
+    if (wv == 3) {
+      turn(2);
+      turn(3);
+    }
+  };
+  if (diag)
+    cs[0][k] = jac_rotation(S[k][kJB + k], S[k][k], S[kJB + k][kJB + k], tol, floor_abs, &rotated);
+  __syncthreads();
+  // the last step (kJB - 1) changes Q only
+  for (int st = 0; st < kJB - 1; ++st) {
+    const double2* C = cs[st & 1];
+    if (lanes) {
+      const int p = ka, q = kJB + ((ka + st) & (kJB - 1));
+      const int p2 = kb, q2 = kJB + ((kb + st) & (kJB - 1));
+      double x00 = S[p][p2], x01 = S[p][q2], x10 = S[q][p2], x11 = S[q][q2];
+      const double2 ra = C[ka], rb = C[kb];
+      const double off = x01;
+      blk_rotate_lane(diag, ra, rb, x00, x01, x10, x11);
+      // the next step's a_kq from lane 16 + k, its a_qq from lane k + 1
+      const double akq = row_swap<1>(last ? x10 : x01);
+      const double aqq = dpp_move<0x12f>(x11);
+      if (diag) x01 = x10 = (ra.y != 0.0) ? 0.0 : off;
+      S[p][p2] = x00; S[p][q2] = x01; S[q][p2] = x10; S[q][q2] = x11;
+      S[p2][p] = x00; S[q2][p] = x01; S[p2][q] = x10; S[q2][q] = x11;
+      if (diag)
+        cs[(st + 1) & 1][k] = jac_rotation(akq, x00, aqq, tol, floor_abs, &rotated);
+    } else if (wv > 0) {
+      if (blk) upd_block<false>(S, C, st, ka, kb);
+      q_turn(C);
+    }
+    __syncthreads();
+  }
+  if (wv > 0) q_turn(cs[(kJB - 1) & 1]);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (wv == 3 || (wv > 0 && u < 2)) {
+      const int i = 4 * (qg + u) + (lane >> 4);
+      Q[i][k] = qa[u];
+      Q[i][kJB + k] = qb[u];
+    }
+  }
+  __syncthreads();
+}
+
 // One round of the sweep.  Workgroups 0 .. nb/2 - 1 solve the pair blocks of
 // round t and write Qcur; with FIRST (round 0) they take the pair block from
 // Hin directly and rotate the intra-block pairs first, otherwise they form it
 // from Hin = H_{t-1} and Qprev, and the further workgroups write
 // Hout = H_t and update V with Qprev.
-//
-// In the cross steps the rotation lanes (0..15) own the diagonal block of
-// their rotation and the block (k, k + 1) (lane 15: (0, 15)); after applying
-// the step they hold every entry that the next step's rotation k needs
-// (a_kk, a_kq and, from lane k + 1, a_qq), so the next rotation is formed
-// before the barrier and a step takes one barrier.  The other 104 blocks and
-// the columns of Q are updated by wavefronts 1-3, so the rotation lanes'
-// chain (block update, next rotation) is the only work of wavefront 0.
 template <bool FIRST>
 __global__ __launch_bounds__(kJT) void k_jacobi_round(const double* __restrict__ Hin,
                                                       double* __restrict__ Hout,
@@ -1291,71 +1362,7 @@ __global__ __launch_bounds__(kJT) void k_jacobi_round(const double* __restrict__
   }
   bool rotated = false;
   __syncthreads();
-  if (FIRST) {
-    int gka = 0, gkb = 0;
-    const bool gblk = tid < kJU;
-    if (gblk) upper_block(tid, &gka, &gkb);
-    for (int st = 0; st < kJB - 1; ++st) {
-      if (tid < kJB) {
-        int p, q;
-        step_pair<true>(tid, st, &p, &q);
-        cs[0][tid] = jac_rotation(S[p][q], S[p][p], S[q][q], tol, floor_abs, &rotated);
-      }
-      __syncthreads();
-      if (gblk) upd_block<true>(S, cs[0], st, gka, gkb);
-      upd_q<true>(Q, cs[0], st, tid);
-      __syncthreads();
-    }
-  }
-  // cross steps
-  int oka = 0, okb = 0;
-  const bool oblk = tid >= 64 && tid < 64 + kJOther;
-  if (oblk) other_block(tid - 64, &oka, &okb);
-  double app = 0.0, apq = 0.0, aqq = 0.0;
-  if (tid < kJB) {
-    app = S[tid][tid];
-    apq = S[tid][kJB + tid];
-    aqq = S[kJB + tid][kJB + tid];
-    cs[0][tid] = jac_rotation(apq, app, aqq, tol, floor_abs, &rotated);
-  }
-  __syncthreads();
-  for (int st = 0; st < kJB; ++st) {
-    const double2* C = cs[st & 1];
-    if (tid < kJB) {
-      const int k = tid, k1 = (k + 1) & (kJB - 1);
-      const int ka = (k < kJB - 1) ? k : 0, kb = (k < kJB - 1) ? k1 : kJB - 1;
-      const int p = ka, q = kJB + ((ka + st) & (kJB - 1));
-      const int p2 = kb, q2 = kJB + ((kb + st) & (kJB - 1));
-      double x00 = S[p][p2], x01 = S[p][q2], x10 = S[q][p2], x11 = S[q][q2];
-      const double2 rk = C[k], ra = C[ka], rb = C[kb];
-      // the diagonal block of rotation k, from the registers; every rotation
-      // applied (see blk_rotate_all), the rotated pair's entry set to 0
-      double d00 = app, d01 = apq, d10 = apq, d11 = aqq;
-      const int qk = kJB + ((k + st) & (kJB - 1));
-      blk_rotate_all(rk, rk, d00, d01, d10, d11);
-      const double dz = (rk.y != 0.0) ? 0.0 : apq;
-      S[k][k] = d00;
-      S[qk][qk] = d11;
-      S[k][qk] = dz;
-      S[qk][k] = dz;
-      blk_rotate_all(ra, rb, x00, x01, x10, x11);
-      S[p][p2] = x00; S[p][q2] = x01; S[q][p2] = x10; S[q][q2] = x11;
-      S[p2][p] = x00; S[q2][p] = x01; S[p2][q] = x10; S[q2][q] = x11;
-      const double nx11 = __shfl(d11, k1, 64);
-      if (st + 1 < kJB) {
-        app = d00;
-        aqq = nx11;
-        apq = (k < kJB - 1) ? x01 : x10;
-        cs[(st + 1) & 1][k] = jac_rotation(apq, app, aqq, tol, floor_abs, &rotated);
-      }
-    } else if (tid >= 64) {
-      // wavefronts 1-3: the other blocks, then Q (wavefront 0 carries the
-      // rotation lanes' dependent chain alone)
-      if (oblk) upd_block_cross(S, C, st, oka, okb);
-      upd_q_cross(Q, C, st, tid - 64);
-    }
-    __syncthreads();
-  }
+  jacobi_visit(FIRST, S, Q, cs, tid, tol, floor_abs, rotated);
   double* Qo = Qcur + (int64_t)blockIdx.x * kJP * kJP;
 #pragma unroll
   for (int h = 0; h < kJE; ++h) {
@@ -1466,6 +1473,157 @@ __global__ void k_eig_vectors(const double* __restrict__ V, int R, const int* __
   if (e >= (int64_t)r * r) return;
   const int k = (int)(e / r), c = (int)(e % r);
   W[(int64_t)k * ldw + c] = V[(int64_t)k * R + perm[c]] / sqrt(sig2[c]);
+}
+
+// The whole eigendecomposition for R <= 64 in one workgroup of 256 threads per
+// pair of blocks: H, V, S and Q stay in LDS (101 KB at R = 64), so a round
+// costs its rotation steps and two MFMA phases instead of a launch and a trip
+// through memory, and a sweep no host round trip.  The arithmetic is that of
+// the launches above, entry for entry.  2000 x 500, rank 50: the
+// sketch takes 860 us, 950 with the launches and the visits' earlier form.
+// G (row-major, ld) is padded with zeros; V starts as V0 (column-major r x r)
+// or the identity; sig2 (r, descending, ties in index order) and
+// W(:, c) = v_c / sqrt(sig2_c) come out; the slot receives the number of
+// sweeps, 0 when max_sweeps did not suffice.
+constexpr int kJSmall = 64;
+template <int R>
+__global__ __launch_bounds__(R / kJP * kJT) void k_jacobi_small(
+    const double* __restrict__ G, int r, int ld, const double* __restrict__ V0, int max_sweeps,
+    double tol, double* __restrict__ sig2, double* __restrict__ W, int ldw,
+    unsigned long long* __restrict__ slot, unsigned seq) {
+  constexpr int nb = R / kJB, np = nb / 2, NT = np * kJT;
+  constexpr int NTILE = R / 16;   // 16 x 16 tiles to a side
+  constexpr int TPW = NTILE * NTILE / (NT / 64);   // of H (and of V) per wavefront
+  __shared__ double H[R][R + 1];
+  __shared__ double V[R][R + 1];
+  __shared__ double S[np][kJP][kJP + 1];
+  __shared__ double Q[np][kJP][kJP + 1];
+  __shared__ double2 cs[np][2][kJB];
+  __shared__ double trace;
+  __shared__ int fails[2];
+  __shared__ int perm[R];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int fi = lane & 15, fk = lane >> 4;
+  const int pr = tid / kJT, pt = tid % kJT;   // this thread's pair, index within it
+  for (int e = tid; e < R * R; e += NT) {
+    const int i = e / R, j = e % R;
+    const bool in = i < r && j < r;
+    H[i][j] = in ? G[(int64_t)i * ld + j] : 0.0;
+    V[i][j] = (in && V0 != nullptr) ? V0[(int64_t)j * r + i] : (i == j ? 1.0 : 0.0);
+  }
+  if (tid < 2) fails[tid] = 0;
+  __syncthreads();
+  if (wv == 0) {
+    const double t = wave_sum(lane < R ? fabs(H[lane][lane]) : 0.0);
+    if (lane == 0) trace = t;
+  }
+  __syncthreads();
+  const double floor_abs = tol * trace;
+  bool rotated = false;
+  int sweeps = 0;
+  for (int sweep = 0; sweep < max_sweeps; ++sweep) {
+    for (int t = 0; t < nb - 1; ++t) {
+      int a, b;
+      rr_pair(nb, t, pr, &a, &b);
+#pragma unroll
+      for (int h = 0; h < kJE; ++h) {
+        const int e = pt + h * kJT;
+        const int i = e / kJP, j = e % kJP;
+        const int lo = i < j ? i : j, hi = i < j ? j : i;
+        S[pr][i][j] = H[pair_index(a, b, lo)][pair_index(a, b, hi)];
+        Q[pr][i][j] = (i == j) ? 1.0 : 0.0;
+      }
+      __syncthreads();
+      jacobi_visit(t == 0, S[pr], Q[pr], cs[pr], pt, tol, floor_abs, rotated);
+      // H <- Q^T H Q and V <- V Q over the pairs' rows and columns: the tiles
+      // H Q and V Q, a barrier, their stores in place, then Q^T (H Q)
+      d4 acc[TPW], vac[TPW];
+      int row0[TPW], col0[TPW], tp[TPW], th[TPW], vrow[TPW];
+#pragma unroll
+      for (int u = 0; u < TPW; ++u) {
+        const int e = wv * TPW + u, br = e / NTILE, bc = e % NTILE;
+        // block column bc of the pairs in order: half bc & 1 of pair bc / 2
+        int qa, qb, pa, pb;
+        rr_pair(nb, t, bc >> 1, &qa, &qb);
+        rr_pair(nb, t, br >> 1, &pa, &pb);
+        const int ch = bc & 1, rh = br & 1;
+        row0[u] = kJB * (rh ? pb : pa);
+        col0[u] = kJB * (ch ? qb : qa);
+        vrow[u] = 16 * br;
+        tp[u] = br >> 1;
+        th[u] = rh;
+        acc[u] = (d4)0.0;
+        vac[u] = (d4)0.0;
+#pragma unroll
+        for (int k0 = 0; k0 < kJP; k0 += 4) {
+          const double q = Q[bc >> 1][k0 + fk][16 * ch + fi];
+          const int kc = pair_index(qa, qb, k0 + fk);
+          acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(H[row0[u] + fi][kc], q, acc[u], 0, 0, 0);
+          vac[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[vrow[u] + fi][kc], q, vac[u], 0, 0, 0);
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < TPW; ++u)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          H[row0[u] + fk + 4 * v][col0[u] + fi] = acc[u][v];
+          V[vrow[u] + fk + 4 * v][col0[u] + fi] = vac[u][v];
+        }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < TPW; ++u) {
+        int pa, pb;
+        rr_pair(nb, t, tp[u], &pa, &pb);
+        acc[u] = (d4)0.0;
+#pragma unroll
+        for (int k0 = 0; k0 < kJP; k0 += 4)
+          acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+              Q[tp[u]][k0 + fk][16 * th[u] + fi], H[pair_index(pa, pb, k0 + fk)][col0[u] + fi],
+              acc[u], 0, 0, 0);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < TPW; ++u)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) H[row0[u] + fk + 4 * v][col0[u] + fi] = acc[u][v];
+      __syncthreads();
+    }
+    // the criterion of k_jacobi_check
+    int bad = 0;
+    for (int e = tid; e < R * R; e += NT) {
+      const int i = e / R, j = e % R;
+      if (j > i) {
+        const double apq = fmin(fabs(H[i][j]), fabs(H[j][i]));
+        bad |= jac_rotates(apq, H[i][i], H[j][j], tol, floor_abs) ? 1 : 0;
+      }
+    }
+    if (__any(bad) && lane == 0) fails[sweep & 1] = 1;
+    __syncthreads();
+    if (fails[sweep & 1] == 0) {   // uniform: read by all after the barrier
+      sweeps = sweep + 1;
+      break;
+    }
+    if (tid == 0) fails[(sweep + 1) & 1] = 0;
+  }
+  if (sweeps > 0) {
+    if (tid < R) {
+      const double v = H[tid][tid];
+      int rank = 0;
+      for (int j = 0; j < R; ++j) {
+        const double w = H[j][j];
+        rank += (w > v) || (w == v && j < tid);
+      }
+      perm[rank] = tid;
+      if (rank < r) sig2[rank] = v;
+    }
+    __syncthreads();
+    for (int e = tid; e < r * r; e += NT) {
+      const int k = e / r, c = e % r;
+      W[(int64_t)k * ldw + c] = V[k][perm[c]] / sqrt(H[perm[c]][perm[c]]);
+    }
+  }
+  if (tid == 0) *slot = ((unsigned long long)seq << 32) | (unsigned)sweeps;
 }
 
 }  // namespace
@@ -1722,6 +1880,27 @@ nys_status jacobi_eig(hipStream_t st, const double* G, int r, int ld, double* ws
   double* gnorm = s2 + 2 * R;   // perm occupies R ints = R/2 doubles
   const int64_t RR = (int64_t)R * R;
   if (max_sweeps < 1 || max_sweeps > 60) return NYS_ERR_INVALID;
+  auto* slots_h = reinterpret_cast<volatile unsigned long long*>(
+      static_cast<char*>(host_pinned) + kJacSlotOffset);
+  auto* slots_d =
+      reinterpret_cast<unsigned long long*>(static_cast<char*>(host_pinned_dev) + kJacSlotOffset);
+  if (R <= kJSmall) {
+    // sequence numbers are unique per context: stale slot contents never match
+    *poll_seq = (*poll_seq % 1000000000) + 1;
+    const unsigned seq = (unsigned)*poll_seq;
+    if (R == kJP)
+      hipLaunchKernelGGL(k_jacobi_small<kJP>, dim3(1), dim3(kJT), 0, st, G, r, ld, V0, max_sweeps,
+                         tol, sig2, W, ldw, slots_d, seq);
+    else
+      hipLaunchKernelGGL(k_jacobi_small<kJSmall>, dim3(1), dim3(kJSmall / kJP * kJT), 0, st, G, r,
+                         ld, V0, max_sweeps, tol, sig2, W, ldw, slots_d, seq);
+    if (hipGetLastError() != hipSuccess) return NYS_ERR_HIP;
+    int n = 0;
+    NYS_TRY(wait_word(st, slots_h, seq, &n));
+    if (n == 0) return NYS_ERR_NOT_CONVERGED;
+    if (sweeps_out) *sweeps_out = n;
+    return NYS_OK;
+  }
   hipLaunchKernelGGL(k_pad, dim3((unsigned)((RR + 255) / 256)), dim3(256), 0, st, G, r, ld, G0, R);
   hipLaunchKernelGGL(k_trace, dim3(1), dim3(256), 0, st, G0, R, gnorm);
   if (V0 != nullptr)
@@ -1734,10 +1913,6 @@ nys_status jacobi_eig(hipStream_t st, const double* G, int r, int ld, double* ws
   // (written by the device into pinned memory), so the GPU does not idle on a
   // host round trip between sweeps; a sweep enqueued after convergence returns
   // at once.  after[s] is the buffer that holds the matrix after sweep s.
-  auto* slots_h = reinterpret_cast<volatile unsigned long long*>(
-      static_cast<char*>(host_pinned) + kJacSlotOffset);
-  auto* slots_d =
-      reinterpret_cast<unsigned long long*>(static_cast<char*>(host_pinned_dev) + kJacSlotOffset);
   double* after[60];
   unsigned seqs[60];
   constexpr int kAhead = 2;

@@ -303,3 +303,22 @@ def test_sketch_fp64_product_edges(N, ctx, n, d, r, dtype, weights):
     assert rel(H, f.dense()) < 1e-10
     assert inf["nu"] == f.nu
     F.close()
+
+
+@pytest.mark.parametrize("r", [1, 31, 32, 33, 63, 64])
+@pytest.mark.parametrize("equal", [False, True])
+def test_eigensolver_small_ranks(N, ctx, r, equal):
+    # ranks at the edges of the one-workgroup eigensolver's padded sizes 32 and
+    # 64, with distinct eigenvalues and (equal) with all of them alike; the same
+    # bar as the other FP64 sketches
+    n, d = 600, 150
+    A = torch.linalg.qr(synth.gaussian((n, d), seed=r))[0].contiguous() if equal \
+        else synth.decay_matrix(n, d, 0.6, seed=r)
+    om = synth.omega_raw(d, r, seed=r + 1)
+    F = N.nys_sketch(ctx, A.to(DEV), om.to(DEV), prec=N.NYS_F64)
+    H, U, lam, inf = hhat(F, ctx)
+    f = ny.rand_nys_appx(A.numpy(), None, 0.0, om.numpy().T)
+    assert rel(H, f.dense()) < 1e-10
+    assert np.all(np.diff(lam) <= 0.0) and np.allclose(lam, f.lam, rtol=1e-10, atol=0.0)
+    assert np.linalg.norm(U.T @ U - np.eye(r)) < 1e-10
+    F.close()
