@@ -598,20 +598,20 @@ nys_status pcg_run(nys_ctx ctx, const nys_dense& A, const double* D, double c, d
   double true_rr = -1.0;
   for (;;) {
     NYS_TRY(launch_zero_state(ws.st, st));
-    // w0 = rhs - H_rho x0 ; y0 = P^-1 w0 ; p0 = y0 (the judge may still change w0)
-    const FusedDot* dot0 = fuse && !(x_alt != nullptr && restarts == 0) ? &fdot : nullptr;
+    // w0 = rhs - H_rho x0 ; y0 = P^-1 w0 ; p0 = y0.  U^T w0 has its own launch:
+    // the judge may change w0, and a rejected candidate leaves the same bits
     const AtbKey key{A.data, D, A.n, d, A.ld, x};
     if (hx_tag >= 0 && restarts == 0 && ctx->hx_tag == hx_tag && ctx->hx_key == key &&
         ctx->hx_rho == rho && ctx->hx_c == c) {
       // H_rho x0 from the previous solve's true-residual pass (x0 unchanged)
       NYS_TRY(launch_reduce_update(1, ws.ypart, 0, pl.ldy, ws.qpart, d, 1.0, ctx->hx.as<double>(),
                                    nullptr, ws.w, rhs, ws.wy, 0, nullptr, 0, ws.wwpart, ws.rrpart,
-                                   ws.st, st, -1, false, ws.rj, dot0));
+                                   ws.st, st, -1, false, ws.rj));
     } else {
       NYS_TRY(ctx_gram(ctx, A, pl, kModeHess, x, D, nullptr, ws.ypart, ws.qpart, nullptr));
       NYS_TRY(launch_reduce_update(1, ws.ypart, pl.ny(), pl.ldy, ws.qpart, d, rho_eff, x, nullptr,
                                    ws.w, rhs, ws.wy, 0, nullptr, 0, ws.wwpart, ws.rrpart, ws.st,
-                                   st, pl.nq(), false, ws.rj, dot0));
+                                   st, pl.nq(), false, ws.rj));
     }
     ctx->hx_key = AtbKey{};
     if (x_alt != nullptr && restarts == 0) {
@@ -623,12 +623,10 @@ nys_status pcg_run(nys_ctx ctx, const nys_dense& A, const double* D, double c, d
                                    ws.rrpart2, ws.st, st, pl.nq(), false, ws.rj));
       NYS_TRY(launch_judge(ws.wwpart, ws.wwpart2, ws.nred, x, x_alt, ws.w, ws.w2, d, ws.st, st));
     }
-    if (dot0 == nullptr)
-      NYS_TRY(launch_precond_dot(U, u32, d, r, ws.w, ws.cvec, ws.st, ws.wwpart, ws.nred,
-                                 ws.rrpart, -1, 1, tol_rel, tol_abs, st));
+    NYS_TRY(launch_precond_dot(U, u32, d, r, ws.w, ws.cvec, ws.st, ws.wwpart, ws.nred,
+                               ws.rrpart, -1, 1, tol_rel, tol_abs, st));
     NYS_TRY(launch_precond_update(U, u32, d, r, lam, lam_s, rho, ws.cvec, ws.w, ws.p, ws.wy, 0,
-                                  ws.wwpart, ws.nred, ws.pppart, ws.st, 1, st, nullptr, 0, false,
-                                  nullptr, dot0, ws.rrpart, tol_rel, tol_abs));
+                                  ws.wwpart, ws.nred, ws.pppart, ws.st, 1, st));
     // Iterations are enqueued `ahead` at a time beyond the last state the host
     // has read: the state after each iteration reaches a pinned host slot with
     // a sequence number (copied there by the first thread of the next

@@ -560,7 +560,7 @@ inline int nblk(int64_t d, int b) { return (int)((d + b - 1) / b); }
 //   op 2 (true):    w = rhs - v  (true residual, FP64 accumulation); v -> x if x != NULL
 //   op 3 (plain):   w = v
 //   op 4 (carry):   x = rhs - w  (H_rho x from the recursive residual; ypart unused)
-// c = U^T w formed by the partial reduction (op 0 and 1): its `parts`
+// c = U^T w formed by the partial reduction (op 0): its `parts`
 // workgroups leave partials of ldc entries (ldc = r rounded up to even), which
 // are added, and ||w||^2 tested, by launch_precond_update.
 struct FusedDot {
@@ -635,9 +635,7 @@ nys_status launch_precond_update(const void* U, bool u32, int64_t d, int r, cons
                                  double* p, double* wy, int k, const double* wwpart, int nww,
                                  double* pppart, PcgDev* st, int mode, hipStream_t stream,
                                  PcgDev* host_slot = nullptr, int seq = 0, bool pre = false,
-                                 const double* gpre = nullptr, const FusedDot* dot = nullptr,
-                                 const double* rrpart = nullptr, double tol_rel = 0.0,
-                                 double tol_abs = 0.0);
+                                 const double* gpre = nullptr, const FusedDot* dot = nullptr);
 // large d: g_i = s_i c_i (c summed from its slices) and sum_i s_i c_i^2 into
 // gout[0, r) and gout[1024], once per iteration, for launch_precond_update
 nys_status launch_c_reduce(const double* cvec, int64_t d, int r, const double* lam, double lam_s,

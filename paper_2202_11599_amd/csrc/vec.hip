@@ -133,7 +133,7 @@ __device__ __forceinline__ bool pcg_stops(int mode, int k, double ww, double rr,
 // 256 threads: RJ lanes x (256 / RJ) slices of the workgroup partials, each
 // lane summing VW adjacent columns; the slices are combined in a fixed order
 // through LDS.
-// UT other than void (op 0 and 1): the workgroup also leaves its columns'
+// UT other than void (op 0): the workgroup also leaves its columns'
 // share of c = U^T w in cpart[blockIdx.x * ldc + i] (i < ldc, ldc = r rounded
 // up to even), which k_precond_update adds in workgroup order after testing
 // ||w||^2.  That takes the launch of k_precond_dot out of the iteration, whose
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(256) void k_precond_dot(
 // mode 0: p = y + beta p (beta = (w^T y)/wy[k]), wy[k+1] = w^T y
 // mode 1: p = y, wy[0] = w^T y
 // mode 2: p (output) = y, standalone apply
-// FUSED (modes 0 and 1, after the reduction that leaves U^T w): c comes as nsl
+// FUSED (mode 0, after the reduction that leaves U^T w): c comes as nsl
 // workgroup partials of ldc entries, and ||w||^2 is tested here.
 template <typename UT, int NU, int VJ, bool FUSED>
 __global__ __launch_bounds__(256) void k_precond_update(
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(256) void k_precond_update(
     double* __restrict__ p, double* __restrict__ wy, int k, const double* __restrict__ wwpart,
     int nww, double* __restrict__ pppart, PcgDev* __restrict__ st, int mode,
     PcgDev* __restrict__ host_slot, int seq, int nsl, int pre, const double* __restrict__ gpre,
-    int ldc, const double* __restrict__ rrpart, double tol_rel, double tol_abs) {
+    int ldc) {
   // host_slot (pinned host memory, may be NULL): receives the state at the end
   // of the iteration, read by the host once the kernel has completed.
   // gpre (may be NULL): g and sum s c^2 already reduced by k_c_reduce
@@ -446,12 +446,10 @@ __global__ __launch_bounds__(256) void k_precond_update(
     if (mode == 0) pold = p[j];
   }
   const double wyk = (mode == 0) ? wy[k & (kWyRing - 1)] : 0.0;
-  [[maybe_unused]] double rv[4];
   if constexpr (FUSED) {
     // the lead thread of this very launch may set done: one reading for the
     // whole workgroup
     __shared__ int done;
-    pre_load(rrpart, mode == 1 ? nww : 0, rv);
     if (tid == 0) done = st->done;
     __syncthreads();
     if (done) return;
@@ -527,12 +525,7 @@ __global__ __launch_bounds__(256) void k_precond_update(
   if (mode != 2) {
     const double ww = (pre && mode == 0) ? st->wwn : pre_sum(wwpart, nww, wv, sh4);
     if constexpr (FUSED) {
-      double rr = 0.0;
-      if (mode == 1) {
-        __syncthreads();
-        rr = pre_sum(rrpart, nww, rv, sh4);
-      }
-      if (pcg_stops(mode, k, ww, rr, tol_rel, tol_abs, st, blockIdx.x == 0 && tid == 0)) return;
+      if (pcg_stops(0, k, ww, 0.0, 0.0, 0.0, st, blockIdx.x == 0 && tid == 0)) return;
     }
     __syncthreads();
     wy_new = ww + (gpre != nullptr ? gpre[1024] : block_sum_value(sc, sh4));
@@ -820,7 +813,7 @@ nys_status launch_reduce_update(int op, const double* ypart, int G, int ldy, con
     else go(k_reduce_update<kRedBlockWide / 2, 2, T>, kRedBlockWide, U);
   };
   if (dot != nullptr) {
-    if ((rj != kRedBlock && rj != kRedBlockWide) || !wide || (op != 0 && op != 1))
+    if ((rj != kRedBlock && rj != kRedBlockWide) || !wide || op != 0)
       return NYS_ERR_INVALID;
     if (dot->u32) go_dot(static_cast<const float*>(dot->U));
     else go_dot(static_cast<const double*>(dot->U));
@@ -884,10 +877,9 @@ nys_status launch_precond_update(const void* U, bool u32, int64_t d, int r, cons
                                  double* p, double* wy, int k, const double* wwpart, int nww,
                                  double* pppart, PcgDev* st, int mode, hipStream_t stream,
                                  PcgDev* host_slot, int seq, bool pre, const double* gpre,
-                                 const FusedDot* dot, const double* rrpart, double tol_rel,
-                                 double tol_abs) {
+                                 const FusedDot* dot) {
   if (r > 1024) return NYS_ERR_INVALID;
-  if (dot != nullptr && (pre || mode == 2 || dot->ldc > 512 || dot->parts < 1))
+  if (dot != nullptr && (pre || mode != 0 || dot->ldc > 512 || dot->parts < 1))
     return NYS_ERR_INVALID;
   const int vj = vec_block(d);
   const int grid = nblk(d, vj);
@@ -901,7 +893,7 @@ nys_status launch_precond_update(const void* U, bool u32, int64_t d, int r, cons
   auto go = [&](auto kern, const auto* u) {
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, stream, u, d, r, lam, lam_s, rho, cvec, w,
                        p, wy, k, wwpart, nww, pppart, st, mode, host_slot, seq, nsl, pre ? 1 : 0,
-                       gpre, dot ? dot->ldc : 0, rrpart, tol_rel, tol_abs);
+                       gpre, dot ? dot->ldc : 0);
   };
   auto pick = [&](const auto* u) {
     using T = std::remove_const_t<std::remove_pointer_t<decltype(u)>>;
