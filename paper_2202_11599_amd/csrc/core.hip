@@ -425,6 +425,42 @@ __device__ __forceinline__ void upper_tile(int e, int n, int* I, int* J) {
   *J = a + e;
 }
 
+// Upper Cholesky factor of the b x b block in C (upper triangle read and
+// written, b <= kCB) by one wavefront, in registers; rdiag = 1 / its diagonal.
+// False on a non-positive or non-finite pivot.
+constexpr int kCB = 32;
+__device__ __forceinline__ bool chol_block(double (&C)[kCB][kCB + 1], double (&rdiag)[kCB], int b,
+                                           int lane) {
+  // lane j (mod 32) holds column j, padded to 32 x 32 with the identity
+  // beyond b; entries below the diagonal are carried but never read
+  const int j = lane & (kCB - 1);
+  double col[kCB];
+#pragma unroll
+  for (int p = 0; p < kCB; ++p)
+    col[p] = (p < b && j < b && p <= j) ? C[p][j] : (p == j ? 1.0 : 0.0);
+  bool ok = true;
+  double rj = 1.0;
+#pragma unroll
+  for (int i = 0; i < kCB; ++i) {
+    const double dii = readlane_f64(col[i], i);
+    ok = ok && (dii > 0.0) && isfinite(dii);
+    double piv, rinv;
+    chol_pivot(dii, &piv, &rinv);
+    col[i] = (j == i) ? piv : col[i] * rinv;
+    if (j == i) rj = rinv;
+#pragma unroll
+    for (int p = 0; p < kCB; ++p)
+      if (p > i) col[p] = fma(-readlane_f64(col[i], p), col[i], col[p]);
+  }
+  if (lane < b) {
+#pragma unroll
+    for (int p = 0; p < kCB; ++p)
+      if (p <= j) C[p][j] = col[p];
+    rdiag[j] = rj;
+  }
+  return ok;
+}
+
 // Upper Cholesky factor C (C^T C = M) in place, row-major with leading
 // dimension ld; only the upper triangle of M is read, and the strict lower
 // triangle receives C^T (M[j][i] = C[i][j]), so that column l of C is
@@ -436,7 +472,6 @@ __device__ __forceinline__ void upper_tile(int e, int n, int* I, int* J) {
 // columns at once), and the trailing upper triangle takes the rank-kCB update
 // as 16 x 16 tiles on the FP64 matrix cores.  *fail = 1 on a non-positive or
 // non-finite pivot.
-constexpr int kCB = 32;
 constexpr int kCholOneWg = 256;
 constexpr int kCholT = 512;   // threads of k_chol_upper
 
@@ -457,33 +492,7 @@ __global__ __launch_bounds__(kCholT) void k_chol_upper(double* __restrict__ M, i
     }
     __syncthreads();
     if (tid < 64) {
-      // lane j (mod 32) holds column j, padded to 32 x 32 with the identity
-      // beyond b; entries below the diagonal are carried but never read
-      const int j = lane & (kCB - 1);
-      double col[kCB];
-#pragma unroll
-      for (int p = 0; p < kCB; ++p)
-        col[p] = (p < b && j < b && p <= j) ? C[p][j] : (p == j ? 1.0 : 0.0);
-      bool ok = true;
-      double rj = 1.0;
-#pragma unroll
-      for (int i = 0; i < kCB; ++i) {
-        const double dii = readlane_f64(col[i], i);
-        ok = ok && (dii > 0.0) && isfinite(dii);
-        double piv, rinv;
-        chol_pivot(dii, &piv, &rinv);
-        col[i] = (j == i) ? piv : col[i] * rinv;
-        if (j == i) rj = rinv;
-#pragma unroll
-        for (int p = 0; p < kCB; ++p)
-          if (p > i) col[p] = fma(-readlane_f64(col[i], p), col[i], col[p]);
-      }
-      if (lane < b) {
-#pragma unroll
-        for (int p = 0; p < kCB; ++p)
-          if (p <= j) C[p][j] = col[p];
-        rdiag[j] = rj;
-      }
+      const bool ok = chol_block(C, rdiag, b, lane);
       if (!ok && lane == 0) bad = 1;
     }
     __syncthreads();
@@ -550,47 +559,32 @@ __global__ __launch_bounds__(kCholT) void k_chol_upper(double* __restrict__ M, i
 }
 
 // ---- blocked Cholesky for r > kCholOneWg (same contract as k_chol_upper)
-constexpr int kLB = 64;
+// Blocks of 32: with 64 the diagonal block took 85 us in LDS (two barriers a
+// column), the block row 48 and the update 29, 13 times at r = 800; 32 rows fit
+// a wavefront's registers (20000 x 20000, rank 800: the sketch with its two
+// factorisations 31.0 -> 28.7 ms).
+constexpr int kLB = 32;
+static_assert(kLB == kCB, "the diagonal block's factor is chol_block's");
 
-// Diagonal block M[kb:kb+b, kb:kb+b] <- its upper Cholesky factor (LDS).
-__global__ __launch_bounds__(256) void k_chol_diag(double* __restrict__ M, int ld, int kb, int b,
-                                                   int* __restrict__ fail) {
-  __shared__ double C[kLB][kLB + 1];
-  __shared__ double rowv[kLB];
-  __shared__ int bad;
+// Diagonal block M[kb:kb+b, kb:kb+b] <- its upper Cholesky factor.
+__global__ __launch_bounds__(64) void k_chol_diag(double* __restrict__ M, int ld, int kb, int b,
+                                                  int* __restrict__ fail) {
+  __shared__ double C[kCB][kCB + 1];
+  __shared__ double rdiag[kCB];
   if (*fail) return;
-  const int tid = threadIdx.x;
-  if (tid == 0) bad = 0;
-  for (int e = tid; e < b * b; e += 256) {
+  const int lane = threadIdx.x;
+  for (int e = lane; e < b * b; e += 64) {
     const int i = e / b, j = e % b;
     C[i][j] = (j >= i) ? M[(int64_t)(kb + i) * ld + kb + j] : 0.0;
   }
   __syncthreads();
-  // thread column q = tid % kLB, rows p = tid / kLB + 4 k of the b x b block
-  const int tq = tid % kLB;
-  for (int i = 0; i < b; ++i) {
-    if (tid >= i && tid < b) {
-      const double dii = C[i][i];
-      if (tid == i && (!(dii > 0.0) || !isfinite(dii))) bad = 1;
-      double piv, rinv;
-      chol_pivot(dii, &piv, &rinv);
-      rowv[tid] = (tid == i) ? piv : C[i][tid] * rinv;
-    }
-    __syncthreads();
-    if (bad) break;
-    if (tid >= i && tid < b) C[i][tid] = rowv[tid];
-    if (tq < b) {
-      const double rq = rowv[tq];
-      for (int pp = tid / kLB; pp <= tq; pp += 256 / kLB)
-        if (pp > i) C[pp][tq] -= rowv[pp] * rq;
-    }
-    __syncthreads();
-  }
-  if (bad) {
-    if (tid == 0) *fail = 1;
+  const bool ok = chol_block(C, rdiag, b, lane);
+  __syncthreads();
+  if (!ok) {
+    if (lane == 0) *fail = 1;
     return;
   }
-  for (int e = tid; e < b * b; e += 256) {
+  for (int e = lane; e < b * b; e += 64) {
     const int i = e / b, j = e % b;
     if (j >= i) M[(int64_t)(kb + i) * ld + kb + j] = C[i][j];
   }
@@ -650,13 +644,13 @@ __global__ __launch_bounds__(256) void k_chol_trail(double* __restrict__ M, int 
     Xq[i][jj] = jj < nq ? M[(int64_t)(kb + i) * ld + c + q0 + jj] : 0.0;
   }
   __syncthreads();
-  // 16 outputs per thread: rows pr = tid / 16 + 16 a, columns qc = tid % 16 + 16 e
+  // rows pr = tid / 16 + 16 a, columns qc = tid % 16 + 16 e
   const int pr0 = tid >> 4, qc0 = tid & 15;
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
+  for (int a = 0; a < kLB / 16; ++a) {
     const int pp = pr0 + 16 * a;
 #pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2) {
+    for (int e2 = 0; e2 < kLB / 16; ++e2) {
       const int qq = qc0 + 16 * e2;
       if (pp >= np || qq >= nq) continue;
       if (ti == tj && qq < pp) continue;   // upper triangle only
@@ -1794,7 +1788,7 @@ nys_status chol_upper(hipStream_t st, double* M, int r, int ld, int* fail) {
   for (int kb = 0; kb < r; kb += kLB) {
     const int b = std::min(kLB, r - kb);
     const int nrest = r - kb - b;
-    hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, M, ld, kb, b, fail);
+    hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(64), 0, st, M, ld, kb, b, fail);
     if (nrest > 0) {
       const int tc = (nrest + kLB - 1) / kLB;
       hipLaunchKernelGGL(k_chol_panel, dim3(tc), dim3(256), 0, st, M, ld, kb, b, nrest, fail);

@@ -322,3 +322,18 @@ def test_eigensolver_small_ranks(N, ctx, r, equal):
     assert np.all(np.diff(lam) <= 0.0) and np.allclose(lam, f.lam, rtol=1e-10, atol=0.0)
     assert np.linalg.norm(U.T @ U - np.eye(r)) < 1e-10
     F.close()
+
+
+@pytest.mark.parametrize("r", [257, 288, 289])
+def test_blocked_cholesky_block_edges(N, ctx, r):
+    # the blocked Cholesky's blocks of 32: one past its smallest rank, whole
+    # blocks, a last block of one; the bars of the large ranks above
+    n, d = 2000, 700
+    A64 = synth.decay_matrix(n, d, 0.6, seed=r)
+    om = synth.omega_raw(d, r, seed=r + 1)
+    F = N.nys_sketch(ctx, A64.to(DEV), om.to(DEV), prec=N.NYS_F64)
+    H, U, lam, inf = hhat(F, ctx)
+    f = ny.rand_nys_appx(A64.numpy(), None, 0.0, om.numpy().T)
+    assert rel(H, f.dense()) < 1e-10 and inf["nu"] == f.nu
+    assert np.linalg.norm(U.T @ U - np.eye(r)) < 1e-11 * r
+    F.close()
