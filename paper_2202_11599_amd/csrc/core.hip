@@ -1630,7 +1630,7 @@ __global__ __launch_bounds__(R / kJP * kJT) void k_jacobi_small(
 // loads besides (about 1400 cycles for the steps in flight).  1024 SIMDs take
 // the units in turn, a unit starts with about 2500 cycles of latency, and a
 // split adds a launch and the partial sums' way through the caches.  The
-// cheapest shape that the partial-sum buffer holds is taken: 2000 x 100 x 20000
+// cheapest shape that the planned partial-sum buffer holds is taken: 2000 x 100 x 20000
 // (A^T T, FP32 A) 187 us with 16 chunks of 32 x 64 tiles, 236 with 25 (a fourth
 // turn of the SIMDs for the last units); 6000 x 300 x 6000 418 us unsplit, 470
 // with 10 chunks.
@@ -1691,8 +1691,8 @@ static GemmShape gemm64_shape(int M, int N, int K, double ta_a, double ta_b, siz
 
 nys_status gemm64(hipStream_t st, int M, int N, int K, const void* A, bool a_f32, int64_t sam,
                   int64_t sak, const void* B, bool b_f32, int64_t sbk, int64_t sbn, double* C,
-                  int64_t scm, int64_t scn, double alpha, double beta, double* split_ws,
-                  size_t split_ws_elems, const double* wk, const double* A2, double ca) {
+                  int64_t scm, int64_t scn, double alpha, double beta, const SplitBuf& split,
+                  const double* wk, const double* A2, double ca) {
   if (M <= 0 || N <= 0) return NYS_OK;
   if (scm != 1 && scn == 1) {
     // row-major C: the kernel stores along m, so form C^T = B^T A^T
@@ -1709,25 +1709,40 @@ nys_status gemm64(hipStream_t st, int M, int N, int K, const void* A, bool a_f32
   const bool akc = sak == 1, bkc = sbk == 1 && !(A2 != nullptr && sbn == 1);
   const GemmShape sh = gemm64_shape(M, N, K, akc ? (a_f32 ? 1.0 : 2.0) : 1.0,
                                     bkc ? (b_f32 ? 1.0 : 2.0) : 1.5,
-                                    split_ws != nullptr ? split_ws_elems : 0);
+                                    split.ptr != nullptr ? split.plan : 0);
+  // panels of C whose partials fit the buffer (all of C as a rule)
+  int pm = M, pn = N;
+  if (sh.S > 1 && (size_t)sh.S * M * N > split.elems) {
+    pm = (int)std::min<size_t>(M, split.elems / ((size_t)sh.S * N) / 32 * 32);
+    if (pm == 0) {
+      pm = std::min(M, 32);
+      pn = (int)std::min<size_t>(N, split.elems / ((size_t)sh.S * pm));
+      if (pn == 0) return NYS_ERR_INVALID;
+    }
+  }
   GemmArgs g;
-  g.M = M; g.N = N; g.K = K;
+  g.K = K;
   g.kchunk = sh.kchunk;
-  g.MT = (M + 16 * sh.RB - 1) / (16 * sh.RB);
-  g.NBT = sh.NBT;
-  g.NT = ((N + 15) / 16 + sh.NBT - 1) / sh.NBT;
   g.S = sh.S;
   g.sam = sam; g.sak = sak; g.sbk = sbk; g.sbn = sbn; g.scm = scm; g.scn = scn;
-  g.split_stride = (int64_t)M * N;
   g.alpha = alpha; g.beta = beta; g.ca = ca;
-  const int64_t units = (int64_t)g.MT * g.NT * g.S;
-  if (units > (int64_t)1 << 30) return NYS_ERR_INVALID;
-  const dim3 grid((unsigned)((units + 3) / 4));
-  double* out = g.S > 1 ? split_ws : C;
+  auto panel = [&](int m0, int n0) -> nys_status {
+    g.M = std::min(pm, M - m0);
+    g.N = std::min(pn, N - n0);
+    g.MT = (g.M + 16 * sh.RB - 1) / (16 * sh.RB);
+    g.NBT = sh.NBT;
+    g.NT = ((g.N + 15) / 16 + sh.NBT - 1) / sh.NBT;
+    g.split_stride = (int64_t)g.M * g.N;
+    const int64_t units = (int64_t)g.MT * g.NT * g.S;
+    if (units > (int64_t)1 << 30) return NYS_ERR_INVALID;
+    const dim3 grid((unsigned)((units + 3) / 4));
+    double* Cp = C + m0 * scm + n0 * scn;
+    double* out = g.S > 1 ? split.ptr : Cp;
 #define NYS_GEMM1(TA, TB, AK, BK, RBV, NT, FU)                                                    \
   hipLaunchKernelGGL((k_gemm64<TA, TB, AK, BK, RBV, NT, FU>), grid, dim3(256), 0, st, g,          \
-                     static_cast<const TA*>(A), reinterpret_cast<const TA*>(A2),                  \
-                     static_cast<const TB*>(B), out, wk)
+                     static_cast<const TA*>(A) + m0 * sam,                                        \
+                     FU ? reinterpret_cast<const TA*>(A2) + m0 * sam : nullptr,                   \
+                     static_cast<const TB*>(B) + n0 * sbn, out, wk)
   // without a k-contiguous operand there is one order
 #define NYS_GEMM(TA, TB, AK, BK, FU)                                                              \
   do {                                                                                            \
@@ -1740,39 +1755,43 @@ nys_status gemm64(hipStream_t st, int M, int N, int K, const void* A, bool a_f32
       else NYS_GEMM1(TA, TB, AK, BK, 1, kOne, FU);                                                \
     }                                                                                             \
   } while (0)
-  if (!a_f32 && !b_f32) {
-    if (A2 != nullptr) {
-      if (akc || bkc) return NYS_ERR_INVALID;
-      NYS_GEMM(double, double, false, false, true);
-    } else if (akc && bkc) {
-      NYS_GEMM(double, double, true, true, false);
-    } else if (akc) {
-      NYS_GEMM(double, double, true, false, false);
-    } else if (bkc) {
-      NYS_GEMM(double, double, false, true, false);
+    if (!a_f32 && !b_f32) {
+      if (A2 != nullptr) {
+        if (akc || bkc) return NYS_ERR_INVALID;
+        NYS_GEMM(double, double, false, false, true);
+      } else if (akc && bkc) {
+        NYS_GEMM(double, double, true, true, false);
+      } else if (akc) {
+        NYS_GEMM(double, double, true, false, false);
+      } else if (bkc) {
+        NYS_GEMM(double, double, false, true, false);
+      } else {
+        NYS_GEMM(double, double, false, false, false);
+      }
+    } else if (A2 != nullptr || !bkc) {
+      return NYS_ERR_INVALID;
+    } else if (a_f32 && b_f32) {   // T^T T, X X^T
+      if (!akc) return NYS_ERR_INVALID;
+      NYS_GEMM(float, float, true, true, false);
+    } else if (a_f32) {            // A Omega, A^T T
+      if (akc) NYS_GEMM(float, double, true, true, false);
+      else NYS_GEMM(float, double, false, true, false);
     } else {
-      NYS_GEMM(double, double, false, false, false);
+      return NYS_ERR_INVALID;
     }
-  } else if (A2 != nullptr || !bkc) {
-    return NYS_ERR_INVALID;
-  } else if (a_f32 && b_f32) {   // T^T T, X X^T
-    if (!akc) return NYS_ERR_INVALID;
-    NYS_GEMM(float, float, true, true, false);
-  } else if (a_f32) {            // A Omega, A^T T
-    if (akc) NYS_GEMM(float, double, true, true, false);
-    else NYS_GEMM(float, double, false, true, false);
-  } else {
-    return NYS_ERR_INVALID;
-  }
 #undef NYS_GEMM
 #undef NYS_GEMM1
-  if (hipGetLastError() != hipSuccess) return NYS_ERR_HIP;
-  if (g.S > 1) {
-    const int64_t tot = (int64_t)M * N;
-    hipLaunchKernelGGL(k_split_reduce, dim3((unsigned)((tot + kSrOut - 1) / kSrOut)), dim3(256), 0, st,
-                       M, N, g.S, split_ws, C, scm, scn, alpha, beta);
     if (hipGetLastError() != hipSuccess) return NYS_ERR_HIP;
-  }
+    if (g.S > 1) {
+      const int64_t tot = (int64_t)g.M * g.N;
+      hipLaunchKernelGGL(k_split_reduce, dim3((unsigned)((tot + kSrOut - 1) / kSrOut)), dim3(256),
+                         0, st, g.M, g.N, g.S, split.ptr, Cp, scm, scn, alpha, beta);
+      if (hipGetLastError() != hipSuccess) return NYS_ERR_HIP;
+    }
+    return NYS_OK;
+  };
+  for (int n0 = 0; n0 < N; n0 += pn)
+    for (int m0 = 0; m0 < M; m0 += pm) NYS_TRY(panel(m0, n0));
   return NYS_OK;
 }
 

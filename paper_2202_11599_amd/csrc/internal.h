@@ -312,11 +312,19 @@ nys_status admm_solve_batched(nys_ctx ctx, int count, const nys_problem* P,
 // A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn], C(m,n) = C[m*scm + n*scn];
 // with A2 the left operand is A + ca A2.  Each operand has unit stride along
 // one of its indices (FP32 operands along k, or m for A; A2: A along m, B along n).
+//
+// Split-K partial sums: the split is chosen for a buffer of `plan` doubles and
+// the partials written to ptr, which holds elems; where they do not fit, the
+// product is formed in panels of C with the same split, so that the order of
+// summation follows from the sizes and plan alone.
+struct SplitBuf {
+  double* ptr = nullptr;
+  size_t elems = 0, plan = 0;
+};
 nys_status gemm64(hipStream_t st, int M, int N, int K, const void* A, bool a_f32, int64_t sam,
                   int64_t sak, const void* B, bool b_f32, int64_t sbk, int64_t sbn, double* C,
-                  int64_t scm, int64_t scn, double alpha, double beta, double* split_ws,
-                  size_t split_ws_elems, const double* wk = nullptr, const double* A2 = nullptr,
-                  double ca = 0.0);
+                  int64_t scm, int64_t scn, double alpha, double beta, const SplitBuf& split,
+                  const double* wk = nullptr, const double* A2 = nullptr, double ca = 0.0);
 nys_status chol_upper(hipStream_t st, double* M, int r, int ld, int* fail);
 nys_status trinv_upper(hipStream_t st, const double* Cm, int r, int ld, double* Z, int ldz);
 nys_status power_iter(hipStream_t st, const double* G, int r, int ld, int iters, double* out);

@@ -734,25 +734,53 @@ __global__ void k_to_f32(const double* __restrict__ x, int64_t n, float* __restr
 inline unsigned blocks(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 struct CoreWs {
-  double *GY, *GO, *M, *Cinv, *Bm, *G, *W, *sig2, *jac, *split, *scal;
+  double *GY, *GO, *M, *Cinv, *Bm, *G, *W, *sig2, *jac, *scal;
+  SplitBuf split;
   int* ints;
-  size_t split_elems;
 };
 
-// Doubles of the split-K partial sums.  From rank 65 on at least 8 MB and 32
-// (16 above rank 256) partials of an r x r product, which a product with few
-// tiles wants; where that does not fit a caller's workspace, the least (small).
-size_t core_split_elems(int64_t d, int r, bool small) {
-  const size_t least = std::max<size_t>((size_t)16 * r * r, (size_t)4 * d * std::min(r, 64));
-  if (small || r <= 64) return least;
-  return std::max<size_t>({least, (size_t)1 << 20, (size_t)(r <= 256 ? 32 : 16) * r * r});
+// Doubles of the split-K partial sums that the core's workspace holds
+size_t core_split_elems(int64_t d, int r) {
+  return std::max<size_t>((size_t)16 * r * r, (size_t)4 * d * std::min(r, 64));
 }
 
-size_t core_ws_bytes_of(int64_t d, int r, bool small = false) {
+// The same for the products over n (Y = A^T T; A Omega of a symmetric A), which
+// have few tiles and many k: from rank 65 on at least 8 MB and 32 (16 above
+// rank 256) partials of an r x r product.  Whole sketches with the split of
+// core_split_elems and with this one (us): 200000 x 1000 rank 150 6975 / 4960,
+// 60000 x 1000 rank 100 2680 / 2115, 20000 x 2000 rank 100 2115 / 2050; the
+// other products gain nothing from more (100000 x 4000 rank 200 in FP32 6300 /
+// 6310).  Held for the one product only, so that no other buffer of a call has
+// to do without it, and planned for whether it is to be had or not (SplitBuf):
+// a factor's bits do not depend on the memory that is left.
+size_t n_split_elems(int64_t d, int r) {
+  const size_t least = core_split_elems(d, r);
+  if (r <= 64) return least;
+  return std::max<size_t>({least, (size_t)1 << 20, (size_t)(r <= 256 ? 32 : 16) * r * r});
+}
+class NSplit {
+ public:
+  NSplit(const CoreWs& w, int64_t d, int r) : buf_(w.split) {
+    buf_.plan = n_split_elems(d, r);
+    if (buf_.plan <= buf_.elems || own_.reserve(sizeof(double) * buf_.plan) != NYS_OK) return;
+    buf_.ptr = own_.as<double>();
+    buf_.elems = buf_.plan;
+  }
+  ~NSplit() { own_.release(); }
+  NSplit(const NSplit&) = delete;
+  NSplit& operator=(const NSplit&) = delete;
+  const SplitBuf& get() const { return buf_; }
+
+ private:
+  SplitBuf buf_;
+  DevBuf own_;
+};
+
+size_t core_ws_bytes_of(int64_t d, int r) {
   const size_t rr = align_up(sizeof(double) * (size_t)r * r);
   const size_t dr = align_up(sizeof(double) * (size_t)d * r);
   const size_t jac = align_up(sizeof(double) * jacobi_ws_doubles(r));
-  const size_t split = align_up(sizeof(double) * core_split_elems(d, r, small));
+  const size_t split = align_up(sizeof(double) * core_split_elems(d, r));
   return 6 * rr + dr + jac + split + align_up(sizeof(double) * 1024) + 4096 + 4096;
 }
 
@@ -760,13 +788,8 @@ nys_status core_workspace(nys_ctx ctx, int64_t d, int r, CoreWs* w) {
   const size_t rr = align_up(sizeof(double) * (size_t)r * r);
   const size_t dr = align_up(sizeof(double) * (size_t)d * r);
   const size_t jac = align_up(sizeof(double) * jacobi_ws_doubles(r));
-  bool small = false;
-  if (ctx->core_ws.reserve(core_ws_bytes_of(d, r)) != NYS_OK) {
-    small = true;
-    NYS_TRY(ctx->core_ws.reserve(core_ws_bytes_of(d, r, true)));
-  }
-  w->split_elems = core_split_elems(d, r, small);
-  const size_t split = align_up(sizeof(double) * w->split_elems);
+  const size_t elems = core_split_elems(d, r);
+  NYS_TRY(ctx->core_ws.reserve(core_ws_bytes_of(d, r)));
   char* p = static_cast<char*>(ctx->core_ws.ptr);
   auto take = [&](size_t b) { char* q = p; p += b; return reinterpret_cast<double*>(q); };
   w->GY = take(rr);
@@ -777,7 +800,7 @@ nys_status core_workspace(nys_ctx ctx, int64_t d, int r, CoreWs* w) {
   w->W = take(rr);
   w->Bm = take(dr);
   w->jac = take(jac);
-  w->split = take(split);
+  w->split = SplitBuf{take(align_up(sizeof(double) * elems)), elems, elems};
   w->sig2 = take(align_up(sizeof(double) * 1024));
   w->scal = take(4096);
   w->ints = reinterpret_cast<int*>(take(4096));
@@ -828,18 +851,18 @@ nys_status orthonormalize(nys_ctx ctx, double* Om, int64_t d, int m, const CoreW
   double* err_dev = reinterpret_cast<double*>(w.ints + 2);
   NYS_TRY_HIP(hipMemsetAsync(w.ints, 0, sizeof(int), st));
   NYS_TRY(gemm64(st, m, m, (int)d, Om, false, d, 1, Om, false, 1, d, w.M, m, 1, 1.0, 0.0,
-                 w.split, w.split_elems));
+                 w.split));
   double err = 0.0;
   for (int pass = 0; pass < 2; ++pass) {
     NYS_TRY(chol_upper(st, w.M, m, m, w.ints));
     NYS_TRY(trinv_upper(st, w.M, m, m, w.Cinv, m));
     // Bm = Om Rinv  (d x m col-major), then copy back
     NYS_TRY(gemm64(st, (int)d, m, m, Om, false, 1, d, w.Cinv, false, m, 1, tmp, 1, d, 1.0, 0.0,
-                   w.split, w.split_elems));
+                   w.split));
     NYS_TRY_HIP(hipMemcpyAsync(Om, tmp, sizeof(double) * d * m, hipMemcpyDeviceToDevice, st));
     // Q^T Q: the acceptance test, and the next pass's Gram
     NYS_TRY(gemm64(st, m, m, (int)d, Om, false, d, 1, Om, false, 1, d, w.M, m, 1, 1.0, 0.0,
-                   w.split, w.split_elems));
+                   w.split));
     hipLaunchKernelGGL(k_orth_err, dim3(1), dim3(1024), 0, st, w.M, m, err_dev);
     unsigned char hb[16];
     NYS_TRY(read_back(ctx, w.ints, sizeof(hb), hb));
@@ -869,18 +892,17 @@ nys_status nys_core(nys_ctx ctx, nys_factor F, double test_mu, int* above) {
   const double* Y = F->Y.as<double>();
   const double* Om = F->Omega.as<double>();
   // ||Y||_2 = sqrt(lambda_max(Y^T Y))
-  NYS_TRY(gemm64(st, r, r, (int)d, Y, false, d, 1, Y, false, 1, d, w.GY, r, 1, 1.0, 0.0, w.split,
-                 w.split_elems));
+  NYS_TRY(gemm64(st, r, r, (int)d, Y, false, d, 1, Y, false, 1, d, w.GY, r, 1, 1.0, 0.0, w.split));
   NYS_TRY(power_iter(st, w.GY, r, r, 300, w.scal));
   // Omega^T Omega
   NYS_TRY(gemm64(st, r, r, (int)d, Om, false, d, 1, Om, false, 1, d, w.GO, r, 1, 1.0, 0.0,
-                 w.split, w.split_elems));
+                 w.split));
   // base core matrix Omega^T Y (FP64 form; also for an explicit symmetric
   // matrix) or the stored T^T D T + c Omega^T Omega
   const double* base;
   if (F->prec == NYS_F64 || F->sym || F->sparse) {
     NYS_TRY(gemm64(st, r, r, (int)d, Om, false, d, 1, Y, false, 1, d, w.G, r, 1, 1.0, 0.0,
-                   w.split, w.split_elems));
+                   w.split));
     base = w.G;
   } else {
     base = F->Mbase.as<double>();
@@ -908,16 +930,16 @@ nys_status nys_core(nys_ctx ctx, nys_factor F, double test_mu, int* above) {
   // summation that small ranks keep (see gemm64_shape)
   if (r > 64) {
     NYS_TRY(gemm64(st, (int)d, r, r, Y, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, 1.0, 0.0,
-                   w.split, w.split_elems, nullptr, Om, nu));
+                   w.split, nullptr, Om, nu));
   } else {
     NYS_TRY(gemm64(st, (int)d, r, r, Y, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, 1.0, 0.0,
-                   w.split, w.split_elems));
+                   w.split));
     NYS_TRY(gemm64(st, (int)d, r, r, Om, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, nu, 1.0,
-                   w.split, w.split_elems));
+                   w.split));
   }
   // G = B^T B, eigendecomposition G = V Sigma^2 V^T
   NYS_TRY(gemm64(st, r, r, (int)d, w.Bm, false, d, 1, w.Bm, false, 1, d, w.G, r, 1, 1.0, 0.0,
-                 w.split, w.split_elems));
+                 w.split));
   if (test_mu >= 0.0) {
     // inertia of G - (nu + test_mu) I through one Cholesky attempt
     hipLaunchKernelGGL(k_sub_diag, dim3(blocks((int64_t)r * r)), dim3(256), 0, st, w.G, r,
@@ -944,7 +966,7 @@ nys_status nys_core(nys_ctx ctx, nys_factor F, double test_mu, int* above) {
   if (F->basis_hint != nullptr) {
     double* Vb = w.GO;   // r x r column-major (free after the shifted Cholesky)
     NYS_TRY(gemm64(st, r, r, (int)d, w.Bm, false, d, 1, F->basis_hint, false, 1, d, Vb, 1, r,
-                   1.0, 0.0, w.split, w.split_elems));
+                   1.0, 0.0, w.split));
     double err = 0.0;
     nys_status so = orthonormalize(ctx, Vb, r, r, w, w.W, &err);
     // CholeskyQR is exact to rounding only for a well-conditioned V0:
@@ -953,9 +975,9 @@ nys_status nys_core(nys_ctx ctx, nys_factor F, double test_mu, int* above) {
     if (so == NYS_OK) {
       // G' = V0^T (G V0): T1 (column-major) in GY, G' (row-major) in M
       NYS_TRY(gemm64(st, r, r, r, w.G, false, r, 1, Vb, false, 1, r, w.GY, 1, r, 1.0, 0.0,
-                     w.split, w.split_elems));
+                     w.split));
       NYS_TRY(gemm64(st, r, r, r, Vb, false, r, 1, w.GY, false, 1, r, w.M, r, 1, 1.0, 0.0,
-                     w.split, w.split_elems));
+                     w.split));
       V0 = Vb;
       Gj = w.M;
     } else if (so != NYS_ERR_NOT_SPD) {
@@ -971,7 +993,7 @@ nys_status nys_core(nys_ctx ctx, nys_factor F, double test_mu, int* above) {
   // U = B V Sigma^-1
   NYS_TRY(F->U.reserve(sizeof(double) * d * r));
   NYS_TRY(gemm64(st, (int)d, r, r, w.Bm, false, 1, d, w.W, false, r, 1, F->U.as<double>(), 1, d,
-                 1.0, 0.0, w.split, w.split_elems));
+                 1.0, 0.0, w.split));
   NYS_TRY(F->lam.reserve(sizeof(double) * r));
   hipLaunchKernelGGL(k_lambda, dim3(blocks(r)), dim3(256), 0, st, w.sig2, nu, r,
                      F->lam.as<double>());
@@ -1160,13 +1182,6 @@ Sk32Shape sk32_shape(int64_t n, int64_t d, int m, int num_cu, bool bf) {
   return s;
 }
 
-// Doubles for the split-K partials of T = A Omega in FP64: four copies of T, at
-// most 64 MB (20000 x 100 at 2000 columns: 250 us in three chunks, 285 in one).
-// None up to 64 columns, which keep the split that w.split allows.
-size_t t_split_elems(int64_t n, int m) {
-  return m <= 64 ? 0 : std::min<size_t>((size_t)4 * n * m, (size_t)1 << 23);
-}
-
 // Sketch one block of m new columns into F (columns r_old .. r_old+m-1).
 nys_status sketch_block(nys_ctx ctx, const nys_dense& A, const double* D, double c,
                         const double* omega, int m, nys_factor F) {
@@ -1207,8 +1222,9 @@ nys_status sketch_block(nys_ctx ctx, const nys_dense& A, const double* D, double
   } else if (F->sym && F->prec == NYS_F64) {
     // explicit symmetric H = A + c I (kernel SVM): Y = A Omega + c Omega, FP64 sums
     NYS_TRY_HIP(hipMemcpyAsync(Y + d * r0, Om, sizeof(double) * d * m, hipMemcpyDeviceToDevice, st));
+    const NSplit split(w, d, std::max(r1, m));
     NYS_TRY(gemm64(st, (int)n, m, (int)d, A.data, a32, A.ld, 1, Om, false, 1, d, Y + d * r0, 1, d,
-                   1.0, c, w.split, w.split_elems));
+                   1.0, c, split.get()));
   } else if (F->sym) {
     // the same in FP32: Omega rounded to FP32 (the rounded values written
     // back, so the core sees the Omega the products used), Y = A Omega by the
@@ -1226,20 +1242,15 @@ nys_status sketch_block(nys_ctx ctx, const nys_dense& A, const double* D, double
     hipLaunchKernelGGL(k_sym_y, dim3(blocks((int64_t)m * d)), dim3(256), 0, st, T + ldt * r0, ldt,
                        (int)d, m, Om, c, Y + d * r0);
   } else if (F->prec == NYS_F64) {
-    // T = A Omega (n x m, column-major) in FP64 tiles, Y = A^T (D o T) + c Omega;
-    // T's split-K partials follow it (left out where a caller's workspace is short)
-    size_t tsplit = t_split_elems(n, m);
-    if (ctx->gemm_ws.reserve(sizeof(double) * (n * m + tsplit) + 256) != NYS_OK) {
-      tsplit = 0;
-      NYS_TRY(ctx->gemm_ws.reserve(sizeof(double) * n * m + 256));
-    }
+    // T = A Omega (n x m, column-major) in FP64 tiles, Y = A^T (D o T) + c Omega
+    NYS_TRY(ctx->gemm_ws.reserve(sizeof(double) * n * m + 256));
     double* T = ctx->gemm_ws.as<double>();
     NYS_TRY(gemm64(st, (int)n, m, (int)d, A.data, a32, A.ld, 1, Om, false, 1, d, T, 1, n, 1.0, 0.0,
-                   tsplit > w.split_elems ? T + n * m : w.split,
-                   std::max(tsplit, w.split_elems)));
+                   w.split));
     NYS_TRY_HIP(hipMemcpyAsync(Y + d * r0, Om, sizeof(double) * d * m, hipMemcpyDeviceToDevice, st));
+    const NSplit split(w, d, std::max(r1, m));
     NYS_TRY(gemm64(st, (int)d, m, (int)n, A.data, a32, 1, A.ld, T, false, 1, n, Y + d * r0, 1, d,
-                   1.0, c, w.split, w.split_elems, D));
+                   1.0, c, split.get(), D));
   } else {
     if (!a32) return NYS_ERR_INVALID;
     const bool bf = (F->prec == NYS_BF16);
@@ -1288,11 +1299,11 @@ nys_status sketch_block(nys_ctx ctx, const nys_dense& A, const double* D, double
                          gs.G, r1, r0, m, sym, Mb, ldm);
     } else {
       NYS_TRY(gemm64(st, r1, m, (int)n, T, true, ldt, 1, T + ldt * r0, true, 1, ldt, Mb + r0, ldm,
-                     1, 1.0, 0.0, w.split, w.split_elems, D));
+                     1, 1.0, 0.0, w.split, D));
     }
     if (c != 0.0)
       NYS_TRY(gemm64(st, r1, m, (int)d, F->Omega.ptr, false, d, 1, Om, false, 1, d, Mb + r0, ldm,
-                     1, c, 1.0, w.split, w.split_elems));
+                     1, c, 1.0, w.split));
     hipLaunchKernelGGL(k_mirror_cols, dim3(blocks((int64_t)r1 * m)), dim3(256), 0, st, Mb, ldm, r0,
                        r1);
   }
@@ -1384,7 +1395,7 @@ nys_status sketch_round(nys_ctx ctx, const nys_dense* A, const double* D, double
 void sketch_ws_bytes(const nys_dense& A, int m, int r, int num_cu, size_t* tmp,
                      size_t* factor_out) {
   const int64_t n = A.n, d = A.d;
-  size_t g = sizeof(double) * ((size_t)n * m + t_split_elems(n, m)) + 256;   // FP64 form
+  size_t g = sizeof(double) * (size_t)n * m + 256;                       // FP64 form
   g = std::max(g, sizeof(double) * (size_t)(n + 2 * d) * m + 256);       // sparse form
   if (A.dtype == NYS_F32) {
     const Sk32Shape s = sk32_shape(n, d, m, num_cu, false);               // FP32 >= BF16
