@@ -27,9 +27,11 @@
  *    n-vector of non-negative Hessian weights (H^l of the loss, Section 2.1);
  *    D == NULL means the identity (least squares).  Entry points that take a
  *    caller's D (nys_sketch, nys_sketch_adaptive, nys_hessian_apply,
- *    pcg_solve) check it on the device first and synchronise the stream:
- *    a negative weight gives NYS_ERR_INVALID, a NaN or infinite one
- *    NYS_ERR_NONFINITE.  A NaN or infinity in A, b or rhs surfaces as
+ *    pcg_solve) check it on the device and wait for the verdict before they
+ *    write any output: a negative weight gives NYS_ERR_INVALID, a NaN or
+ *    infinite one NYS_ERR_NONFINITE.  The work queued on the stream before the
+ *    call has completed by then, and a refused call leaves none of its own
+ *    running.  A NaN or infinity in A, b or rhs surfaces as
  *    NYS_ERR_NONFINITE from the first residual or sketch norm it reaches.
  *  - The Gaussian test-matrix entries `omega` are passed in by the caller:
  *    FP64, column-major d x r (column k at omega + k*d).  They may come from

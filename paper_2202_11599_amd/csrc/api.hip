@@ -438,7 +438,8 @@ nys_status ctx_gram(nys_ctx ctx, const nys_dense& A, const GramPlan& plan, int m
   return NYS_OK;
 }
 
-nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out) {
+nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out,
+                         const VecCheck* pending) {
   if (const nys_sparse_s* S = as_sparse(A)) {
     *out = make_sparse_plan(S);
     return NYS_OK;
@@ -474,6 +475,7 @@ nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out) {
     *out = make_gram_plan(A, ctx->num_cu);
     return NYS_OK;
   }
+  if (pending != nullptr) NYS_TRY(check_end(ctx, *pending));
   int gmax = 0;
   for (auto& c : cands) gmax = std::max(gmax, c.grid);
   const int ldy = cands[0].ldy;
@@ -1095,19 +1097,24 @@ nys_status nys_hessian_apply(nys_ctx ctx, const nys_dense* A, const double* D, d
   if (!(rho + c >= 0.0)) return NYS_ERR_INVALID;
   NYS_TRY_HIP(hipSetDevice(ctx->device));
   nys::CtxScope ctx_scope(ctx);
-  // D's check runs before the pass over A and is waited for while that runs;
-  // v is only written after it
+  // D's check runs before the pass over A and is waited for while that runs (a
+  // shape that has to be timed first waits for it); v is only written after it,
+  // and a refused call returns when its pass has ended
   VecCheck chk;
   NYS_TRY(check_begin(ctx, D, A->n, 0, &chk));
   GramPlan pl;
   PcgWs ws;
   auto pass = [&]() -> nys_status {
-    NYS_TRY(ctx_gram_plan(ctx, *A, &pl));
+    NYS_TRY(ctx_gram_plan(ctx, *A, &pl, &chk));
     NYS_TRY(pcg_workspace(ctx, pl, A->d, 1, &ws));
     return ctx_gram(ctx, *A, pl, kModeHess, p, D, nullptr, ws.ypart, ws.qpart, nullptr);
   };
   const nys_status passed = pass();
-  NYS_TRY(check_end(ctx, chk));
+  const nys_status checked = check_end(ctx, chk);
+  if (checked != NYS_OK) {
+    (void)hipStreamSynchronize(ctx->stream);
+    return checked;
+  }
   NYS_TRY(passed);
   NYS_TRY(launch_reduce_update(3, ws.ypart, pl.ny(), pl.ldy, ws.qpart, A->d, rho + c, p, nullptr,
                                v, nullptr, nullptr, 0, nullptr, 0, nullptr, nullptr, ws.st,

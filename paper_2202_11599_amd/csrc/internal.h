@@ -270,7 +270,11 @@ size_t align_up(size_t x);
 // Launch shape for A: the fastest of gram_candidates() timed on A itself the
 // first time this (dtype, n, d, ld, alignment) is seen, cached in the context.
 // NYSADMM_GRAM_PLAN forces a shape, NYSADMM_TUNE=0 uses the heuristic.
-nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out);
+// pending: a begun argument check, ended (and its error returned) before
+// anything is timed.
+struct VecCheck;
+nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out,
+                         const VecCheck* pending = nullptr);
 // launch_gram on the context's stream, timed when profiling is on
 // note (may be NULL): pinned host slot that the launch's first thread fills
 // with the PCG state *done belongs to (done = &PcgDev::done), sequence number
@@ -281,9 +285,11 @@ nys_status ctx_gram(nys_ctx ctx, const nys_dense& A, const GramPlan& plan, int m
 nys_status validate_dense(const nys_dense* A);
 // Device check of a caller's n-vector (kind as launch_check_vec), in two parts:
 // check_begin enqueues it on the context's stream, check_end waits for its
-// result (NYS_ERR_NONFINITE for NaN/Inf, NYS_ERR_INVALID for a broken rule).
-// Work enqueued between them must write nothing that the caller owns.  Every
-// begun check is ended before the call returns; check_vector does both.
+// result (NYS_ERR_NONFINITE for NaN/Inf, NYS_ERR_INVALID for a broken rule; the
+// same again when it is ended twice).  Work enqueued between them must write
+// nothing that the caller owns, and a call that ends in an error waits for it:
+// it reads the caller's buffers.  Every begun check is ended before the call
+// returns; check_vector does both.
 struct VecCheck {
   int grid = 0;        // workgroups that report, 0: nothing to wait for
   unsigned seq = 0;

@@ -170,3 +170,39 @@ def test_weight_check_reaches_every_entry(N, ctx, n):
     N.nys_hessian_apply(ctx, A, p, rho=0.0, D=D, out=out)
     torch.cuda.synchronize()
     assert bool((out == 3.0 * n).all())   # whole numbers: exact
+
+
+@pytest.mark.parametrize("shape,timed", [((60000, 4000), True),   # a shape that is timed first
+                                         ((80000, 900), False)])  # whole rows per wavefront
+def test_refused_weights_leave_nothing_running(N, shape, timed, monkeypatch, capfd):
+    """A call that D's check refuses has no pass over A in flight when it
+    returns, and times no launch shape before the verdict."""
+    monkeypatch.setenv("NYSADMM_VERBOSE", "1")
+    n, d = shape
+    ctx = N.Context()
+    A = torch.ones((n, d), dtype=torch.float32, device=DEV)
+    p = torch.ones(d, dtype=torch.float64, device=DEV)
+    out = torch.full((d,), 7.0, dtype=torch.float64, device=DEV)
+    D = torch.ones(n, dtype=torch.float64, device=DEV)
+    call = lambda: N.nys_hessian_apply(ctx, A, p, rho=0.0, D=D, out=out)
+    stream = torch.cuda.current_stream()
+    for bad, want in ((-1.0, N.NYS_ERR_INVALID), (float("inf"), N.NYS_ERR_NONFINITE)):
+        D[n - 1] = bad
+        torch.cuda.synchronize()
+        got = status_of(N, call)
+        idle = stream.query()
+        assert got == want and idle
+        assert "matvec plan" not in capfd.readouterr().err
+        # once more with the shape known
+        D[n - 1] = 1.0
+        call()
+        torch.cuda.synchronize()
+        assert bool((out == float(n) * d).all())   # whole numbers: exact
+        assert not timed or "matvec plan" in capfd.readouterr().err or bad != -1.0
+        out.fill_(7.0)
+        D[n - 1] = bad
+        torch.cuda.synchronize()
+        got = status_of(N, call)
+        idle = stream.query()
+        assert got == want and idle and bool((out == 7.0).all())
+    ctx.close()
