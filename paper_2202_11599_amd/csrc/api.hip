@@ -451,12 +451,20 @@ nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out,
   }
   const char* forced = getenv("NYSADMM_GRAM_PLAN");
   const char* tune = getenv("NYSADMM_TUNE");
+  const bool rows = gram_rows_plan(A, ctx->num_cu, out);
+  if (rows && forced != nullptr && strcmp(forced, "rows") == 0) return NYS_OK;
   if (forced != nullptr || (tune != nullptr && tune[0] == '0') || A.n < 4096) {
     *out = make_gram_plan(A, ctx->num_cu);
     return NYS_OK;
   }
-  // whole rows per wavefront where that applies (fixed shape, nothing to tune)
-  if (gram_rows_plan(A, ctx->num_cu, out)) return NYS_OK;
+  // Whole rows per wavefront (one fixed shape) without timing anything for an A
+  // that stays in the memory-side cache: 1.18 to 1.85 times as fast there as the
+  // best of the candidates (180 MB, FP32 and FP64 of 60 to 1024 columns, odd
+  // ones too).  For one that streams it is timed with them: columns that leave
+  // its lanes half empty or end in single elements lose (1.6 GB: FP64 257
+  // columns 358 us against 276, FP32 511 378 against 306, 1003 283 against 266),
+  // the others gain (FP32 1001 258 against 265, FP64 1024 241 against 249).
+  if (rows && !gram_streams(A)) return NYS_OK;
   const int esize = A.dtype == NYS_F64 ? 8 : 4;
   const bool aligned = ((uintptr_t)A.data % 16 == 0) && ((A.ld * esize) % 16 == 0);
   char key[160];
@@ -471,6 +479,7 @@ nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out,
     return NYS_OK;
   }
   std::vector<GramPlan> cands = gram_candidates(A, ctx->num_cu);
+  if (rows) cands.push_back(*out);
   if (cands.empty()) {
     *out = make_gram_plan(A, ctx->num_cu);
     return NYS_OK;
@@ -513,9 +522,10 @@ nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out,
   scratch.release();
   ctx->plans[key] = bestp;
   if (getenv("NYSADMM_VERBOSE"))
-    fprintf(stderr, "nysadmm: matvec plan for %lld x %lld: waves %d, chunks %d, rows %d, %d wg/CU, "
+    fprintf(stderr, "nysadmm: matvec plan for %lld x %lld: waves %d, chunks %d, rows %d%s, %d wg/CU, "
             "grid %d (%.1f us, %zu candidates)\n", (long long)A.n, (long long)A.d, bestp.waves,
-            bestp.cpl, bestp.rows, bestp.per_cu, bestp.grid, 1e3 * best / 3, cands.size());
+            bestp.cpl, bestp.rows, bestp.rowwave ? " (whole rows per wavefront)" : "",
+            bestp.per_cu, bestp.grid, 1e3 * best / 3, cands.size());
   *out = bestp;
   return NYS_OK;
 }

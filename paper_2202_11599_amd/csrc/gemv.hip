@@ -106,7 +106,6 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES >= 4 ? 2 : 1)) void k_gram(
 // 33.7 (38.8), 200000 x 1000 237 (243).
 constexpr int kRwW = 8;
 constexpr int kRwCpl = 8;
-constexpr int64_t kRwCachedBytes = (int64_t)240 << 20;
 template <typename T, int CPL, int R, bool NTL>
 __global__ __launch_bounds__(kRwW * 64, 2) void k_gram_rows(
     const T* __restrict__ A, int64_t n, int d, int64_t ld, int64_t rows_per_wg, int mode,
@@ -296,7 +295,7 @@ nys_status launch_rows(const nys_dense& A, const GramPlan& pl, int mode, const d
                          pl.rows_per_wg, mode, p, aux, auxout, ypart, pl.ldy, qpart, done, note,
                          note_seq);
   };
-  if (A.n * A.ld * (int64_t)sizeof(T) > kRwCachedBytes) go(k_gram_rows<T, CPL, R, true>);
+  if (gram_streams(A)) go(k_gram_rows<T, CPL, R, true>);
   else go(k_gram_rows<T, CPL, R, false>);
   return hipGetLastError() == hipSuccess ? NYS_OK : NYS_ERR_HIP;
 }
@@ -359,7 +358,7 @@ bool gram_rows_plan(const nys_dense& A, int num_cu, GramPlan* pl) {
   // 2048 FP32 columns fill the registers (256, a few spilled): where the
   // pass streams from HBM anyway the one-workgroup-per-row form is faster
   // (200000 x 2000: 250 us against 263; 20000 x 2000 from the cache: 36 against 32)
-  if (A.dtype == NYS_F32 && A.d > 1024 && A.n * A.ld * 4 > kRwCachedBytes) return false;
+  if (A.dtype == NYS_F32 && A.d > 1024 && gram_streams(A)) return false;
   *pl = GramPlan{};
   pl->rowwave = true;
   pl->waves = kRwW;
@@ -415,7 +414,7 @@ std::vector<GramPlan> gram_candidates(const nys_dense& A, int num_cu) {
 // Heuristic plan: the narrowest row coverage with 4 chunks per lane when it
 // fits in at most 4 waves (two workgroups per CU, rows in double-buffered
 // groups of 2), else 2 chunks per lane.  NYSADMM_GRAM_PLAN="waves,cpl,rows,
-// wg_per_cu" overrides (launch-shape sweeps).
+// wg_per_cu" overrides (launch-shape sweeps; "rows" is ctx_gram_plan's).
 GramPlan make_gram_plan(const nys_dense& A, int num_cu) {
   GramPlan pl;
   const int vn = A.dtype == NYS_F64 ? 2 : 4;

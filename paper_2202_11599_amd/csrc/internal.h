@@ -267,9 +267,12 @@ struct PcgWs {
 
 // ---- api.hip
 size_t align_up(size_t x);
-// Launch shape for A: the fastest of gram_candidates() timed on A itself the
-// first time this (dtype, n, d, ld, alignment) is seen, cached in the context.
-// NYSADMM_GRAM_PLAN forces a shape, NYSADMM_TUNE=0 uses the heuristic.
+// Launch shape for A: below 4096 rows the heuristic one, whole rows per
+// wavefront for narrow rows of an A that the memory-side cache holds, otherwise
+// the fastest of gram_candidates() (and of whole rows per wavefront, where they
+// apply) timed on A itself the first time this (dtype, n, d, ld, alignment) is
+// seen, cached in the context.  NYSADMM_GRAM_PLAN forces a shape ("rows": whole
+// rows per wavefront), NYSADMM_TUNE=0 uses the heuristic.
 // pending: a begun argument check, ended (and its error returned) before
 // anything is timed.
 struct VecCheck;
@@ -503,6 +506,12 @@ std::vector<GramPlan> gram_candidates(const nys_dense& A, int num_cu);
 // the plan of k_gram_rows, false where it does not apply
 constexpr int64_t kRwMinRows = 4096;
 bool gram_rows_plan(const nys_dense& A, int num_cu, GramPlan* pl);
+// true for an A that the memory-side cache (256 MB) does not hold from one pass
+// to the next, next to the vectors and partial sums
+constexpr int64_t kCachedBytes = (int64_t)240 << 20;
+inline bool gram_streams(const nys_dense& A) {
+  return A.n * A.ld * (A.dtype == NYS_F64 ? 8 : 4) > kCachedBytes;
+}
 // Launch the fused pass  t = A p;  s = mode(t);  y_g = sum_{rows of g} s_i A_i.
 nys_status launch_gram(const nys_dense& A, const GramPlan& plan, int mode, const double* p,
                        const double* aux, double* auxout, double* ypart, double* qpart,

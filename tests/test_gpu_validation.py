@@ -172,8 +172,8 @@ def test_weight_check_reaches_every_entry(N, ctx, n):
     assert bool((out == 3.0 * n).all())   # whole numbers: exact
 
 
-@pytest.mark.parametrize("shape,timed", [((60000, 4000), True),   # a shape that is timed first
-                                         ((80000, 900), False)])  # whole rows per wavefront
+@pytest.mark.parametrize("shape,timed", [((60000, 4000), True),    # a shape that is timed first
+                                         ((60000, 1000), False)])  # whole rows per wavefront
 def test_refused_weights_leave_nothing_running(N, shape, timed, monkeypatch, capfd):
     """A call that D's check refuses has no pass over A in flight when it
     returns, and times no launch shape before the verdict."""
