@@ -3,16 +3,16 @@
 // instances advance in lockstep:
 //   * the matvec pair of every instance runs over a list of (instance, row
 //     range) tiles: one launch for all instances of up to 2048 FP32 / 1024
-//     FP64 columns (k_brows), one per bucket of row widths for the wider ones
-//     (k_bgram); instances whose PCG has converged skip their tiles;
+//     FP64 columns (k_brows) of a batch that the memory-side cache holds, one
+//     per bucket of row widths otherwise (k_bgram, or k_brows where it is the
+//     faster one); instances whose PCG has converged skip their tiles;
 //   * the d-vector kernels run over (instance, block) item lists;
 //   * the iteration index lives on the device (PcgDev::k), so a chunk of PCG
 //     iterations is captured once into a hipGraph and replayed until every
 //     instance has converged;
-//   * the launch shape of each bucket of wide instances (waves, chunks, rows
-//     per group, rows per tile, workgroups per CU) is picked by timing
-//     candidates on the batch itself the first time it is seen (autotune,
-//     cached in the context).
+//   * the launch shape of each such bucket (waves, chunks, rows per group,
+//     rows per tile, workgroups per CU) is picked by timing candidates on the
+//     batch itself the first time it is seen (autotune, cached in the context).
 // Per instance the arithmetic is that of the single-problem path: FP64
 // products and sums of the stored A, the same PCG recurrences and tests.
 #include <algorithm>
@@ -152,11 +152,13 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES >= 4 ? 2 : 1)) void k_bgram(
 // and 128 KB in flight per CU (two workgroups).  Plain loads: a batch that fits
 // the memory-side cache is read from there (non-temporal ones: 15.3 instead of
 // 13.8 ms for the call below; 2 to 5% either way where it does not fit).
-// Order of summation: that of k_bgram with W wavefronts (two for aligned rows
-// of up to 512 chunks / 4) and two chunks per lane (dot: lane chains over the
-// chunks of virtual wavefront w, butterfly, then w ascending; y: rows ascending
-// within the tile), bit for bit: the PCG runs of low-rank factors carry a
-// last-bit change into the eighth digit of their iterates.
+// Order of summation, fixed by the columns and the tile: the dot of a row is
+// the sum of W parts in ascending order, part w a butterfly over the lanes of
+// each lane's chain through its two chunks (w + m W of the row's chunks for
+// aligned rows, 2 w + m otherwise; of two parts, one a chunk, for aligned rows of
+// W = 1); a column of y adds the tile's rows in ascending order.  Another order
+// would be as accurate; this one is kept because the PCG runs of low-rank
+// factors carry a last-bit change into the eighth digit of their iterates.
 // Measured on 8 instances of 2000..12000 x 300..1500 (203 MB), 10 ADMM
 // iterations (184 passes): 13.8 ms, against 36.9 with one launch of k_bgram per
 // row-width bucket (about 180 us per pass: a tile's 128 rows went through one
@@ -763,6 +765,7 @@ struct Bucket {
   int f64 = 0, waves = 4, cpl = 2, rows = 4, aligned = 1;
   int per_cu = 2;
   bool narrow = false;      // k_brows: rows of at most kBrRowBytes, any type and alignment
+  bool mixed = false;       // of all widths in one launch: k_brows without a choice
   int64_t tile_rows = 256;
   std::vector<int> insts;
   BTile* tiles = nullptr;   // device (inside the batch buffer)
@@ -894,8 +897,12 @@ inline size_t au(size_t x) { return (x + 255) / 256 * 256; }
 
 int cover_of(int waves, int cpl, int vn) { return waves * 64 * cpl * vn; }
 
+constexpr int64_t kFinest = 128;   // finest tiling the tuner may choose
+
 // candidate launch shapes for a bucket whose widest instance has d_max columns
-std::vector<Bucket> bucket_candidates(const Bucket& base, int d_max, int num_cu) {
+// and whose instances have `finest` tiles of kFinest rows: k_brows where the
+// rows allow it, then, unless the bucket is mixed, the shapes of k_bgram
+std::vector<Bucket> bucket_candidates(const Bucket& base, int d_max, int64_t finest, int num_cu) {
   static const int shapes[][3] = {{1, 2, 4}, {1, 2, 8}, {2, 2, 4}, {2, 2, 8}, {4, 2, 4},
                                   {4, 2, 8}, {8, 2, 4}, {8, 2, 8}, {1, 3, 2}, {2, 3, 2},
                                   {4, 3, 2}, {8, 3, 2}, {1, 4, 2}, {2, 4, 2}, {4, 4, 2},
@@ -907,6 +914,17 @@ std::vector<Bucket> bucket_candidates(const Bucket& base, int d_max, int num_cu)
     if (c >= d_max && (best < 0 || c < best)) best = c;
   }
   std::vector<Bucket> out;
+  if (base.mixed || (int64_t)d_max * (base.f64 ? 8 : 4) <= kBrRowBytes) {
+    // the finest tiles until they fill the device eight times over (two
+    // workgroups per CU), then longer ones: fewer partial sums to write and
+    // add (a sixteenth of A's bytes each way at 128 rows)
+    Bucket b = base;
+    b.narrow = true;
+    b.tile_rows = kFinest;
+    while (finest * kFinest / b.tile_rows > 16 * (int64_t)num_cu) b.tile_rows *= 2;
+    out.push_back(b);
+    if (base.mixed) return out;
+  }
   for (auto& sh : shapes) {
     const int c = cover_of(sh[0], sh[1], vn);
     if (c < d_max || c > 2 * best) continue;
@@ -947,9 +965,6 @@ void make_tiles(const Bucket& b, const std::vector<BInst>& h, std::vector<BTile>
   }
 }
 
-// Lay out the batch: per-instance vectors, partial sums sized for the finest
-constexpr int64_t kFinest = 128;   // finest tiling the tuner may choose
-
 // device bytes of one instance's vectors and partial sums in the batch buffer
 size_t inst_bytes(int64_t n, int64_t d) {
   const int G = (int)((n + kFinest - 1) / kFinest);
@@ -960,6 +975,7 @@ size_t inst_bytes(int64_t n, int64_t d) {
          au(sizeof(double) * kNS * ((d + 255) / 256));
 }
 
+// Lay out the batch: per-instance vectors, partial sums sized for the finest
 // tiling, tile and item lists; bucket the instances by row width.
 nys_status batch_build(nys_ctx ctx, int count, const nys_problem* P, const nys_admm_opts* O,
                        nys_factor* F, nys_admm_state* S, int max_iter, Batch* B) {
@@ -971,11 +987,22 @@ nys_status batch_build(nys_ctx ctx, int count, const nys_problem* P, const nys_a
     off[q] = bytes;
     bytes += inst_bytes(P[q].A.n, P[q].A.d);
   }
-  // buckets by row width
+  // Buckets by row width.  A batch that stays in the memory-side cache has all
+  // its narrow instances in one k_brows launch; one that streams from HBM has
+  // them by width too, with k_brows as one of the shapes to time, because which
+  // is faster there depends on how the columns fill the lanes.  A solve of 48
+  // passes, k_brows / the best of k_bgram (ms): 2.4 GB 2 x 230769 x 1300 30.0 /
+  // 24.1, 16 x 187500 x 100 FP64 43.2 / 34.5, 2 x 1000000 x 300 19.5 / 19.8;
+  // 150 MB 2 x 93750 x 200 3.8 / 4.8, 2 x 93750 x 100 FP64 4.4 / 4.8 (never
+  // slower at 60 and 150 MB).
+  int64_t a_bytes = 0;
+  for (int q = 0; q < count; ++q)
+    a_bytes += P[q].A.n * P[q].A.ld * (P[q].A.dtype == NYS_F64 ? 8 : 4);
+  const bool streams = a_bytes > kCachedBytes;
   std::map<std::pair<int, int>, std::vector<int>> groups;   // (f64|aligned, cover class)
   for (int q = 0; q < count; ++q) {
     const nys_dense& A = P[q].A;
-    if (brows_ok(A)) {
+    if (brows_ok(A) && !streams) {
       groups[{-1, 0}].push_back(q);
       continue;
     }
@@ -1103,21 +1130,12 @@ nys_status batch_build(nys_ctx ctx, int count, const nys_problem* P, const nys_a
       d_max = std::max(d_max, B->h[q].d);
       finest_tiles += (P[q].A.n + kFinest - 1) / kFinest;
     }
-    if (g.first.first < 0) {
-      // the finest tiles until they fill the device eight times over (two
-      // workgroups per CU), then longer ones: fewer partial sums to write and
-      // add (a sixteenth of A's bytes each way at 128 rows)
-      b.narrow = true;
-      b.tile_rows = kFinest;
-      while (finest_tiles * kFinest / b.tile_rows > 16 * (int64_t)ctx->num_cu) b.tile_rows *= 2;
-      b.tiles = tiles_dev + tile_cursor;
-      tile_cursor += (size_t)finest_tiles;
-      B->buckets.push_back(b);
-      continue;
+    b.mixed = g.first.first < 0;
+    if (!b.mixed) {
+      b.f64 = (g.first.first & 2) ? 1 : 0;
+      b.aligned = g.first.first & 1;
     }
-    b.f64 = (g.first.first & 2) ? 1 : 0;
-    b.aligned = g.first.first & 1;
-    std::vector<Bucket> c = bucket_candidates(b, d_max, ctx->num_cu);
+    std::vector<Bucket> c = bucket_candidates(b, d_max, finest_tiles, ctx->num_cu);
     if (c.empty()) return NYS_ERR_INVALID;
     b = c[0];
     b.tiles = tiles_dev + tile_cursor;
@@ -1162,13 +1180,17 @@ nys_status batch_tune(nys_ctx ctx, Batch* B) {
   NYS_TRY_HIP(hipEventCreate(&e0));
   NYS_TRY_HIP(hipEventCreate(&e1));
   for (Bucket& bk : B->buckets) {
-    if (bk.narrow) {
+    if (bk.mixed) {
       NYS_TRY(upload_tiles(ctx, &bk, B->h, ctx->num_cu));
       for (int q : bk.insts) B->h[q].G = (int)((B->h[q].n + bk.tile_rows - 1) / bk.tile_rows);
       continue;
     }
     int d_max = 0;
-    for (int q : bk.insts) d_max = std::max(d_max, B->h[q].d);
+    int64_t finest = 0;
+    for (int q : bk.insts) {
+      d_max = std::max(d_max, B->h[q].d);
+      finest += (B->h[q].n + kFinest - 1) / kFinest;
+    }
     std::string key = "batch|" + std::to_string(bk.f64) + "|" + std::to_string(bk.aligned);
     for (int q : bk.insts)
       key += "|" + std::to_string(B->h[q].n) + "x" + std::to_string(B->h[q].d);
@@ -1176,6 +1198,7 @@ nys_status batch_tune(nys_ctx ctx, Batch* B) {
     std::vector<Bucket> cands;
     if (hit != ctx->bplans.end()) {
       Bucket b = bk;
+      b.narrow = hit->second[0] == 0;
       b.waves = hit->second[0];
       b.cpl = hit->second[1];
       b.rows = hit->second[2];
@@ -1183,7 +1206,8 @@ nys_status batch_tune(nys_ctx ctx, Batch* B) {
       b.tile_rows = hit->second[4];
       cands.push_back(b);
     } else {
-      cands = bucket_candidates(bk, d_max, ctx->num_cu);
+      bk.narrow = false;
+      cands = bucket_candidates(bk, d_max, finest, ctx->num_cu);
       const char* tune = getenv("NYSADMM_TUNE");
       if (tune != nullptr && tune[0] == '0') cands.resize(1);
     }
@@ -1213,12 +1237,12 @@ nys_status batch_tune(nys_ctx ctx, Batch* B) {
     }
     NYS_TRY(upload_tiles(ctx, &bestb, B->h, ctx->num_cu));
     bk = bestb;
-    ctx->bplans[key] = {bk.waves, bk.cpl, bk.rows, bk.per_cu, (int)bk.tile_rows};
+    ctx->bplans[key] = {bk.narrow ? 0 : bk.waves, bk.cpl, bk.rows, bk.per_cu, (int)bk.tile_rows};
     if (getenv("NYSADMM_VERBOSE"))
-      fprintf(stderr, "nysadmm: batched bucket (%zu instances, d <= %d): waves %d, chunks %d, "
+      fprintf(stderr, "nysadmm: batched bucket (%zu instances, d <= %d): %s, waves %d, chunks %d, "
               "rows %d, %d wg/CU, tile %lld rows, %d tiles (%.1f us)\n", bk.insts.size(), d_max,
-              bk.waves, bk.cpl, bk.rows, bk.per_cu, (long long)bk.tile_rows, bk.ntiles,
-              cands.size() > 1 ? 1e3 * best / 2 : -1.0);
+              bk.narrow ? "blocks of rows" : "rows in turn", bk.waves, bk.cpl, bk.rows, bk.per_cu,
+              (long long)bk.tile_rows, bk.ntiles, cands.size() > 1 ? 1e3 * best / 2 : -1.0);
     // the partial-sum count of each instance follows the chosen tiling
     for (int q : bk.insts) B->h[q].G = (int)((B->h[q].n + bk.tile_rows - 1) / bk.tile_rows);
   }
