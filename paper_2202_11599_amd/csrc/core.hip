@@ -1627,9 +1627,10 @@ __global__ __launch_bounds__(R / kJP * kJT) void k_jacobi_small(
 // share of the CU's address unit, which four SIMDs use and which a 16 x 16
 // operand block holds for 64 cycles (k-contiguous FP32, 16 rows of 64 bytes)
 // to 128 (FP64); a unit alone on its SIMD waits for its
-// loads besides (about 1400 cycles for the steps in flight).  1024 SIMDs take
-// the units in turn, a unit starts with about 2500 cycles of latency, and a
-// split adds a launch and the partial sums' way through the caches.  The
+// loads besides (about 1400 cycles for the steps in flight).  The device's SIMDs
+// take the units in turn, a unit starts with about 2500 cycles of latency, and a
+// split adds a launch and the partial sums' way through the caches (cycles,
+// clock and bytes per second as fitted on an MI355X with all its 256 CUs).  The
 // cheapest shape that the planned partial-sum buffer holds is taken: 2000 x 100 x 20000
 // (A^T T, FP32 A) 187 us with 16 chunks of 32 x 64 tiles, 236 with 25 (a fourth
 // turn of the SIMDs for the last units); 6000 x 300 x 6000 418 us unsplit, 470
@@ -1643,7 +1644,10 @@ struct GemmShape {
   int RB, NBT, S, kchunk;
   bool nat;
 };
-static GemmShape gemm64_shape(int M, int N, int K, double ta_a, double ta_b, size_t split_elems) {
+static GemmShape gemm64_shape(int M, int N, int K, double ta_a, double ta_b, size_t split_elems,
+                              int num_cu) {
+  constexpr double kCyclesPerUs = 2400.0, kBytesPerUs = 3e6;
+  const double simds = 4.0 * num_cu;
   const int nblk = (N + 15) / 16;
   GemmShape best{1, std::min(kGemmNB, nblk), 1, std::max(16, (K + 15) / 16 * 16), true};
   if (K <= 0) return best;
@@ -1675,10 +1679,10 @@ static GemmShape gemm64_shape(int M, int N, int K, double ta_a, double ta_b, siz
         last_kc = kc;
         const int Se = (K + kc - 1) / kc;
         const double units = (double)MT * NT * Se;
-        const double w = units / 1024.0;
+        const double w = units / simds;
         const double turns = w > 1.0 ? 0.5 * (std::ceil(0.98 * w) + w + 0.35) : 1.0;
-        double us = (turns * (kc / 16) * (units > 1024 ? busy : alone) + 2500.0) / 2400.0;
-        if (Se > 1) us += 4.0 + 2.0 * Se * 8.0 * (double)M * N / 3e6;
+        double us = (turns * (kc / 16) * (units > simds ? busy : alone) + 2500.0) / kCyclesPerUs;
+        if (Se > 1) us += 4.0 + 2.0 * Se * 8.0 * (double)M * N / kBytesPerUs;
         if (us < best_us) {
           best_us = us;
           best = GemmShape{RB, std::min(NB, nblk), Se, kc, fixed};
@@ -1689,11 +1693,12 @@ static GemmShape gemm64_shape(int M, int N, int K, double ta_a, double ta_b, siz
   return best;
 }
 
-nys_status gemm64(hipStream_t st, int M, int N, int K, const void* A, bool a_f32, int64_t sam,
+nys_status gemm64(nys_ctx ctx, int M, int N, int K, const void* A, bool a_f32, int64_t sam,
                   int64_t sak, const void* B, bool b_f32, int64_t sbk, int64_t sbn, double* C,
                   int64_t scm, int64_t scn, double alpha, double beta, const SplitBuf& split,
                   const double* wk, const double* A2, double ca) {
   if (M <= 0 || N <= 0) return NYS_OK;
+  hipStream_t st = ctx->stream;
   if (scm != 1 && scn == 1) {
     // row-major C: the kernel stores along m, so form C^T = B^T A^T
     if (A2 != nullptr) return NYS_ERR_INVALID;
@@ -1709,7 +1714,7 @@ nys_status gemm64(hipStream_t st, int M, int N, int K, const void* A, bool a_f32
   const bool akc = sak == 1, bkc = sbk == 1 && !(A2 != nullptr && sbn == 1);
   const GemmShape sh = gemm64_shape(M, N, K, akc ? (a_f32 ? 1.0 : 2.0) : 1.0,
                                     bkc ? (b_f32 ? 1.0 : 2.0) : 1.5,
-                                    split.ptr != nullptr ? split.plan : 0);
+                                    split.ptr != nullptr ? split.plan : 0, ctx->num_cu);
   // panels of C whose partials fit the buffer (all of C as a rule)
   int pm = M, pn = N;
   if (sh.S > 1 && (size_t)sh.S * M * N > split.elems) {

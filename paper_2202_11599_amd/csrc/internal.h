@@ -330,7 +330,7 @@ struct SplitBuf {
   double* ptr = nullptr;
   size_t elems = 0, plan = 0;
 };
-nys_status gemm64(hipStream_t st, int M, int N, int K, const void* A, bool a_f32, int64_t sam,
+nys_status gemm64(nys_ctx ctx, int M, int N, int K, const void* A, bool a_f32, int64_t sam,
                   int64_t sak, const void* B, bool b_f32, int64_t sbk, int64_t sbn, double* C,
                   int64_t scm, int64_t scn, double alpha, double beta, const SplitBuf& split,
                   const double* wk = nullptr, const double* A2 = nullptr, double ca = 0.0);

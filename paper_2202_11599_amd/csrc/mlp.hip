@@ -390,13 +390,13 @@ nys_status ws_forward(nys_ctx ctx, nys_ws_model m, const double* X, int64_t B, A
   WsPtrs p = ws_ptrs(m, m->params.as<double>());
   hipLaunchKernelGGL(k_standardise, dim3(blocks(B * ni)), dim3(256), 0, st, X, p.mu, p.sig, B, ni,
                      a->Xn);
-  NYS_TRY(gemm64(st, (int)B, h, ni, a->Xn, false, ni, 1, p.W1, false, h, 1, a->A1, h, 1, 1.0, 0.0,
+  NYS_TRY(gemm64(ctx, (int)B, h, ni, a->Xn, false, ni, 1, p.W1, false, h, 1, a->A1, h, 1, 1.0, 0.0,
                  SplitBuf{}));
   hipLaunchKernelGGL(k_bias_gelu, dim3(blocks(B * h)), dim3(256), 0, st, a->A1, p.b1, B, h, a->H1);
-  NYS_TRY(gemm64(st, (int)B, h, h, a->H1, false, h, 1, p.W2, false, h, 1, a->A2, h, 1, 1.0, 0.0,
+  NYS_TRY(gemm64(ctx, (int)B, h, h, a->H1, false, h, 1, p.W2, false, h, 1, a->A2, h, 1, 1.0, 0.0,
                  SplitBuf{}));
   hipLaunchKernelGGL(k_bias_gelu, dim3(blocks(B * h)), dim3(256), 0, st, a->A2, p.b2, B, h, a->H2);
-  NYS_TRY(gemm64(st, (int)B, no, h, a->H2, false, h, 1, p.W3, false, no, 1, a->O, no, 1, 1.0, 0.0,
+  NYS_TRY(gemm64(ctx, (int)B, no, h, a->H2, false, h, 1, p.W3, false, no, 1, a->O, no, 1, 1.0, 0.0,
                  SplitBuf{}));
   hipLaunchKernelGGL(k_bias, dim3(blocks(B * no)), dim3(256), 0, st, a->O, p.b3, B, no);
   return hipGetLastError() == hipSuccess ? NYS_OK : NYS_ERR_HIP;
@@ -414,21 +414,21 @@ nys_status ws_backward(nys_ctx ctx, nys_ws_model m, const double* Tg, const doub
                      a->part);
   hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, st, a->part, (int)nb, loss_dev);
   // layer 3
-  NYS_TRY(gemm64(st, h, no, (int)B, a->H2, false, 1, h, a->G, false, no, 1, g.W3, no, 1, 1.0, 0.0,
+  NYS_TRY(gemm64(ctx, h, no, (int)B, a->H2, false, 1, h, a->G, false, no, 1, g.W3, no, 1, 1.0, 0.0,
                  SplitBuf{}));
   hipLaunchKernelGGL(k_colsum, dim3(blocks(no)), dim3(256), 0, st, a->G, B, no, g.b3);
-  NYS_TRY(gemm64(st, (int)B, h, no, a->G, false, no, 1, p.W3, false, 1, no, a->gH, h, 1, 1.0, 0.0,
+  NYS_TRY(gemm64(ctx, (int)B, h, no, a->G, false, no, 1, p.W3, false, 1, no, a->gH, h, 1, 1.0, 0.0,
                  SplitBuf{}));
   hipLaunchKernelGGL(k_gelu_back, dim3(blocks(B * h)), dim3(256), 0, st, a->gH, a->A2, B * h, a->gA);
   // layer 2
-  NYS_TRY(gemm64(st, h, h, (int)B, a->H1, false, 1, h, a->gA, false, h, 1, g.W2, h, 1, 1.0, 0.0,
+  NYS_TRY(gemm64(ctx, h, h, (int)B, a->H1, false, 1, h, a->gA, false, h, 1, g.W2, h, 1, 1.0, 0.0,
                  SplitBuf{}));
   hipLaunchKernelGGL(k_colsum, dim3(blocks(h)), dim3(256), 0, st, a->gA, B, h, g.b2);
-  NYS_TRY(gemm64(st, (int)B, h, h, a->gA, false, h, 1, p.W2, false, 1, h, a->gH, h, 1, 1.0, 0.0,
+  NYS_TRY(gemm64(ctx, (int)B, h, h, a->gA, false, h, 1, p.W2, false, 1, h, a->gH, h, 1, 1.0, 0.0,
                  SplitBuf{}));
   hipLaunchKernelGGL(k_gelu_back, dim3(blocks(B * h)), dim3(256), 0, st, a->gH, a->A1, B * h, a->gA);
   // layer 1
-  NYS_TRY(gemm64(st, ni, h, (int)B, a->Xn, false, 1, ni, a->gA, false, h, 1, g.W1, h, 1, 1.0, 0.0,
+  NYS_TRY(gemm64(ctx, ni, h, (int)B, a->Xn, false, 1, ni, a->gA, false, h, 1, g.W1, h, 1, 1.0, 0.0,
                  SplitBuf{}));
   hipLaunchKernelGGL(k_colsum, dim3(blocks(h)), dim3(256), 0, st, a->gA, B, h, g.b1);
   return hipGetLastError() == hipSuccess ? NYS_OK : NYS_ERR_HIP;

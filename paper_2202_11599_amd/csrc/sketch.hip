@@ -850,18 +850,18 @@ nys_status orthonormalize(nys_ctx ctx, double* Om, int64_t d, int m, const CoreW
   // back together
   double* err_dev = reinterpret_cast<double*>(w.ints + 2);
   NYS_TRY_HIP(hipMemsetAsync(w.ints, 0, sizeof(int), st));
-  NYS_TRY(gemm64(st, m, m, (int)d, Om, false, d, 1, Om, false, 1, d, w.M, m, 1, 1.0, 0.0,
+  NYS_TRY(gemm64(ctx, m, m, (int)d, Om, false, d, 1, Om, false, 1, d, w.M, m, 1, 1.0, 0.0,
                  w.split));
   double err = 0.0;
   for (int pass = 0; pass < 2; ++pass) {
     NYS_TRY(chol_upper(st, w.M, m, m, w.ints));
     NYS_TRY(trinv_upper(st, w.M, m, m, w.Cinv, m));
     // Bm = Om Rinv  (d x m col-major), then copy back
-    NYS_TRY(gemm64(st, (int)d, m, m, Om, false, 1, d, w.Cinv, false, m, 1, tmp, 1, d, 1.0, 0.0,
+    NYS_TRY(gemm64(ctx, (int)d, m, m, Om, false, 1, d, w.Cinv, false, m, 1, tmp, 1, d, 1.0, 0.0,
                    w.split));
     NYS_TRY_HIP(hipMemcpyAsync(Om, tmp, sizeof(double) * d * m, hipMemcpyDeviceToDevice, st));
     // Q^T Q: the acceptance test, and the next pass's Gram
-    NYS_TRY(gemm64(st, m, m, (int)d, Om, false, d, 1, Om, false, 1, d, w.M, m, 1, 1.0, 0.0,
+    NYS_TRY(gemm64(ctx, m, m, (int)d, Om, false, d, 1, Om, false, 1, d, w.M, m, 1, 1.0, 0.0,
                    w.split));
     hipLaunchKernelGGL(k_orth_err, dim3(1), dim3(1024), 0, st, w.M, m, err_dev);
     unsigned char hb[16];
@@ -892,16 +892,16 @@ nys_status nys_core(nys_ctx ctx, nys_factor F, double test_mu, int* above) {
   const double* Y = F->Y.as<double>();
   const double* Om = F->Omega.as<double>();
   // ||Y||_2 = sqrt(lambda_max(Y^T Y))
-  NYS_TRY(gemm64(st, r, r, (int)d, Y, false, d, 1, Y, false, 1, d, w.GY, r, 1, 1.0, 0.0, w.split));
+  NYS_TRY(gemm64(ctx, r, r, (int)d, Y, false, d, 1, Y, false, 1, d, w.GY, r, 1, 1.0, 0.0, w.split));
   NYS_TRY(power_iter(st, w.GY, r, r, 300, w.scal));
   // Omega^T Omega
-  NYS_TRY(gemm64(st, r, r, (int)d, Om, false, d, 1, Om, false, 1, d, w.GO, r, 1, 1.0, 0.0,
+  NYS_TRY(gemm64(ctx, r, r, (int)d, Om, false, d, 1, Om, false, 1, d, w.GO, r, 1, 1.0, 0.0,
                  w.split));
   // base core matrix Omega^T Y (FP64 form; also for an explicit symmetric
   // matrix) or the stored T^T D T + c Omega^T Omega
   const double* base;
   if (F->prec == NYS_F64 || F->sym || F->sparse) {
-    NYS_TRY(gemm64(st, r, r, (int)d, Om, false, d, 1, Y, false, 1, d, w.G, r, 1, 1.0, 0.0,
+    NYS_TRY(gemm64(ctx, r, r, (int)d, Om, false, d, 1, Y, false, 1, d, w.G, r, 1, 1.0, 0.0,
                    w.split));
     base = w.G;
   } else {
@@ -929,16 +929,16 @@ nys_status nys_core(nys_ctx ctx, nys_factor F, double test_mu, int* above) {
   // at 20000 x 800); up to 64 the two products are added, the order of
   // summation that small ranks keep (see gemm64_shape)
   if (r > 64) {
-    NYS_TRY(gemm64(st, (int)d, r, r, Y, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, 1.0, 0.0,
+    NYS_TRY(gemm64(ctx, (int)d, r, r, Y, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, 1.0, 0.0,
                    w.split, nullptr, Om, nu));
   } else {
-    NYS_TRY(gemm64(st, (int)d, r, r, Y, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, 1.0, 0.0,
+    NYS_TRY(gemm64(ctx, (int)d, r, r, Y, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, 1.0, 0.0,
                    w.split));
-    NYS_TRY(gemm64(st, (int)d, r, r, Om, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, nu, 1.0,
+    NYS_TRY(gemm64(ctx, (int)d, r, r, Om, false, 1, d, w.Cinv, false, r, 1, w.Bm, 1, d, nu, 1.0,
                    w.split));
   }
   // G = B^T B, eigendecomposition G = V Sigma^2 V^T
-  NYS_TRY(gemm64(st, r, r, (int)d, w.Bm, false, d, 1, w.Bm, false, 1, d, w.G, r, 1, 1.0, 0.0,
+  NYS_TRY(gemm64(ctx, r, r, (int)d, w.Bm, false, d, 1, w.Bm, false, 1, d, w.G, r, 1, 1.0, 0.0,
                  w.split));
   if (test_mu >= 0.0) {
     // inertia of G - (nu + test_mu) I through one Cholesky attempt
@@ -965,7 +965,7 @@ nys_status nys_core(nys_ctx ctx, nys_factor F, double test_mu, int* above) {
   const double* Gj = w.G;
   if (F->basis_hint != nullptr) {
     double* Vb = w.GO;   // r x r column-major (free after the shifted Cholesky)
-    NYS_TRY(gemm64(st, r, r, (int)d, w.Bm, false, d, 1, F->basis_hint, false, 1, d, Vb, 1, r,
+    NYS_TRY(gemm64(ctx, r, r, (int)d, w.Bm, false, d, 1, F->basis_hint, false, 1, d, Vb, 1, r,
                    1.0, 0.0, w.split));
     double err = 0.0;
     nys_status so = orthonormalize(ctx, Vb, r, r, w, w.W, &err);
@@ -974,9 +974,9 @@ nys_status nys_core(nys_ctx ctx, nys_factor F, double test_mu, int* above) {
     if (so == NYS_OK && !(err <= 1e-13 * r)) so = NYS_ERR_NOT_SPD;
     if (so == NYS_OK) {
       // G' = V0^T (G V0): T1 (column-major) in GY, G' (row-major) in M
-      NYS_TRY(gemm64(st, r, r, r, w.G, false, r, 1, Vb, false, 1, r, w.GY, 1, r, 1.0, 0.0,
+      NYS_TRY(gemm64(ctx, r, r, r, w.G, false, r, 1, Vb, false, 1, r, w.GY, 1, r, 1.0, 0.0,
                      w.split));
-      NYS_TRY(gemm64(st, r, r, r, Vb, false, r, 1, w.GY, false, 1, r, w.M, r, 1, 1.0, 0.0,
+      NYS_TRY(gemm64(ctx, r, r, r, Vb, false, r, 1, w.GY, false, 1, r, w.M, r, 1, 1.0, 0.0,
                      w.split));
       V0 = Vb;
       Gj = w.M;
@@ -992,7 +992,7 @@ nys_status nys_core(nys_ctx ctx, nys_factor F, double test_mu, int* above) {
                                                                           : "identity"));
   // U = B V Sigma^-1
   NYS_TRY(F->U.reserve(sizeof(double) * d * r));
-  NYS_TRY(gemm64(st, (int)d, r, r, w.Bm, false, 1, d, w.W, false, r, 1, F->U.as<double>(), 1, d,
+  NYS_TRY(gemm64(ctx, (int)d, r, r, w.Bm, false, 1, d, w.W, false, r, 1, F->U.as<double>(), 1, d,
                  1.0, 0.0, w.split));
   NYS_TRY(F->lam.reserve(sizeof(double) * r));
   hipLaunchKernelGGL(k_lambda, dim3(blocks(r)), dim3(256), 0, st, w.sig2, nu, r,
@@ -1223,7 +1223,7 @@ nys_status sketch_block(nys_ctx ctx, const nys_dense& A, const double* D, double
     // explicit symmetric H = A + c I (kernel SVM): Y = A Omega + c Omega, FP64 sums
     NYS_TRY_HIP(hipMemcpyAsync(Y + d * r0, Om, sizeof(double) * d * m, hipMemcpyDeviceToDevice, st));
     const NSplit split(w, d, std::max(r1, m));
-    NYS_TRY(gemm64(st, (int)n, m, (int)d, A.data, a32, A.ld, 1, Om, false, 1, d, Y + d * r0, 1, d,
+    NYS_TRY(gemm64(ctx, (int)n, m, (int)d, A.data, a32, A.ld, 1, Om, false, 1, d, Y + d * r0, 1, d,
                    1.0, c, split.get()));
   } else if (F->sym) {
     // the same in FP32: Omega rounded to FP32 (the rounded values written
@@ -1245,11 +1245,11 @@ nys_status sketch_block(nys_ctx ctx, const nys_dense& A, const double* D, double
     // T = A Omega (n x m, column-major) in FP64 tiles, Y = A^T (D o T) + c Omega
     NYS_TRY(ctx->gemm_ws.reserve(sizeof(double) * n * m + 256));
     double* T = ctx->gemm_ws.as<double>();
-    NYS_TRY(gemm64(st, (int)n, m, (int)d, A.data, a32, A.ld, 1, Om, false, 1, d, T, 1, n, 1.0, 0.0,
+    NYS_TRY(gemm64(ctx, (int)n, m, (int)d, A.data, a32, A.ld, 1, Om, false, 1, d, T, 1, n, 1.0, 0.0,
                    w.split));
     NYS_TRY_HIP(hipMemcpyAsync(Y + d * r0, Om, sizeof(double) * d * m, hipMemcpyDeviceToDevice, st));
     const NSplit split(w, d, std::max(r1, m));
-    NYS_TRY(gemm64(st, (int)d, m, (int)n, A.data, a32, 1, A.ld, T, false, 1, n, Y + d * r0, 1, d,
+    NYS_TRY(gemm64(ctx, (int)d, m, (int)n, A.data, a32, 1, A.ld, T, false, 1, n, Y + d * r0, 1, d,
                    1.0, c, split.get(), D));
   } else {
     if (!a32) return NYS_ERR_INVALID;
@@ -1298,11 +1298,11 @@ nys_status sketch_block(nys_ctx ctx, const nys_dense& A, const double* D, double
       hipLaunchKernelGGL(k_gram_t_reduce, dim3(blocks((int64_t)r1 * m)), dim3(256), 0, st, Wp,
                          gs.G, r1, r0, m, sym, Mb, ldm);
     } else {
-      NYS_TRY(gemm64(st, r1, m, (int)n, T, true, ldt, 1, T + ldt * r0, true, 1, ldt, Mb + r0, ldm,
+      NYS_TRY(gemm64(ctx, r1, m, (int)n, T, true, ldt, 1, T + ldt * r0, true, 1, ldt, Mb + r0, ldm,
                      1, 1.0, 0.0, w.split, D));
     }
     if (c != 0.0)
-      NYS_TRY(gemm64(st, r1, m, (int)d, F->Omega.ptr, false, d, 1, Om, false, 1, d, Mb + r0, ldm,
+      NYS_TRY(gemm64(ctx, r1, m, (int)d, F->Omega.ptr, false, d, 1, Om, false, 1, d, Mb + r0, ldm,
                      1, c, 1.0, w.split));
     hipLaunchKernelGGL(k_mirror_cols, dim3(blocks((int64_t)r1 * m)), dim3(256), 0, st, Mb, ldm, r0,
                        r1);

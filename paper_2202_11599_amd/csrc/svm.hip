@@ -460,7 +460,7 @@ nys_status nys_kernel_rbf(nys_ctx ctx, const float* X, int64_t n, int64_t p, int
   for (int64_t i0 = 0; i0 < n; i0 += blk) {
     const int64_t rows = std::min(blk, n - i0);
     // G = X[i0 : i0 + rows] X^T  (FP64 products and sums of the FP32 features)
-    NYS_TRY(gemm64(st, (int)rows, (int)n, (int)p, X + i0 * ldx, true, ldx, 1, X, true, 1, ldx, G,
+    NYS_TRY(gemm64(ctx, (int)rows, (int)n, (int)p, X + i0 * ldx, true, ldx, 1, X, true, 1, ldx, G,
                    n, 1, 1.0, 0.0, SplitBuf{}));
     hipLaunchKernelGGL(k_rbf_rows, dim3(blocks256(rows * n)), dim3(256), 0, st, G, rows, n, i0,
                        sq, b, gamma, H, ldh);
