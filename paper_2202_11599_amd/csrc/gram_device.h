@@ -157,14 +157,12 @@ __device__ __forceinline__ void realign_group(typename Chunk<T>::V (&a)[R][CPL],
 
 // Row dots of one group, cross-wave reduction, epilogue, and the A^T update.
 // The R row sums of a wavefront are formed together in the vector ALU
-// (wave_sums), except for LSUM: there each is a butterfly of LDS permutes with
-// the same bits.  Four wavefronts of four aligned chunks a row (up to 4096
-// FP32 columns) wait for memory with the vector ALU as the next limit, so the
-// permutes' idle LDS unit is the better place: 100000 x 4000 takes 248 us
-// against 250.  Everything else is faster in the ALU (us, permutes / ALU:
-// 99999 x 4001 unaligned 298 / 276, 60000 x 5000 244 / 219, 60000 x 6000
-// 257 / 230, 50000 x 8000 272 / 255, 60000 x 3000 124 / 120).
-template <typename T, int WAVES, int CPL, int R, bool LSUM = false>
+// (wave_sums), with the bits of a butterfly of LDS permutes for each.  Pair in
+// us, permutes / ALU: 99999 x 4001 unaligned 298 / 276, 60000 x 5000 244 / 219,
+// 60000 x 6000 257 / 230, 50000 x 8000 272 / 255, 20000 x 4000 65.0 / 62.6,
+// 100000 x 3100 206 / 195; of 35 aligned FP32 shapes of 2600 to 4096 columns
+// only 100000 x 4000 is faster with the permutes (247.8 / 249.6), 50000 x 4000 as fast.
+template <typename T, int WAVES, int CPL, int R>
 __device__ __forceinline__ void process_group(
     typename Chunk<T>::V (&a)[R][CPL], const double (&av)[R], int64_t row, int64_t r1, int mode,
     const double (&pr)[CPL][Chunk<T>::N], double (&yr)[CPL][Chunk<T>::N], double& q,
@@ -183,13 +181,9 @@ __device__ __forceinline__ void process_group(
       for (int m = 0; m < CPL; ++m)
 #pragma unroll
         for (int v = 0; v < VN; ++v) acc = fma((double)a[i][m][v], pr[m][v], acc);
-      if (LSUM) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-      }
       t[i] = acc;
     }
-    if (!LSUM) wave_sums(t);
+    wave_sums(t);
     // The FP64 copies made for the dot products die here: the A^T pass
     // converts the stored row again instead of keeping twice the registers
     // live across the barrier.
