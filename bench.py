@@ -822,7 +822,7 @@ def bench_path(args, N, synth, torch):
     # the captured PCG graphs: one batched pair launch per row-width bucket
     # over all instances (all stay active through the fixed 50 iterations)
     out["roofline"] = roofline(prof, total_bytes, None, None)
-    out["roofline"]["kernel"] = ("k_bgram (batched fused pair, one launch per row-width bucket; "
+    out["roofline"]["kernel"] = ("k_bgram, k_brows (batched fused pair, one launch per row-width bucket; "
                                  "timed over the true-residual passes)")
     out["roofline"]["traffic"] = None
     out["roofline"]["alg_bytes_per_launch_note"] = "sum over instances of n_i d_i 4 bytes"

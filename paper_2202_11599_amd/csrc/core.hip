@@ -1,5 +1,5 @@
 // FP64 kernels of the Nystrom core (Algorithm RandNysAppx after the sketch):
-// tiled FP64 GEMM, in-place upper Cholesky, upper triangular inverse, power
+// FP64 GEMM, in-place upper Cholesky, upper triangular inverse, power
 // iteration for ||Y||_2, two-sided block Jacobi eigensolver, eigenpair sort.
 // All of them are small (r <= 1024) and latency bound; they run once per
 // sketch, never inside the PCG loop.
@@ -29,9 +29,9 @@ namespace {
 // sums run in ascending k whatever the layout); without, MFMA s sums the k's
 // k0 + s + 4 row, in either operand.  The MFMA's
 // rows are n and its columns m: a store instruction writes 16 consecutive m.
-// Measured on A Omega and A^T T at 20000 x 2000, 100 columns, FP32 A: 250
-// and 187 us, 32 and 43 TFLOP/s (64 x 64 tiles through LDS with two barriers
-// per 16 k before: 1.22 ms each); 20000 x 800 x 800 in FP64 486 us, 53 TFLOP/s
+// Measured in the sketch of 20000 x 2000, 100 columns, FP32 A: A Omega 241 us,
+// A^T T 262, 33 and 30 TFLOP/s (64 x 64 tiles through LDS with two barriers
+// per 16 k before: 1.22 ms each); 20000 x 800 x 800 in FP64 516 us, 50 TFLOP/s
 // (1.1 ms before); 2000 x 50 x 500 13 us (75 before).
 typedef double d4 __attribute__((ext_vector_type(4)));
 // vectors at element alignment: the hardware takes them at any 4-byte boundary
@@ -1632,14 +1632,14 @@ __global__ __launch_bounds__(R / kJP * kJT) void k_jacobi_small(
 // split adds a launch and the partial sums' way through the caches (cycles,
 // clock and bytes per second as fitted on an MI355X with all its 256 CUs).  The
 // cheapest shape that the planned partial-sum buffer holds is taken: 2000 x 100 x 20000
-// (A^T T, FP32 A) 187 us with 16 chunks of 32 x 64 tiles, 236 with 25 (a fourth
-// turn of the SIMDs for the last units); 6000 x 300 x 6000 418 us unsplit, 470
-// with 10 chunks.
+// (A^T T, FP32 A) with buffers for them 187 us with 16 chunks of 32 x 64 tiles, 236
+// with 25 (a fourth turn of the SIMDs for the last units), 262 with the five that
+// 8 MB hold; 6000 x 300 x 6000 418 us unsplit, 470 with 10 chunks.
 // Products of at most 64 rows or columns (the factors of small ranks) sum in
 // ascending k and split K by the count of 64 x 64 tiles, whatever the tile
-// here: PCG runs of 25 and more iterations carry a last-bit change of the
-// factor into the eighth digit of their iterates, and those of low-rank
-// factors are that long, so these keep one order of summation.
+// here: an order kept for its bits, as accurate as the other one.  PCG runs of 25
+// and more iterations carry a last-bit change of the factor into the eighth digit
+// of their iterates, and those of low-rank factors are that long.
 struct GemmShape {
   int RB, NBT, S, kchunk;
   bool nat;
