@@ -478,6 +478,12 @@ nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out,
     *out = pl;
     return NYS_OK;
   }
+  if (rows) {
+    // nothing can be timed on a stream that is being captured
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    NYS_TRY_HIP(hipStreamIsCapturing(ctx->stream, &cap));
+    if (cap != hipStreamCaptureStatusNone) return NYS_OK;
+  }
   std::vector<GramPlan> cands = gram_candidates(A, ctx->num_cu);
   if (rows) cands.push_back(*out);
   if (cands.empty()) {

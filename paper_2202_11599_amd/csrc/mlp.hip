@@ -11,7 +11,7 @@
 // with Adam (bias-corrected).
 //
 // Precisions (nys_ws_set_precision):
-//   FP64  everything FP64: the library's tiled FP64 GEMM and the elementwise
+//   FP64  everything FP64: the library's FP64 GEMM and the elementwise
 //         kernels here (the form that matches the FP64 oracle to rounding);
 //   FP32  FP32 master weights, activations, gradients and Adam state; the
 //         matrix products on FP32 MFMA (16x16x4) with FP32 accumulation;

@@ -81,3 +81,28 @@ def test_streaming_pair_is_timed(N, monkeypatch, capfd, n, d, timed):
     assert ("matvec plan for" in capfd.readouterr().err) == timed
     assert bool((v == float(n) * d).all())   # whole numbers: exact
     ctx.close()
+
+
+def test_first_pair_inside_a_capture(N):
+    """A narrow shape that would be timed is captured on its first call too, in
+    a workspace (nothing is allocated), and the graph replays."""
+    n, d = 300000, 257
+    stream = torch.cuda.Stream()
+    A = torch.randn(n, d, device=DEV, dtype=torch.float32)
+    p = torch.ones(d, device=DEV, dtype=torch.float64)
+    out = torch.zeros_like(p)
+    ctx = N.Context(stream=stream)
+    ctx.set_workspace(torch.empty(ctx.workspace_query(A, 1), dtype=torch.uint8, device=DEV))
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        N.nys_hessian_apply(ctx, A, p, rho=0.5, out=out)
+    for k in range(4):
+        p.copy_(torch.randn(d, device=DEV, dtype=torch.float64))
+        out.fill_(7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = pair_fp64(A, None, p, 0.5)
+        assert float((out - ref).norm() / ref.norm()) < 3e-12, k
+    ctx.close()
