@@ -334,12 +334,17 @@ nys_status check_vector(nys_ctx ctx, const double* v, int64_t n, int kind) {
   return check_end(ctx, c);
 }
 
+// Bytes of the partial sums of a plan's pass (y first, then q)
+size_t gram_part_bytes(const GramPlan& pl) {
+  return align_up(sizeof(double) * (size_t)pl.ny() * pl.ldy) +
+         align_up(sizeof(double) * (size_t)std::max(pl.nq(), 1)) +
+         align_up(sizeof(double) * pl.tmp_doubles());
+}
+
 // Carves the PCG workspace out of the context buffers.
 nys_status pcg_workspace(nys_ctx ctx, const GramPlan& pl, int64_t d, int max_iter, PcgWs* ws) {
   const size_t yb = align_up(sizeof(double) * ((size_t)pl.ny() * pl.ldy));
-  const size_t ypb = yb + align_up(sizeof(double) * (size_t)std::max(pl.nq(), 1)) +
-                     align_up(sizeof(double) * pl.tmp_doubles());
-  NYS_TRY(ctx->ypart.reserve(ypb));
+  NYS_TRY(ctx->ypart.reserve(gram_part_bytes(pl)));
   ws->ypart = ctx->ypart.as<double>();
   ws->qpart = reinterpret_cast<double*>(reinterpret_cast<char*>(ctx->ypart.ptr) + yb);
   const size_t nv = align_up(sizeof(double) * d);
@@ -470,13 +475,19 @@ nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out,
   char key[160];
   snprintf(key, sizeof(key), "%d|%lld|%lld|%lld|%d", (int)A.dtype, (long long)A.n,
            (long long)A.d, (long long)A.ld, (int)aligned);
+  // Whole rows per wavefront need the fewest partial sums: a workspace that
+  // holds no more than those is served with them, timed or not
+  const GramPlan rowplan = rows ? *out : GramPlan{};
+  auto take = [&](const GramPlan& pl) {
+    *out = rows && ctx->ypart.reserve(gram_part_bytes(pl)) != NYS_OK ? rowplan : pl;
+    return NYS_OK;
+  };
   auto it = ctx->plans.find(key);
   if (it != ctx->plans.end()) {
     GramPlan pl = it->second;
     pl.aligned = aligned;
     // the grid depends only on n and the shape; recompute for this pointer
-    *out = pl;
-    return NYS_OK;
+    return take(pl);
   }
   if (rows) {
     // nothing can be timed on a stream that is being captured
@@ -485,7 +496,7 @@ nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out,
     if (cap != hipStreamCaptureStatusNone) return NYS_OK;
   }
   std::vector<GramPlan> cands = gram_candidates(A, ctx->num_cu);
-  if (rows) cands.push_back(*out);
+  if (rows) cands.push_back(rowplan);
   if (cands.empty()) {
     *out = make_gram_plan(A, ctx->num_cu);
     return NYS_OK;
@@ -497,7 +508,9 @@ nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out,
   // scratch: partial sums of the widest candidate, and an input vector of zeros
   DevBuf scratch;
   const size_t yb = align_up(sizeof(double) * (size_t)gmax * ldy);
-  NYS_TRY(scratch.reserve(yb + align_up(sizeof(double) * gmax) + align_up(sizeof(double) * A.d)));
+  const nys_status room = scratch.reserve(yb + align_up(sizeof(double) * gmax) +
+                                          align_up(sizeof(double) * A.d));
+  if (room != NYS_OK) return rows ? NYS_OK : room;
   double* yp = scratch.as<double>();
   double* qp = reinterpret_cast<double*>(static_cast<char*>(scratch.ptr) + yb);
   double* pv = reinterpret_cast<double*>(static_cast<char*>(scratch.ptr) + yb +
@@ -532,8 +545,7 @@ nys_status ctx_gram_plan(nys_ctx ctx, const nys_dense& A, GramPlan* out,
             "grid %d (%.1f us, %zu candidates)\n", (long long)A.n, (long long)A.d, bestp.waves,
             bestp.cpl, bestp.rows, bestp.rowwave ? " (whole rows per wavefront)" : "",
             bestp.per_cu, bestp.grid, 1e3 * best / 3, cands.size());
-  *out = bestp;
-  return NYS_OK;
+  return take(bestp);
 }
 
 nys_status read_pcg_state(nys_ctx ctx, const PcgWs& ws, PcgDev* out) {
@@ -984,10 +996,7 @@ nys_status nys_workspace_query(nys_ctx ctx, const nys_dense* A, int r_max, int c
       c = gram_candidates(*A, ctx->num_cu);
       c.push_back(make_gram_plan(*A, ctx->num_cu));
     }
-    for (const GramPlan& pl : c)
-      part = std::max(part, align_up(sizeof(double) * (size_t)pl.ny() * pl.ldy) +
-                                align_up(sizeof(double) * (size_t)std::max(pl.nq(), 1)) +
-                                align_up(sizeof(double) * pl.tmp_doubles()));
+    for (const GramPlan& pl : c) part = std::max(part, gram_part_bytes(pl));
   }
   total += 2 * part + align_up(sizeof(double) * d);
   // PCG vectors and scalars, H_rho x

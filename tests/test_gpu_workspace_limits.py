@@ -79,3 +79,23 @@ def test_factor_bits_in_every_workspace(N, n, d, r, dtype):
     print(f"[workspace bits] {n} x {d} rank {r}: served {sum(served)} of {len(served)}", flush=True)
     assert served[0] and not served[-1]
     assert served == sorted(served, reverse=True)   # none below the first that is refused
+
+
+def test_streaming_pair_served_with_the_fewest_partial_sums(N):
+    # 300000 x 257 FP32 streams from HBM, so its launch shapes are timed, which
+    # takes their partial sums (up to 2048 rows of 320 doubles, 5.2 MB) once for
+    # the timing and once to keep; whole rows per wavefront leave 256 rows, 0.7 MB,
+    # next to 0.6 MB of vectors
+    n, d = 300000, 257
+    A = torch.randn(n, d, device=DEV, dtype=torch.float32)
+    p = torch.randn(d, device=DEV, dtype=torch.float64)
+    ref = A.double().t().contiguous() @ (A.double() @ p) + 0.5 * p
+    for size in (3 << 20, 8 << 20, 64 << 20):
+        ctx = N.Context()
+        buf = torch.empty(size, dtype=torch.uint8, device=DEV)
+        ctx.set_workspace(buf)
+        for _ in range(2):
+            v = N.nys_hessian_apply(ctx, A, p, rho=0.5)
+            torch.cuda.synchronize()
+            assert float((v - ref).norm() / ref.norm()) < 3e-12, size
+        ctx.close()
