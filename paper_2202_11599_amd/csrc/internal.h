@@ -272,7 +272,9 @@ size_t align_up(size_t x);
 // the fastest of gram_candidates() (and of whole rows per wavefront, where they
 // apply) timed on A itself the first time this (dtype, n, d, ld, alignment) is
 // seen, cached in the context.  NYSADMM_GRAM_PLAN forces a shape ("rows": whole
-// rows per wavefront), NYSADMM_TUNE=0 uses the heuristic.
+// rows per wavefront), NYSADMM_TUNE=0 uses the heuristic.  Narrow rows take whole
+// rows per wavefront untimed where nothing can be timed (a captured stream) or the
+// partial sums of the other shapes do not fit.
 // pending: a begun argument check, ended (and its error returned) before
 // anything is timed.
 struct VecCheck;
@@ -317,11 +319,6 @@ nys_status admm_solve_batched(nys_ctx ctx, int count, const nys_problem* P,
                               const nys_admm_opts* O, nys_admm_state* S, nys_admm_info* I);
 
 // ---- core.hip
-// C(m,n) = alpha sum_k A(m,k) w_k B(k,n) + beta C(m,n) in FP64 (w NULL: 1),
-// A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn], C(m,n) = C[m*scm + n*scn];
-// with A2 the left operand is A + ca A2.  Each operand has unit stride along
-// one of its indices (FP32 operands along k, or m for A; A2: A along m, B along n).
-//
 // Split-K partial sums: the split is chosen for a buffer of `plan` doubles and
 // the partials written to ptr, which holds elems; where they do not fit, the
 // product is formed in panels of C with the same split, so that the order of
@@ -330,6 +327,10 @@ struct SplitBuf {
   double* ptr = nullptr;
   size_t elems = 0, plan = 0;
 };
+// C(m,n) = alpha sum_k A(m,k) w_k B(k,n) + beta C(m,n) in FP64 (w NULL: 1),
+// A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn], C(m,n) = C[m*scm + n*scn];
+// with A2 the left operand is A + ca A2.  Each operand has unit stride along
+// one of its indices (FP32 operands along k, or m for A; A2: A along m, B along n).
 nys_status gemm64(nys_ctx ctx, int M, int N, int K, const void* A, bool a_f32, int64_t sam,
                   int64_t sak, const void* B, bool b_f32, int64_t sbk, int64_t sbn, double* C,
                   int64_t scm, int64_t scn, double alpha, double beta, const SplitBuf& split,
